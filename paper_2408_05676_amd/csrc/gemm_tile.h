@@ -1,0 +1,319 @@
+// LDS-tiled matrix-core GEMM for many activation rows (more than the weight-streaming kernels take):
+//   Y[M][N] = X[M][Kd] * W[N][Kd]^T,  X fp16 (one or two planes), W fp16 or bf16, fp32 accumulate.
+#pragma once
+
+#include "head_part.h"
+#include "mfma.h"
+
+namespace laser {
+
+typedef float float4a4_t __attribute__((ext_vector_type(4), aligned(4)));   // a caller's buffer may be aligned to its elements only
+
+struct GemmTileArgs {
+    const uint16_t* W;      // [N][Kd] bf16, or the same values already widened to fp16 (WF16 kernels)
+                            // (SwiGLU: [2F][Kd], gate rows then up rows; N = F)
+    const uint16_t* X;      // [M][Kd] fp16
+    const uint16_t* Xlo;    // [M][Kd] low plane of split activations (x = X + Xlo / 4096), SPLIT kernels only
+    int M, N, Kd;
+    int tiles_m, tiles_n;   // tiles_n counts BN-column tiles (SwiGLU: BN / 2 features), times ksplit
+    int ksplit;             // > 1: the reduction is cut into ksplit equal parts, each a unit of its own that STORES its
+                            // partial result at outf + part * M * N (the consumer adds the parts in a fixed order)
+    float* outf;            // GEPI_F32: [ksplit][M][N]
+    uint16_t* outh;         // GEPI_SWIGLU: [M][N] fp16
+    HeadPart hp{};          // GEPI_HEAD*: where the per-(row, chunk) statistics go (chunk = the WN * 16 columns of a wave)
+};
+
+// GEPI_HEAD: the output head. Logits are not stored: each row's columns of a wave are reduced to one record of partial
+// statistics (head_part.h). GEPI_HEAD2: the same with two-entry candidate lists (calls with k <= 2).
+enum { GEPI_F32, GEPI_SWIGLU, GEPI_HEAD, GEPI_HEAD2 };
+
+constexpr int GT_BK = 64;   // reduction step: a staged row is one 128-byte line
+
+// LDS bytes of a ring of ns stages
+constexpr int gemm_tile_lds(int bm, int bn, int ns, bool split) { return (bn + bm * (split ? 2 : 1)) * GT_BK * 2 * ns; }
+
+__device__ inline void mfma_acc(const Frag8& w, const Frag8& x, float4_t& c) {
+    asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+a"(c) : "v"(w.v), "v"(x.v));
+}
+__device__ inline void mfma_acc_v(const Frag8& w, const Frag8& x, float4_t& c) {
+    asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+v"(c) : "v"(w.v), "v"(x.v));
+}
+
+template <int EPI, int WM, int WN, int NWM, int NWN, int NS, bool SPLIT, bool WF16>
+__global__ __launch_bounds__(64 * NWM * NWN, NWM * NWN / 4)
+void gemm_tile_kernel(GemmTileArgs a) {
+    constexpr int NW = NWM * NWN, BM = WM * 16 * NWM, BN = WN * 16 * NWN, BK = GT_BK;
+    constexpr int SBYTES = gemm_tile_lds(BM, BN, 1, SPLIT);
+    constexpr int PIECES = SBYTES / 1024;                    // 1 KB of staged rows: what one load instruction moves
+    constexpr int CH = BK / 8, RPP = 64 / CH;                // 16-byte chunks per staged row, rows per piece
+    constexpr int LPS = (PIECES + NW - 1) / NW;              // load instructions per wave and stage
+    static_assert(SBYTES * NS <= 163840, "LDS");
+    static_assert((NS - 2) * LPS < 64 && NS >= 2, "the wait counter has six bits");
+    __shared__ __attribute__((aligned(1024))) char lds[SBYTES * NS];
+
+    // XCD x takes an equal share of the units (n-tile major, m fastest)
+    const int units = a.tiles_m * a.tiles_n, per = (units + 7) / 8;
+    const int li = blockIdx.x / 8, unit = (blockIdx.x % 8) * per + li;
+    if (li >= per || unit >= units) return;
+    int tn = unit / a.tiles_m;
+    const int tm = unit % a.tiles_m;
+    const int kpart = tn % a.ksplit;
+    tn /= a.ksplit;
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave / NWN, wn = wave % NWN;
+    const int lr = lane & 15, lg = lane >> 4;
+
+    const int nk = a.Kd / BK / a.ksplit;                  // the host guarantees Kd % (BK * ksplit) == 0
+    const size_t k0 = (size_t)kpart * nk * BK;
+    const uint32_t ldb = (uint32_t)a.Kd * 2;                 // bytes per row
+
+    // ---- staging plan: wave w moves pieces w, w + NW, ...; lane l of a piece moves one 16-byte chunk of row l / CH ----
+    // Rows are unpadded; chunk c of row r sits at c ^ swz(r), so that the 16 rows a fragment read touches at one logical
+    // chunk lie in 16 distinct 16-byte bank groups.
+    auto swz = [](int row) { return (row / (16 / CH)) & (CH - 1); };
+    uint32_t voff[LPS];
+    const char* sbase[LPS];
+    uint32_t ldst[LPS];
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
+#pragma unroll
+    for (int j = 0; j < LPS; ++j) {
+        int p = wave + j * NW;
+        p = p < PIECES ? p : PIECES - 1;                     // surplus requests repeat the last piece (same bytes, same place)
+        const int row = p * RPP + lane / CH;
+        const int c = (lane % CH) ^ swz(row);                // the chunk that lives in this slot of the swizzled row
+        ldst[j] = lds0 + p * 1024;
+        if (p * RPP < BN) {
+            // SwiGLU: the 16-row fragments alternate gate, up of the same 16 features
+            const int f = p * RPP / 16;
+            int r0 = tn * BN, r = row;
+            if (EPI == GEPI_SWIGLU) { r0 = tn * (BN / 2) + (f >> 1) * 16; r = row & 15; }
+            const int st = r0 < a.N ? r0 : a.N - 1, wr = r0 + r < a.N ? r0 + r : a.N - 1;
+            const size_t up = (EPI == GEPI_SWIGLU && (f & 1)) ? (size_t)a.N : 0;
+            sbase[j] = reinterpret_cast<const char*>(a.W + (up + st) * a.Kd + k0);
+            voff[j] = (uint32_t)(wr - st) * ldb + c * 16;
+        } else {
+            const bool low = SPLIT && p * RPP >= BN + BM;
+            int xr = tm * BM + row - BN - (low ? BM : 0);
+            xr = xr < a.M ? xr : a.M - 1;
+            sbase[j] = reinterpret_cast<const char*>((low ? a.Xlo : a.X) + (size_t)tm * BM * a.Kd + k0);
+            voff[j] = (uint32_t)(xr - tm * BM) * ldb + c * 16;
+        }
+    }
+    // Load j of the stage of reduction step kt. Requests past the last step are clamped: nobody reads what they bring, but
+    // the counts stay uniform.
+    auto issue = [&](auto jc, int kt, int slot) {
+        constexpr int j = decltype(jc)::value;
+        const char* g = sbase[j] + (size_t)(kt < nk ? kt : nk - 1) * (BK * 2);
+        const uint32_t vo = voff[j], at = ldst[j] + slot * SBYTES;
+        asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %2" ::"v"(vo), "s"(at), "s"(g) : "memory", "m0");
+    };
+
+    float4_t acc[WM][WN];
+    float4_t acl[SPLIT ? WM : 1][SPLIT ? WN : 1];
+#pragma unroll
+    for (int i = 0; i < WM; ++i)
+#pragma unroll
+        for (int j = 0; j < WN; ++j) {
+            acc[i][j] = float4_t{0.f, 0.f, 0.f, 0.f};
+            if constexpr (SPLIT) acl[i][j] = float4_t{0.f, 0.f, 0.f, 0.f};
+        }
+
+    Frag8 fw[2][WN], fx[2][WM], fl[2][SPLIT ? WM : 1];
+    // fragment addresses: the row part of the swizzle depends on the lane only
+    uint32_t ow[2], ox[2];
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+        const uint32_t ch = (uint32_t)(((s * 4 + lg) ^ swz(lr)) * 16);
+        ow[s] = (uint32_t)(wn * WN * 16 + lr) * (BK * 2) + ch;
+        ox[s] = (uint32_t)(BN + wm * WM * 16 + lr) * (BK * 2) + ch;
+    }
+    // fragment r of substep s: the wave's weight fragments, then its activation fragments (high plane, low plane)
+    constexpr int NREAD = WN + WM * (SPLIT ? 2 : 1), NMUL = WM * WN * (SPLIT ? 2 : 1);
+    auto read_frag = [&](auto sc, auto rc, int slot) {
+        constexpr int s = decltype(sc)::value, r = decltype(rc)::value;
+        if constexpr (r < WN) {
+            fw[s][r].v4 = *reinterpret_cast<const u32x4*>(lds + slot * SBYTES + ow[s] + r * 16 * BK * 2);
+        } else {
+            constexpr int i = SPLIT ? (r - WN) / 2 : r - WN;
+            constexpr bool low = SPLIT && ((r - WN) & 1);
+            const u32x4 v = *reinterpret_cast<const u32x4*>(lds + slot * SBYTES + ox[s] + ((low ? BM : 0) + i * 16) * BK * 2);
+            if constexpr (low) fl[s][i].v4 = v;
+            else fx[s][i].v4 = v;
+        }
+    };
+    // Multiplies substep s and reads the fragments of substep rs (of ring slot rslot) meanwhile, one read between every
+    // few matrix instructions. The accumulators are pinned to the accumulation registers by assembly: left to itself
+    // the compiler moves them back and forth between the register files inside the loop.
+    // The loads L0 .. L1-1 of another stage are spread over the same instructions: in a burst they hold up the matrix
+    // instructions behind them, about 32 cycles each.
+    auto multiply_read = [&](auto sc, auto rsc, int rslot, auto l0c, auto l1c, int lkt, int lslot) {
+        constexpr int s = decltype(sc)::value, L0 = decltype(l0c)::value, L1 = decltype(l1c)::value;
+        if constexpr (!WF16) {
+#pragma unroll
+            for (int j = 0; j < WN; ++j) bf16x8_to_f16x8(fw[s][j]);
+            asm volatile("s_nop 1");                         // vector write -> matrix read
+        }
+        static_for<0, NMUL>([&](auto mc) {
+            constexpr int m = decltype(mc)::value;
+            constexpr int i = m / (WN * (SPLIT ? 2 : 1)), q = m % (WN * (SPLIT ? 2 : 1)), j = q % WN;
+            constexpr int r0 = m * NREAD / NMUL, r1 = (m + 1) * NREAD / NMUL;
+            static_for<r0, r1>([&](auto rc) { read_frag(rsc, rc, rslot); });
+            constexpr int l0 = L0 + m * (L1 - L0) / NMUL, l1 = L0 + (m + 1) * (L1 - L0) / NMUL;
+            static_for<l0, l1>([&](auto jc) { issue(jc, lkt, lslot); });
+            constexpr bool inv = i * WN * (SPLIT ? 2 : 1) + q >= 64;      // there are 256 accumulation registers: the rest sit in vector registers
+            if constexpr (SPLIT && q >= WN) { if constexpr (inv) mfma_acc_v(fw[s][j], fl[s][i], acl[i][j]); else mfma_acc(fw[s][j], fl[s][i], acl[i][j]); }
+            else { if constexpr (inv) mfma_acc_v(fw[s][j], fx[s][i], acc[i][j]); else mfma_acc(fw[s][j], fx[s][i], acc[i][j]); }
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    };
+    auto sync = [&] {
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((NS - 2) * LPS) : "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    };
+    using C0 = std::integral_constant<int, 0>;
+    using C1 = std::integral_constant<int, 1>;
+    using L0 = C0;
+    using LA = std::integral_constant<int, LPS>;
+    // A stage is two matrix-instruction steps. In the middle of stage kt: wait for stage kt + 1 and for everybody's last
+    // reads of stage kt's slot, then request stage kt + NS into that slot. A ring of three stages or more spreads its
+    // requests over both halves, a ring of two takes the half right after the wait (the other half would be too late).
+    using LH = std::integral_constant<int, NS >= 3 ? (LPS + 1) / 2 : LPS>;
+#pragma unroll
+    for (int s = 0; s < NS - 1; ++s) static_for<0, LPS>([&](auto jc) { issue(jc, s, s); });
+    static_for<0, LH::value>([&](auto jc) { issue(jc, NS - 1, NS - 1); });
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 2) * LPS + LH::value) : "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    static_for<0, NREAD>([&](auto rc) { read_frag(C0{}, rc, 0); });
+    int slot = 0, pslot = NS - 1;
+    for (int kt = 0; kt < nk; ++kt) {
+        const int nslot = slot + 1 < NS ? slot + 1 : 0;
+        multiply_read(C0{}, C1{}, slot, LH{}, LA{}, kt + NS - 1, pslot);
+        sync();
+        multiply_read(C1{}, C0{}, nslot, L0{}, LH{}, kt + NS, slot);
+        pslot = slot;
+        slot = nslot;
+    }
+    // the surplus requests must not land in a later workgroup's LDS; the last matrix instructions must have written
+    asm volatile("s_waitcnt vmcnt(0)\n\ts_nop 15\n\ts_nop 15" ::: "memory");
+    static_for<0, NMUL>([&](auto mc) {                       // (reads of the results cannot move ahead of that wait)
+        constexpr int m = decltype(mc)::value;
+        constexpr int i = m / (WN * (SPLIT ? 2 : 1)), q = m % (WN * (SPLIT ? 2 : 1)), j = q % WN;
+        float4_t& c = (SPLIT && q >= WN) ? acl[SPLIT ? i : 0][SPLIT ? j : 0] : acc[i][j];
+        if constexpr (m >= 64) asm volatile("" : "+v"(c));
+        else asm volatile("" : "+a"(c));
+    });
+    if constexpr (SPLIT) {
+#pragma unroll
+        for (int i = 0; i < WM; ++i)
+#pragma unroll
+            for (int j = 0; j < WN; ++j)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[i][j][e] += acl[i][j][e] * kLoInv;
+    }
+
+    // ---- epilogue: lane holds columns 4 lg .. 4 lg + 3 of every 16-column fragment, row lr of every 16-row fragment ----
+    if constexpr (EPI == GEPI_HEAD || EPI == GEPI_HEAD2) {
+        constexpr int KD = EPI == GEPI_HEAD2 ? 2 : KT;
+        const int chunk = tn * NWN + wn;
+        if (chunk >= a.hp.chunks) return;
+        const int n0 = tn * BN + wn * WN * 16 + 4 * lg;
+        const int kt = a.hp.topk < KD ? a.hp.topk : KD;
+        static_for<0, WM>([&](auto ic) {                     // (a loop this long is not unrolled by itself, and acc must not be indexed at run time)
+            constexpr int i = decltype(ic)::value;
+            const int row = tm * BM + (wm * WM + i) * 16 + lr;
+            RowStatT<KD> st;
+            st.init();
+            if (row < a.M) {
+                float v[WN * 4];
+                float mx = -INFINITY;
+                int arg = 0x7FFFFFFF;
+#pragma unroll
+                for (int j = 0; j < WN; ++j)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const int n = n0 + j * 16 + e;
+                        const float x = n < a.N ? acc[i][j][e] : -INFINITY;
+                        v[j * 4 + e] = x;
+                        arg = x > mx ? n : arg;                                  // ids ascend: earlier ties stay
+                        mx = fmaxf(mx, x);
+                    }
+                float sum = 0.f;
+                if (mx != -INFINITY) {
+#pragma unroll
+                    for (int j = 0; j < WN; ++j)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) sum += __expf(v[j * 4 + e] - mx);
+                }
+                st.mx = mx; st.sum = sum; st.arg = arg;
+                float thr_v = -INFINITY;
+                int thr_i = 0x7FFFFFFF;
+#pragma unroll
+                for (int j = 0; j < WN; ++j)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const int n = n0 + j * 16 + e;
+                        if (n < a.N && before(v[j * 4 + e], n, thr_v, thr_i)) {
+                            st.push_top(v[j * 4 + e], n);
+#pragma unroll
+                            for (int t = 0; t < KD; ++t) if (t == kt - 1) { thr_v = st.tv[t]; thr_i = st.ti[t]; }
+                        }
+                    }
+                const int cb = a.hp.cand_beg[row], cn = a.hp.cand_cnt[row];
+                for (int c = 0; c < cn; ++c) {
+                    const int x = a.hp.cand_x[cb + c], o = x - n0;
+                    if (o >= 0 && o < WN * 16 && (o & 15) < 4) {
+#pragma unroll
+                        for (int j = 0; j < WN; ++j)
+#pragma unroll
+                            for (int e = 0; e < 4; ++e)
+                                if (o == j * 16 + e) a.hp.cand_lx[cb + c] = v[j * 4 + e];
+                    }
+                }
+                if (a.hp.logits_dbg) {
+#pragma unroll
+                    for (int j = 0; j < WN; ++j)
+                        if (n0 + j * 16 < a.N)                                   // N is a multiple of 16
+                            *reinterpret_cast<float4a4_t*>(a.hp.logits_dbg + (size_t)row * a.N + n0 + j * 16) = float4a4_t{v[j * 4], v[j * 4 + 1], v[j * 4 + 2], v[j * 4 + 3]};
+                }
+            }
+            st.merge_from_lane(16);
+            st.merge_from_lane(32);
+            if (lg == 0 && row < a.M) st.store(a.hp, row, chunk);
+        });
+        return;
+    }
+    float* const outf = a.outf + (size_t)kpart * a.M * a.N;
+#pragma unroll
+    for (int i = 0; i < WM; ++i) {
+        const int row = tm * BM + (wm * WM + i) * 16 + lr;
+        if (row >= a.M) continue;
+        if constexpr (EPI == GEPI_SWIGLU) {
+            static_assert(WN % 2 == 0, "gate and up fragments come in pairs");
+#pragma unroll
+            for (int j = 0; j < WN; j += 2) {
+                const int feat = tn * (BN / 2) + (wn * WN + j) * 8 + 4 * lg;
+                if (feat >= a.N) continue;                   // N is a multiple of 16
+                Frag4 o;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float gt = acc[i][j][e], up = acc[i][j + 1 < WN ? j + 1 : j][e];
+                    o.h[e] = f32_to_f16(gt / (1.f + __expf(-gt)) * up);
+                }
+                *reinterpret_cast<u32x2*>(a.outh + (size_t)row * a.N + feat) = o.v2;
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < WN; ++j) {
+                const int col = tn * BN + (wn * WN + j) * 16 + 4 * lg;
+                if (col >= a.N) continue;
+                *reinterpret_cast<float4_t*>(outf + (size_t)row * a.N + col) = acc[i][j];
+            }
+        }
+    }
+}
+
+}  // namespace laser

@@ -9,7 +9,7 @@
 //             in registers (chunk = wavefront).
 //   M <= 80   the weight-streaming kernel of gemm_mid.h with its head epilogue (chunk = workgroup, 64 or 128
 //             vocabulary entries): the head matrix is read once.
-//   more      the LDS-tiled matrix-core GEMM of gemm_mfma.h with its head epilogue (chunk = 128-column tile).
+//   more      the LDS-tiled matrix-core GEMM of gemm_tile.h with its head epilogue (chunk = a wave's 128 columns).
 // Pass 2: a wavefront per row merges the per-chunk partials. The draft's rank is the number of partial-list entries
 // ordered before it; if a chunk hides an entry that precedes the draft, that chunk already contributes
 // >= LASER_MAX_TOPK >= k listed ones, so "rank < k" is exact. A thread per sequence then examines the nodes in order
@@ -17,7 +17,7 @@
 #include <cmath>
 #include <mutex>
 
-#include "gemm_mfma.h"
+#include "gemm_tile_plan.h"
 #include "gemm_skinny.h"
 #include "gemm_mid.h"
 #include "state.h"
@@ -285,18 +285,17 @@ static int run_head_bufs(Model* m, const uint16_t* h, const int32_t* tokens, con
         GemmMidArgs t{m->d.wlm, h, nullptr, M, V, dm, nullptr, nullptr, nullptr, hp};
         launch_gemm_mid<EPI_HEAD, false>(t, pl, stream);
     } else {
-        const int tiles_m = (M + GM_BM - 1) / GM_BM, tiles_n = (V + 127) / 128;
-        hp.chunks = tiles_n;
+        hp.chunks = (V + 127) / 128;
         if (m->f16_copies && !m->wlm16) {          // first many-row head: widen the head matrix to fp16 once
             const uint16_t* src[1] = {m->d.wlm};
             const size_t n[1] = {(size_t)V * dm};
             const int rc = widen_copies(src, n, 1, &m->wlm16, stream);
             if (rc) return rc;
         }
-        GemmTileArgs t{m->wlm16 ? m->wlm16 : m->d.wlm, h, nullptr, M, V, dm, tiles_m, tiles_n, 1, nullptr, nullptr, hp};
-        const dim3 grid(gemm_mfma_grid(tiles_m, tiles_n));
-        if (m->wlm16) hipLaunchKernelGGL((gemm_mfma_kernel<GEPI_HEAD, 128, false, true>), grid, dim3(256), 0, stream, t);
-        else hipLaunchKernelGGL((gemm_mfma_kernel<GEPI_HEAD, 128, false, false>), grid, dim3(256), 0, stream, t);
+        int ncu = 0;
+        LASER_HIP_CHECK(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, 0));
+        GemmTileArgs t{m->wlm16 ? m->wlm16 : m->d.wlm, h, nullptr, M, V, dm, 0, 0, 1, nullptr, nullptr, hp};
+        launch_tile_head(t, m->wlm16 != nullptr, ncu, stream);
     }
     AcceptArgs aa{hb.hp_max, hb.hp_sum, hb.hp_arg, hb.hp_topv, hb.hp_topi, hb.cand_beg, hb.cand_cnt, hb.cand_x, hb.cand_lx, hb.node_cand,
                   tokens, parent, n_nodes, M, B, K, hp.chunks, topk, mode, p, hb.row_mx, hb.row_sum, hb.row_arg, hb.cand_rank,

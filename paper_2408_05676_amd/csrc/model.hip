@@ -5,7 +5,7 @@
 #include <string>
 #include <vector>
 
-#include "gemm_mfma.h"
+#include "gemm_tile_plan.h"
 #include "gemm_skinny.h"
 #include "gemm_mid.h"
 #include "state.h"
@@ -82,7 +82,7 @@ __global__ __launch_bounds__(256) void embed_rmsnorm_kernel(
 // n_part > 0: the projection before this norm left its result as n_part partial sums (part + p * part_stride, same
 // [row][d] layout): they are added to the residual row in order p = 0, 1, .. and the row is written back, in the
 // same pass that takes the row into registers and sums its squares (every thread touches only its own columns).
-// NPART is a template argument (0, 2, 4 or 8) so that the parts' loads are all issued before the first is added: with
+// NPART is a template argument (0, 1, 2, 4 or 8) so that the parts' loads are all issued before the first is added: with
 // a run-time trip count they were waited for one after the other, a memory round trip each.
 template <int NPART>
 __global__ __launch_bounds__(256) void rmsnorm_kernel(float* __restrict__ x, const float* __restrict__ gain,
@@ -146,6 +146,7 @@ static void launch_rmsnorm(int M, hipStream_t stream, float* x, const float* gai
                            const float* part, int n_part, size_t part_stride) {
     switch (n_part) {
         case 0: hipLaunchKernelGGL(rmsnorm_kernel<0>, dim3(M), dim3(256), 0, stream, x, gain, d, eps, xn, xn_lo, part, part_stride); break;
+        case 1: hipLaunchKernelGGL(rmsnorm_kernel<1>, dim3(M), dim3(256), 0, stream, x, gain, d, eps, xn, xn_lo, part, part_stride); break;
         case 2: hipLaunchKernelGGL(rmsnorm_kernel<2>, dim3(M), dim3(256), 0, stream, x, gain, d, eps, xn, xn_lo, part, part_stride); break;
         case 4: hipLaunchKernelGGL(rmsnorm_kernel<4>, dim3(M), dim3(256), 0, stream, x, gain, d, eps, xn, xn_lo, part, part_stride); break;
         default: hipLaunchKernelGGL(rmsnorm_kernel<8>, dim3(M), dim3(256), 0, stream, x, gain, d, eps, xn, xn_lo, part, part_stride); break;
@@ -288,78 +289,25 @@ int widen_copies(const uint16_t* const* src, const size_t* elems, int n, uint16_
     return LASER_OK;
 }
 
-// Reduction parts for a tiled launch of `tiles` 128 x 128 tiles. Two workgroups share a CU ("slots" = 2 x CUs) and a
-// launch takes ceil(units / slots) rounds; a lone workgroup on a CU runs at about 0.6 of the shared time. Cutting the
-// reduction into S parts makes S times as many units of 1/S the length, which evens out tile counts like 576 (2 rounds
-// for 1.1 rounds of work) or 192 (most slots empty); each part costs one more pass of the output through memory.
-static int choose_ksplit(long tiles, int ksteps, long out_elems, int slots) {
-    int best = 1;
-    double best_cost = 1e30;
-    for (int S = 1; S <= 4; S *= 2) {
-        if (ksteps % S || ksteps / S < 8) continue;
-        if (S > 2 && out_elems > (4L << 20)) continue;          // large outputs: the extra passes cost more than they save
-        const long units = tiles * S;
-        const double rounds = units <= slots / 2 ? 0.6 : (double)((units + slots - 1) / slots);
-        const double cost = rounds / S + 0.04 * (S - 1);
-        if (cost < best_cost - 1e-9) { best_cost = cost; best = S; }
-    }
-    return best;
-}
-
 template <int EPI>
 static int launch_gemm(GemmArgs& a_in, hipStream_t stream) {
     GemmArgs& a = a_in;
     a.n_part = 0;
     if (a.M > kSkinnyMaxRows) {
-        constexpr int GE = EPI == EPI_F32 ? GEPI_F32 : (EPI == EPI_RESID ? GEPI_RESID : GEPI_SWIGLU);
-        const int tiles_m = (a.M + GM_BM - 1) / GM_BM;
         int ncu = 0;
         LASER_HIP_CHECK(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, 0));
-        using std::integral_constant;
-        if constexpr (EPI != EPI_SWIGLU) {
-            // store / accumulate epilogues may split the reduction: partial results go to the workspace and the
-            // next kernel (rotary + cache write, or the norm) adds them up in a fixed order
-            const int bk = a.Xlo ? 32 : 64;
-            const long tiles = (long)tiles_m * ((a.N + 127) / 128);
-            int S = a.want_split ? a.want_split : choose_ksplit(tiles, a.Kd / bk, (long)a.M * a.N, 2 * ncu);
-            if ((a.Kd / bk) % S || !a.part || (size_t)S * a.M * a.N > a.part_floats) S = 1;
-            if (S > 1) {
-                GemmTileArgs t{a.W16 ? a.W16 : a.W, a.X, a.Xlo, a.M, a.N, a.Kd, tiles_m, ((a.N + 127) / 128) * S, S, a.part, nullptr};
-                dim3 grid(gemm_mfma_grid(t.tiles_m, t.tiles_n));
-                auto gos = [&](auto splitc) {
-                    if (a.W16)
-                        hipLaunchKernelGGL((gemm_mfma_kernel<GEPI_F32, 128, decltype(splitc)::value, true>), grid, dim3(256), 0, stream, t);
-                    else
-                        hipLaunchKernelGGL((gemm_mfma_kernel<GEPI_F32, 128, decltype(splitc)::value, false>), grid, dim3(256), 0, stream, t);
-                };
-                if (a.Xlo) gos(integral_constant<bool, true>{});
-                else gos(integral_constant<bool, false>{});
-                LASER_HIP_CHECK(hipGetLastError());
-                a.n_part = S;
-                return LASER_OK;
-            }
+        GemmTileArgs t{a.W16 ? a.W16 : a.W, a.X, a.Xlo, a.M, a.N, a.Kd, 0, 0, 1, nullptr, a.outh};
+        if constexpr (EPI == EPI_SWIGLU) {
+            launch_tile_swiglu(t, a.W16 != nullptr, ncu, stream);
+        } else {
+            // The result goes to the workspace, in one or more reduction parts, and the next kernel (rotary + cache write, or
+            // the norm) adds them up in a fixed order.
+            int max_split = 8;
+            while (max_split > 1 && (size_t)max_split * a.M * a.N > a.part_floats) max_split /= 2;
+            LASER_REQUIRE(a.part && (size_t)a.M * a.N <= a.part_floats, LASER_E_LIMIT, "the partial-result workspace is too small");
+            t.outf = a.part;
+            a.n_part = launch_tile_f32(t, a.W16 != nullptr, ncu, a.want_split, max_split, stream);
         }
-        // narrow outputs: 128-column tiles would leave compute units without work; 64-column tiles double the count
-        const bool narrow = EPI != EPI_SWIGLU && (long)tiles_m * ((a.N + 127) / 128) * 4 < (long)ncu * 5;
-        const int bn = narrow ? 64 : 128;
-        GemmTileArgs t{a.W16 ? a.W16 : a.W, a.X, a.Xlo, a.M, a.N, a.Kd, tiles_m, EPI == EPI_SWIGLU ? (a.N + 63) / 64 : (a.N + bn - 1) / bn, 1, a.outf, a.outh};
-        dim3 grid(gemm_mfma_grid(t.tiles_m, t.tiles_n));
-        auto go = [&](auto bnc, auto splitc) {
-            if (a.W16)
-                hipLaunchKernelGGL((gemm_mfma_kernel<GE, decltype(bnc)::value, decltype(splitc)::value, true>), grid, dim3(256), 0, stream, t);
-            else
-                hipLaunchKernelGGL((gemm_mfma_kernel<GE, decltype(bnc)::value, decltype(splitc)::value, false>), grid, dim3(256), 0, stream, t);
-        };
-        if constexpr (EPI != EPI_SWIGLU) {
-            if (narrow) {
-                if (a.Xlo) go(integral_constant<int, 64>{}, integral_constant<bool, true>{});
-                else go(integral_constant<int, 64>{}, integral_constant<bool, false>{});
-                LASER_HIP_CHECK(hipGetLastError());
-                return LASER_OK;
-            }
-        }
-        if (a.Xlo) go(integral_constant<int, 128>{}, integral_constant<bool, true>{});
-        else go(integral_constant<int, 128>{}, integral_constant<bool, false>{});
         LASER_HIP_CHECK(hipGetLastError());
         return LASER_OK;
     }
