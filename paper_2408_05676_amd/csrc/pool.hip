@@ -20,19 +20,9 @@
 #include <thread>
 #include <vector>
 
-#include "common.h"
+#include "pool.h"
 
 namespace laser {
-
-struct Pool {
-    int32_t* P = nullptr;
-    uint32_t* seq_end = nullptr;
-    uint32_t* sa = nullptr;
-    IndexEntry* table = nullptr;
-    uint64_t cap_mask = 0;
-    int64_t n_tokens = 0, n_keys = 0, n_entries = 0, n_sa = 0, device_bytes = 0;
-    int n_max = 0;
-};
 
 // ------------------------------------------------------------------------------------ kernel
 constexpr int kCand = 512;         // occurrences a wave keeps in LDS (more: streamed from the index, re-checked against the chain)
@@ -571,6 +561,8 @@ namespace {
 
 struct SubPool { int64_t key; uint32_t begin, end; };
 
+constexpr int64_t kDeviceBuildMin = 16384;
+
 }  // namespace
 
 static int build_pool(const int32_t* tokens, const int64_t* seq_off, const int64_t* seq_key,
@@ -584,6 +576,35 @@ static int build_pool(const int32_t* tokens, const int64_t* seq_off, const int64
     std::vector<int64_t> order(n_seq);
     std::iota(order.begin(), order.end(), 0);
     std::stable_sort(order.begin(), order.end(), [&](int64_t x, int64_t y) { return seq_key[x] < seq_key[y]; });
+
+    // Many occurrences: the rest happens on the device, unless it cannot hold the working arrays (17 bytes per token
+    // besides the pool itself). Few: the host is done before the device's ~40 dependent launches are.
+    if (n_tok - n_seq >= kDeviceBuildMin) {
+        PoolLayout lay;
+        uint32_t bits = 0, pos = 0;
+        for (int64_t i = 0; i < n_tok; ++i) bits |= (uint32_t)tokens[i];
+        for (int64_t i = 0; i < n_seq; ++i) {
+            const int64_t s = order[i];
+            const uint32_t len = (uint32_t)(seq_off[s + 1] - seq_off[s]);
+            if (lay.sub_key.empty() || lay.sub_key.back() != seq_key[s]) lay.sub_key.push_back(seq_key[s]);
+            if (bits >> 31)
+                for (uint32_t t = 0; t < len; ++t)
+                    LASER_REQUIRE(tokens[seq_off[s] + t] >= 0, LASER_E_INVALID_ARG, "negative token in sequence %lld", (long long)s);
+            if (len == 0) continue;
+            lay.dst_off.push_back(pos);
+            lay.src_off.push_back((uint32_t)seq_off[s]);
+            lay.sub.push_back((uint32_t)lay.sub_key.size() - 1);
+            pos += len;
+        }
+        lay.dst_off.push_back(pos);
+        lay.token_bits = bits;
+        Pool* p = new Pool();
+        bool no_memory = false;
+        const int rc = build_index_device(tokens, lay, n_max, stream, p, &no_memory);
+        if (rc == LASER_OK) { *out = p; return rc; }
+        delete p;
+        if (!no_memory) return rc;
+    }
 
     std::vector<int32_t> P((size_t)n_tok);
     std::vector<uint32_t> seq_begin((size_t)n_tok), seq_end((size_t)n_tok);
