@@ -561,7 +561,7 @@ namespace {
 
 struct SubPool { int64_t key; uint32_t begin, end; };
 
-constexpr int64_t kDeviceBuildMin = 16384;
+constexpr int64_t kDeviceBuildMin = 4096;   // at 5000 tokens 190 .. 420 us against the host's 300 .. 570, at 2500 180 .. 360 against 120 .. 450, at 20000 210 .. 530 against 600 .. 2700
 
 }  // namespace
 

@@ -8,7 +8,7 @@ from oracle.retrieval import RegroupedPool, retrieve
 
 pytestmark = pytest.mark.gpu
 
-HOST_MAX = 16383          # occurrences (tokens minus sequences) up to which the host builds
+HOST_MAX = 4095          # occurrences (tokens minus sequences) up to which the host builds
 
 
 def _texts(rng, lens, vocab):
