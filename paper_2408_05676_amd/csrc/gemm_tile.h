@@ -40,7 +40,7 @@ __device__ inline void mfma_acc_v(const Frag8& w, const Frag8& x, float4_t& c) {
 }
 
 template <int EPI, int WM, int WN, int NWM, int NWN, int NS, bool SPLIT, bool WF16>
-__global__ __launch_bounds__(64 * NWM * NWN, NWM * NWN / 4)
+__global__ __launch_bounds__(64 * NWM * NWN, (NWM * NWN + 3) / 4)
 void gemm_tile_kernel(GemmTileArgs a) {
     constexpr int NW = NWM * NWN, BM = WM * 16 * NWM, BN = WN * 16 * NWN, BK = GT_BK;
     constexpr int SBYTES = gemm_tile_lds(BM, BN, 1, SPLIT);

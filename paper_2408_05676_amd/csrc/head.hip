@@ -272,6 +272,7 @@ static int run_head_bufs(Model* m, const uint16_t* h, const int32_t* tokens, con
     hipLaunchKernelGGL(head_cands_kernel, dim3(B), dim3(64), 0, stream, tokens, parent, n_nodes, B, K, V,
                        hb.cand_beg, hb.cand_cnt, hb.cand_x, hb.node_cand, hb.cand_lx);
     HeadPart hp{hb.cand_beg, hb.cand_cnt, hb.cand_x, hb.cand_lx, hb.hp_max, hb.hp_sum, hb.hp_arg, hb.hp_topv, hb.hp_topi, 0, topk, logits_dbg};
+    const bool aligned = ((reinterpret_cast<uintptr_t>(h) | (m->f16_copies ? 0 : reinterpret_cast<uintptr_t>(m->d.wlm))) & 15) == 0;
     if (M <= kHeadStreamMaxRows) {
         const int ntiles = V / 16;
         const int tpw = (ntiles + 1023) / 1024;
@@ -279,11 +280,20 @@ static int run_head_bufs(Model* m, const uint16_t* h, const int32_t* tokens, con
         HeadArgs a{m->d.wlm, h, M, V, dm, tpw, hp};
         dim3 grid((unsigned)((m->head_chunks + 3) / 4), 1u);         // at most 16 rows: one row tile
         hipLaunchKernelGGL(lm_head_kernel<1>, grid, dim3(256), 0, stream, a);
-    } else if (M <= kHeadMidMaxRows && dm % kGemmKStep == 0) {
-        const GemmMidPlan pl = gemm_mid_plan(M, V, dm, 1, false, 0);
+    } else if ((M <= kHeadMidMaxRows || !aligned) && dm % kGemmKStep == 0) {
+        // up to kHeadMidMaxRows rows at a time: all of them, except where more rows or their matrix lie off the 16-byte grid
+        // that loads into LDS need
+        const GemmMidPlan pl = gemm_mid_plan(std::min(M, kHeadMidMaxRows), V, dm, 1, false, 0);
         hp.chunks = (V / 16 + pl.NW - 1) / pl.NW;                     // = workgroups of the launch
-        GemmMidArgs t{m->d.wlm, h, nullptr, M, V, dm, nullptr, nullptr, nullptr, hp};
-        launch_gemm_mid<EPI_HEAD, false>(t, pl, stream);
+        for (int r0 = 0; r0 < M; r0 += kHeadMidMaxRows) {
+            HeadPart part = hp;
+            const size_t rec = (size_t)r0 * hp.chunks;
+            part.cand_beg += r0; part.cand_cnt += r0;
+            part.hp_max += rec; part.hp_sum += rec; part.hp_arg += rec; part.hp_topv += rec * KT; part.hp_topi += rec * KT;
+            if (part.logits_dbg) part.logits_dbg += (size_t)r0 * V;
+            GemmMidArgs t{m->d.wlm, h + (size_t)r0 * dm, nullptr, std::min(M - r0, kHeadMidMaxRows), V, dm, nullptr, nullptr, nullptr, part};
+            launch_gemm_mid<EPI_HEAD, false>(t, pl, stream);
+        }
     } else {
         hp.chunks = (V + 127) / 128;
         if (m->f16_copies && !m->wlm16) {          // first many-row head: widen the head matrix to fp16 once

@@ -293,12 +293,17 @@ template <int EPI>
 static int launch_gemm(GemmArgs& a_in, hipStream_t stream) {
     GemmArgs& a = a_in;
     a.n_part = 0;
-    if (a.M > kSkinnyMaxRows) {
+    // Loads into LDS take 16-byte aligned operands; the library's own buffers are, a caller's weights may not be.
+    const uint16_t* const w_tile = a.M > kSkinnyMaxRows && a.W16 ? a.W16 : a.W;
+    const bool aligned = (reinterpret_cast<uintptr_t>(w_tile) & 15) == 0;
+    const bool few = a.M > 16 && a.M <= kSkinnyMaxRows && a.mid_waves == 0 && (EPI != EPI_SWIGLU || a.Xlo);
+    if (aligned && (a.M > kSkinnyMaxRows || few)) {
         int ncu = 0;
         LASER_HIP_CHECK(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, 0));
-        GemmTileArgs t{a.W16 ? a.W16 : a.W, a.X, a.Xlo, a.M, a.N, a.Kd, 0, 0, 1, nullptr, a.outh};
+        GemmTileArgs t{w_tile, a.X, a.Xlo, a.M, a.N, a.Kd, 0, 0, 1, nullptr, a.outh};
         if constexpr (EPI == EPI_SWIGLU) {
-            launch_tile_swiglu(t, a.W16 != nullptr, ncu, stream);
+            if (few) launch_few_swiglu(t, ncu, stream);
+            else launch_tile_swiglu(t, a.W16 != nullptr, ncu, stream);
         } else {
             // The result goes to the workspace, in one or more reduction parts, and the next kernel (rotary + cache write, or
             // the norm) adds them up in a fixed order.
@@ -306,7 +311,8 @@ static int launch_gemm(GemmArgs& a_in, hipStream_t stream) {
             while (max_split > 1 && (size_t)max_split * a.M * a.N > a.part_floats) max_split /= 2;
             LASER_REQUIRE(a.part && (size_t)a.M * a.N <= a.part_floats, LASER_E_LIMIT, "the partial-result workspace is too small");
             t.outf = a.part;
-            a.n_part = launch_tile_f32(t, a.W16 != nullptr, ncu, a.want_split, max_split, stream);
+            a.n_part = few ? launch_few_f32(t, ncu, 0, max_split, stream)
+                           : launch_tile_f32(t, a.W16 != nullptr, ncu, a.want_split, max_split, stream);
         }
         LASER_HIP_CHECK(hipGetLastError());
         return LASER_OK;
@@ -314,13 +320,18 @@ static int launch_gemm(GemmArgs& a_in, hipStream_t stream) {
     const int ntiles = a.N / 16;
     const int mblocks = (a.M + 15) / 16;
     if (mblocks >= 2 && (a.Xlo || EPI == EPI_RESID) && a.Kd % kGemmKStep == 0) {
-        // 17..80 rows: activations staged in LDS and shared by the workgroup's four weight tiles
-        GemmMidArgs t{a.W, a.X, a.Xlo, a.M, a.N, a.Kd, a.outf, a.outh, a.part};
-        const GemmMidPlan pl = gemm_mid_plan(a.M, a.N, a.Kd, a.Xlo ? 2 : 1, EPI == EPI_SWIGLU, a.part ? a.part_floats : 0, a.mid_waves);
-        if (a.Xlo) launch_gemm_mid<EPI, true>(t, pl, stream);
-        else if constexpr (EPI == EPI_RESID) launch_gemm_mid<EPI, false>(t, pl, stream);
-        LASER_HIP_CHECK(hipGetLastError());
-        a.n_part = pl.S > 1 ? pl.S : 0;
+        // option mid_waves, or weights off the 16-byte grid: activations staged through registers, up to 80 rows at a time
+        for (int r0 = 0; r0 < a.M; r0 += kSkinnyMaxRows) {
+            const int M = std::min(a.M - r0, kSkinnyMaxRows);
+            const size_t in = (size_t)r0 * a.Kd, out = (size_t)r0 * a.N;
+            GemmMidArgs t{a.W, a.X + in, a.Xlo ? a.Xlo + in : nullptr, M, a.N, a.Kd, a.outf ? a.outf + out : nullptr, a.outh ? a.outh + out : nullptr, a.part};
+            const bool parts = a.part && a.M <= kSkinnyMaxRows;
+            const GemmMidPlan pl = gemm_mid_plan(M, a.N, a.Kd, a.Xlo ? 2 : 1, EPI == EPI_SWIGLU, parts ? a.part_floats : 0, a.mid_waves);
+            if (a.Xlo) launch_gemm_mid<EPI, true>(t, pl, stream);
+            else if constexpr (EPI == EPI_RESID) launch_gemm_mid<EPI, false>(t, pl, stream);
+            LASER_HIP_CHECK(hipGetLastError());
+            a.n_part = pl.S > 1 ? pl.S : 0;
+        }
         return LASER_OK;
     }
     const int MB = mblocks >= 5 ? 5 : mblocks;
@@ -704,8 +715,8 @@ static int forward(Model* m, KV* kv, const int32_t* ids_dev, const int32_t* pend
         if (rc) return rc;
     }
     if (M > 16 && !m->kpart) {
-        // workspace for reduction-split partial results: up to 8 parts of [max_rows][d] or 2 of [max_rows][3 d]
-        m->kpart_floats = (size_t)d.max_rows * dm * 8;
+        // workspace for reduction-split partial results: up to 8 parts of [max_rows][d] or 2 of [max_rows][3 d], 4 up to 80 rows
+        m->kpart_floats = (size_t)dm * std::max((size_t)d.max_rows * 8, (size_t)std::min(d.max_rows, kSkinnyMaxRows) * 12);
         LASER_HIP_CHECK(hipMalloc((void**)&m->kpart, m->kpart_floats * 4));
     }
     int pend = 0;              // partial results of the last down projection still to be added to the residual
@@ -772,8 +783,9 @@ static int forward(Model* m, KV* kv, const int32_t* ids_dev, const int32_t* pend
         if ((rc = launch_gemm<EPI_RESID>(go, stream))) return rc;
         launch_rmsnorm(M, stream, m->x, d.g2 + (size_t)l * dm, dm, d.eps, m->xn, m->xn_lo, (const float*)m->kpart, go.n_part, (size_t)M * dm);
         // On the tiled many-row path a split operand doubles the matrix work; gate/up (45 % of the layer's
-        // flops) takes the single fp16 rows there unless option "split_ffn" asks for the split (see set_option).
-        const bool split_gu = M <= kSkinnyMaxRows || m->split_ffn;
+        // flops) takes the single fp16 rows there unless option "split_ffn" asks for the split (see set_option). The kernel
+        // for weights off the 16-byte grid knows the split form only.
+        const bool split_gu = M <= kSkinnyMaxRows || m->split_ffn || (!many && (reinterpret_cast<uintptr_t>(d.wgu) & 15) != 0);
         GemmArgs gg{d.wgu + (size_t)l * 2 * F * dm, many ? m->w16[2] + (size_t)l * 2 * F * dm : nullptr, m->xn, split_gu ? m->xn_lo : nullptr, M, F, dm, 1, nullptr, m->act};
         gg.mid_waves = m->mid_waves;
         const bool prof = m->prof_on && m->prof_n < m->prof_cap;
