@@ -12,7 +12,7 @@
 //   more      the LDS-tiled matrix-core GEMM of gemm_tile.h with its head epilogue (chunk = a wave's 128 columns).
 // Pass 2: a wavefront per row merges the per-chunk partials. The draft's rank is the number of partial-list entries
 // ordered before it; if a chunk hides an entry that precedes the draft, that chunk already contributes
-// >= LASER_MAX_TOPK >= k listed ones, so "rank < k" is exact. A thread per sequence then examines the nodes in order
+// >= LASER_MAX_TOPK >= k listed ones, so "rank < k" is exact. A wavefront per sequence then examines the nodes
 // and emits accepted drafts plus the correction token.
 #include <cmath>
 #include <mutex>
@@ -192,56 +192,52 @@ __global__ __launch_bounds__(256) void accept_rows_kernel(AcceptArgs a) {
     }
 }
 
-// Pass 2b, a thread per sequence: the nodes are examined in pseudo-sequence order (a node is verified iff its parent
-// is and its token passes the rule against its parent's row), the deepest verified node -- the first one among
-// equally deep -- ends the accepted branch, and the branch's tokens plus the arg-max of its last row are emitted
-// (Sec. 3.4; Sec. 2.1 for the correction token). For a chain this is the longest accepted prefix.
+// Pass 2b, a wavefront per sequence, lane i = node i: a node is verified iff its parent is and its token passes the rule
+// against its parent's row; the deepest verified node -- the first one among equally deep -- ends the accepted branch,
+// and the branch's tokens plus the arg-max of its last row are emitted (Sec. 3.4; Sec. 2.1 for the correction token).
+// For a chain this is the longest accepted prefix. Bound by dependent loads: the nodes' own are made by all lanes at
+// once, and the walk down the tree -- the nodes verified in turn t are those of depth t -- runs on lane masks.
 __global__ __launch_bounds__(64) void accept_scan_kernel(AcceptArgs a) {
-    const int b = blockIdx.x * 64 + threadIdx.x, R = a.K + 1;
-    if (b >= a.B) return;
+    static_assert(LASER_MAX_DRAFT < 64, "a lane per node and one for the correction token");
+    const int b = blockIdx.x, i = threadIdx.x, R = a.K + 1;
     int nn = a.n_nodes[b];
     nn = nn < 0 ? 0 : (nn > a.K ? a.K : nn);
-    unsigned long long ver = 0;                           // bit i: node i is verified
-    unsigned long long dpk[(LASER_MAX_DRAFT + 8) / 8] = {};   // depth of node i, a byte each
-    int best = -1, best_depth = 0;
-    for (int i = 0; i < nn; ++i) {
-        const int par = tree_parent_of(a.parent, b, a.K, i, nn);
+    int par = -1, tok = -1;
+    bool ok = false;
+    if (i < nn) {
+        par = tree_parent_of(a.parent, b, a.K, i, nn);
+        tok = a.tokens[(size_t)b * a.K + i];
         const int c = a.node_cand[(size_t)b * a.K + i];
-        bool ok = c >= 0 && (par < 0 || ((ver >> par) & 1ull));
-        if (ok) {
-            const int prow = b * R + par + 1, rank = a.cand_rank[c];
-            const float q = __expf(a.cand_lx[c] - a.row_mx[prow]) / a.row_sum[prow];
+        const int prow = b * R + par + 1;
+        const float mx = a.row_mx[prow], sum = a.row_sum[prow];
+        if (c >= 0) {
+            const int rank = a.cand_rank[c];
+            const float q = __expf(a.cand_lx[c] - mx) / sum;
             const bool in_k = rank < a.topk, above = q > a.p, top1 = rank == 0;
             ok = a.mode == LASER_MODE_RV ? (in_k && above)
                : a.mode == LASER_MODE_RV_OR_TOP1 ? (top1 || (in_k && above))
                : a.mode == LASER_MODE_TOPK_ONLY ? in_k : (top1 || above);
         }
-        if (ok) {
-            ver |= 1ull << i;
-            int d = 1;
-            if (par >= 0) {
-                unsigned long long w = 0;
-#pragma unroll
-                for (int s = 0; s < (LASER_MAX_DRAFT + 8) / 8; ++s) w = s == (par >> 3) ? dpk[s] : w;
-                d = (int)((w >> ((par & 7) * 8)) & 0xFF) + 1;
-            }
-#pragma unroll
-            for (int s = 0; s < (LASER_MAX_DRAFT + 8) / 8; ++s)
-                if (s == (i >> 3)) dpk[s] |= (unsigned long long)d << ((i & 7) * 8);
-            if (d > best_depth) { best = i; best_depth = d; }
-        }
     }
-    a.accept_len[b] = best_depth;
-    int32_t* out = a.out_tokens + (size_t)b * R;
-    for (int j = best_depth + 1; j < R; ++j) out[j] = -1;
-    out[best_depth] = a.row_arg[b * R + best + 1];
-    for (int i = best, j = best_depth - 1; j >= 0; --j) {
-        out[j] = a.tokens[(size_t)b * a.K + i];
-        if (a.accept_path) a.accept_path[(size_t)b * a.K + j] = i;
-        i = tree_parent_of(a.parent, b, a.K, i, nn);
+    unsigned long long last = __ballot(ok && par < 0);                // the verified nodes of one depth
+    int depth = 0;
+    while (last) {                                                     // a parent comes before its children: at most nn turns
+        ++depth;
+        const unsigned long long now = __ballot(ok && par >= 0 && ((last >> par) & 1ull));
+        if (!now) break;
+        last = now;
     }
-    if (a.accept_path)
-        for (int j = best_depth; j < a.K; ++j) a.accept_path[(size_t)b * a.K + j] = -1;
+    const int best = depth ? __ffsll(last) - 1 : -1;
+    int out = -1, path = -1;
+    for (int j = depth - 1, n = best; j >= 0; --j) {
+        const int t = __shfl(tok, n);
+        if (i == j) { out = t; path = n; }
+        n = __shfl(par, n);
+    }
+    if (i == depth) out = a.row_arg[b * R + best + 1];
+    if (i == 0) a.accept_len[b] = depth;
+    if (i < R) a.out_tokens[(size_t)b * R + i] = out;
+    if (a.accept_path && i < a.K) a.accept_path[(size_t)b * a.K + i] = path;
 }
 
 // Device buffers of the head: the rows' candidate lists, and per (row, vocabulary chunk) the partial statistics that
@@ -311,7 +307,7 @@ static int run_head_bufs(Model* m, const uint16_t* h, const int32_t* tokens, con
                   tokens, parent, n_nodes, M, B, K, hp.chunks, topk, mode, p, hb.row_mx, hb.row_sum, hb.row_arg, hb.cand_rank,
                   accept_len, out_tokens, accept_path};
     hipLaunchKernelGGL(accept_rows_kernel, dim3((M + 3) / 4), dim3(256), 0, stream, aa);
-    hipLaunchKernelGGL(accept_scan_kernel, dim3((B + 63) / 64), dim3(64), 0, stream, aa);
+    hipLaunchKernelGGL(accept_scan_kernel, dim3(B), dim3(64), 0, stream, aa);
     LASER_HIP_CHECK(hipGetLastError());
     return LASER_OK;
 }
