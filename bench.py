@@ -261,11 +261,11 @@ def run_workload(args, name, steps, warmup, weights_cache):
         dom_name, dom_work, bound = "verify_fused_kernel (whole verify step)", step_bytes, "hbm"
     elif M <= 80:
         # dominant kernel: the gate/up projection (largest weight stream of every layer), weight-streaming form
-        dom_name, bound = ("gemm_mid_kernel" if M > 16 else "gemm_skinny_kernel") + "<gate/up SwiGLU>", "hbm"
+        dom_name, bound = ("gemm_tile_kernel" if M > 16 else "gemm_skinny_kernel") + "<gate/up SwiGLU>", "hbm"
         dom_work = 2 * sh.ffn * sh.d * 2 + M * sh.d * 2 + M * sh.ffn * 2
     else:
         # many rows: the same projection runs as the LDS-tiled matrix-core GEMM and is compute-bound
-        dom_name, bound = "gemm_mfma_kernel<gate/up SwiGLU>", "mfma"
+        dom_name, bound = "gemm_tile_kernel<gate/up SwiGLU>", "mfma"
         dom_work = 2.0 * M * 2 * sh.ffn * sh.d
     if bound == "hbm":
         peak, unit, achieved = HBM_PEAK_GBS, "GB/s", (dom_work / dom_avg_s / 1e9 if dom_n else 0.0)
@@ -441,7 +441,7 @@ def run_stress(args):
                    "contexts_matched_2^20": hit_big,
                    "pool_tokens": int(info["n_tokens"]), "pool_keys": int(info["n_keys"]), "pool_device_GB": info["device_bytes"] / 1e9,
                    "pool_generate_s": t_gen, "pool_build_s": t_build},
-        "roofline": {"bound": "mfma", "kernel": "gemm_mfma_kernel<head epilogue>", "achieved": achieved, "peak": MFMA_F16_PEAK_TFLOPS,
+        "roofline": {"bound": "mfma", "kernel": "gemm_tile_kernel<head epilogue>", "achieved": achieved, "peak": MFMA_F16_PEAK_TFLOPS,
                      "unit": "TFLOP/s", "frac": achieved / MFMA_F16_PEAK_TFLOPS, "traffic": None, "flops_per_launch": flops,
                      "avg_launch_us": head_ms * 1e3, "launches": steps, "measured_peak": mfma_tflops,
                      "frac_of_measured_peak": achieved / mfma_tflops,

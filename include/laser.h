@@ -176,7 +176,8 @@ typedef struct laser_model_desc {
 /* Supported: head_dim 64 or 128; d_model, ffn multiples of 128; vocab multiple of 16 (else
  * LASER_E_SHAPE). Allocates workspace and the RoPE table; synchronises `stream`. n_layers may be 0
  * (head-only use). Further allocations happen lazily, inside the first call that needs them:
- * with more than 16 rows a workspace for reduction-split partial results (max_rows * d_model * 32 bytes);
+ * with more than 16 rows a workspace for reduction-split partial results (d_model * 32 bytes per row of max_rows, 48 for
+ * the first 80 if that is more);
  * with more than 80 rows fp16 copies of the four projection matrices and of the head matrix (2 bytes per parameter:
  * the weight memory doubles) for the tiled many-row kernels. That call synchronises the stream; it fails with
  * LASER_E_HIP if the memory is not there and with LASER_E_LIMIT if a weight exceeds the fp16 range (|w| > 65280).
@@ -341,8 +342,8 @@ int laser_generate(laser_model* model, laser_kv* kv, const laser_pool* pool, con
  * kernel that follows, so a given setting is deterministic; different settings may differ in the
  * last bits. Tuning and test knobs: the default is what the benchmark measures.
  * "f16_copies" = 1 (default) or 0: see laser_model_create.
- * "mid_waves" = 0 (default: chosen per launch shape), 4 or 8: waves per workgroup of the weight-streaming
- * GEMM used with 17..80 rows.
+ * "mid_waves" = 0 (default): 17..80 rows take the tiled GEMM; 4 or 8: the one that stages rows through
+ * registers, with that many waves per workgroup.
  * "attn_whole_min" = 0 (default: half the number of compute units) or a count: from this many (sequence, head,
  * 16-row query tile) triples on, the general path's attention walks a context in one workgroup instead of
  * splitting it into 256-token parts that a second kernel merges.

@@ -167,7 +167,7 @@ struct GemmArgs {
     size_t part_floats = 0;
     int want_split = 0;     // 0: choose; 1, 2, 4: force this many reduction parts
     int n_part = 0;         // out: parts left in `part` for the consumer to add up (0: the result is complete)
-    int mid_waves = 0;      // 17..80 rows: 0 = choose the waves per workgroup, 4 or 8 = force
+    int mid_waves = 0;      // 17..80 rows: 4 or 8 = the register-staged kernel with that many waves per workgroup
 };
 
 template <int MB, int EPI, bool SPLIT>

@@ -46,6 +46,86 @@ struct RetrieveArgs {
     const int32_t* own; const int32_t* own_len; int own_cap;
 };
 
+// The chain from its step j0 (1-based; steps before it are done) to its end, over at most 64 Q survivors: pool occurrences
+// cand[0 .. m) and own-text occurrences own_cand[0 .. mo), number i with lane i % 64. Returns the chain's length (j0 - 1: no
+// survivor has a successor) and this lane's smallest surviving positions. Bound by one memory round trip per kAhead steps;
+// with the vote table of retrieve_kernel alone a step was a round trip and four passes over LDS: 4096 lookups of 16 tokens in
+// a pool of 750 k 103 -> 37 us (90 us with one survivor per lane only: the hot keys' lookups, a few hundred occurrences
+// thinned by a tenth per step, decide when the launch ends).
+template <int Q, bool OWN>
+__device__ inline int follow_lanes(const RetrieveArgs& a, const uint32_t* cand, const uint32_t* cand_end, uint32_t m, const uint32_t* own_cand,
+                                   const int32_t* own, uint32_t own_len, uint32_t mo, int j0, int* chain, uint32_t& lane_min, uint32_t& lane_own) {
+    constexpr int kAhead = 8;
+    const int lane = threadIdx.x;
+    uint32_t e[Q], end[Q];
+    const int32_t* text[Q];
+    bool live[Q], mine_own[Q];
+#pragma unroll
+    for (int s = 0; s < Q; ++s) {
+        const uint32_t i = (uint32_t)(s * 64 + lane);
+        live[s] = i < m + mo;
+        mine_own[s] = OWN && live[s] && i >= m;
+        e[s] = mine_own[s] ? own_cand[OWN ? i - m : 0] : live[s] ? cand[i] : 0u;
+        end[s] = mine_own[s] ? own_len : live[s] ? cand_end[i] : 0u;
+        text[s] = mine_own[s] ? own : a.P;
+    }
+    int len = j0 - 1;
+    bool more = true;
+    for (int j = j0; j <= a.K && more; j += kAhead) {
+        int tok[Q][kAhead];
+#pragma unroll
+        for (int s = 0; s < Q; ++s)
+#pragma unroll
+            for (int q = 0; q < kAhead; ++q)
+                tok[s][q] = live[s] && j + q <= a.K && e[s] + (uint32_t)(j + q) < end[s] ? text[s][e[s] + (uint32_t)(j + q)] : 0;
+#pragma unroll
+        for (int q = 0; q < kAhead; ++q) {
+            bool ok[Q];
+            uint64_t rest[Q], win[Q];
+            int left = 0;                              // voters not counted yet
+#pragma unroll
+            for (int s = 0; s < Q; ++s) {
+                ok[s] = more && live[s] && j + q <= a.K && e[s] + (uint32_t)(j + q) < end[s];
+                rest[s] = __ballot(ok[s]);
+                win[s] = 0;
+                left += __popcll(rest[s]);
+            }
+            int win_tok = 0, win_cnt = 0;
+#pragma unroll
+            for (int s = 0; s < Q; ++s)
+                while (rest[s] && left >= win_cnt) {   // larger count, then smaller token id: an equal count can still win
+                    const int t = __builtin_amdgcn_readlane(tok[s][q], __ffsll((unsigned long long)rest[s]) - 1);
+                    uint64_t same[Q];
+                    int c = 0;
+#pragma unroll
+                    for (int u = 0; u < Q; ++u) {
+                        same[u] = u < s ? 0ull : __ballot(ok[u] && tok[u][q] == t);
+                        c += __popcll(same[u]);
+                        rest[u] &= ~same[u];
+                    }
+                    left -= c;
+                    if (c > win_cnt || (c == win_cnt && t < win_tok)) {
+                        win_cnt = c; win_tok = t;
+#pragma unroll
+                        for (int u = 0; u < Q; ++u) win[u] = same[u];
+                    }
+                }
+            if (win_cnt == 0) { more = false; continue; }          // no survivor has a successor left, or K steps are done
+            if (lane == 0) chain[j + q - 1] = win_tok;
+            len = j + q;
+#pragma unroll
+            for (int s = 0; s < Q; ++s) live[s] = (win[s] >> lane) & 1ull;
+        }
+    }
+    lane_min = lane_own = 0xFFFFFFFFu;
+#pragma unroll
+    for (int s = 0; s < Q; ++s) {
+        if (live[s] && !mine_own[s]) lane_min = min(lane_min, e[s]);
+        if (live[s] && mine_own[s]) lane_own = min(lane_own, e[s]);
+    }
+    return len;
+}
+
 // One wavefront (= one workgroup of 64 lanes) per context. OWN: with the temporary branch. Occurrences in the own
 // text are found by a scan of it (it is at most kOwnMax tokens and the wave has it in L2 anyway), always kept
 // in LDS (own_cand, position-ascending) and take part in every vote and filter next to the pool's.
@@ -126,7 +206,18 @@ __global__ __launch_bounds__(64) void retrieve_kernel(RetrieveArgs a) {
         __syncthreads();
 
         int len = 0;
+        bool in_lanes = false;                     // the survivors ended up one to a lane
+        uint32_t lane_min = 0xFFFFFFFFu, lane_own = 0xFFFFFFFFu;      // ... their smallest positions, pool and own text
         for (int j = 1; j <= a.K; ++j) {
+            // At most 256 survivors: each lane follows one, or up to four, to the end. Their next tokens are requested
+            // eight at a time (neighbours in memory), a vote is a ballot per distinct token, ended when no other token can
+            // win, and the filter is the winner's lane masks: no table, no LDS pass, one memory round trip for eight steps.
+            if (in_lds && m + mo <= 256u) {
+                in_lanes = true;
+                if (m + mo <= 64u) len = follow_lanes<1, OWN>(a, cand, cand_end, m, own_cand, own, own_len, mo, j, chain, lane_min, lane_own);
+                else len = follow_lanes<4, OWN>(a, cand, cand_end, m, own_cand, own, own_len, mo, j, chain, lane_min, lane_own);
+                break;
+            }
             int win_tok = -1, win_cnt = 0;
             // The table is only as large as this vote can need (4 slots per voter, 64..kVote): clearing and scanning
             // 1024 slots with one wave cost more than the votes of the few dozen occurrences a typical lookup has.
@@ -269,7 +360,9 @@ __global__ __launch_bounds__(64) void retrieve_kernel(RetrieveArgs a) {
         }
         // ---- smallest surviving position ----
         uint32_t mn = 0xFFFFFFFFu;
-        if (in_lds) {
+        if (in_lanes) {
+            mn = lane_min;
+        } else if (in_lds) {
             for (uint32_t i = lane; i < m; i += 64) mn = min(mn, cand[i]);
         } else {
             for (uint32_t i = lane; i < count; i += 64) {
@@ -284,7 +377,11 @@ __global__ __launch_bounds__(64) void retrieve_kernel(RetrieveArgs a) {
         // pool positions precede the own text's; a result that survives only there is reported as -2 - position
         // (own_cand stays position-ascending through the filters, so its first entry is the smallest)
         long long idx = (long long)mn;
-        if (OWN && mn == 0xFFFFFFFFu) idx = mo > 0 ? -2ll - (long long)own_cand[0] : -1ll;
+        if (OWN && mn == 0xFFFFFFFFu) {
+            uint32_t first_own = in_lanes ? lane_own : mo > 0 ? own_cand[0] : 0xFFFFFFFFu;
+            for (int off = 32; off > 0; off >>= 1) first_own = min(first_own, (uint32_t)__shfl_xor((int)first_own, off));
+            idx = first_own != 0xFFFFFFFFu ? -2ll - (long long)first_own : -1ll;
+        }
 
         if (len >= a.min_tokens) {
             res_len = len; res_n = n; res_idx = idx; done = true;

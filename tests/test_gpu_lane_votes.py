@@ -1,0 +1,45 @@
+"""Lookups whose survivors are followed by a wavefront's lanes, against the oracle, exactly: suffixes with just under, at and over 64,
+256 and 512 occurrences, pool and own text mixed, chains shorter and longer than the tokens requested at a time."""
+import numpy as np
+import pytest
+
+from tests.test_gpu_retrieval import _compare as compare_pool
+from tests.test_gpu_temp_branch import _compare as compare_own
+
+pytestmark = pytest.mark.gpu
+
+
+def _pool(rng, count, vocab):
+    """`count` occurrences of the token 7 followed by texts of 0..40 tokens that agree for a while; some end at once."""
+    trunk = rng.integers(8, 8 + vocab, 40)
+    seqs = []
+    for _ in range(count):
+        t = trunk.copy()
+        cut = int(rng.integers(0, 41))
+        t[cut:] = rng.integers(8, 8 + vocab, 40 - cut)
+        seqs.append([7] + t[:max(1, int(rng.integers(0, 41)))].tolist())
+    off = np.cumsum([0] + [len(s) for s in seqs]).astype(np.int64)
+    return np.concatenate(seqs).astype(np.int32), off, np.full(count, 3, np.int64), trunk
+
+
+@pytest.mark.parametrize("count", [1, 2, 63, 64, 65, 255, 256, 257, 512, 513])
+@pytest.mark.parametrize("K", [1, 8, 9, 16, 63])
+def test_counts_around_a_wave(count, K):
+    rng = np.random.default_rng(count * 100 + K)
+    toks, off, keys, _ = _pool(rng, count, 3)
+    compare_pool(toks, off, keys, [3, 3, 4], [[1, 7], [toks[0], toks[1]], [1, 7]], 1, 2, K)
+    compare_pool(toks, off, keys, [3], [[1, 7]], 1, 2, K, mt=min(K, 5))
+
+
+@pytest.mark.parametrize("count", [1, 40, 62, 63, 64, 200, 254, 255])
+@pytest.mark.parametrize("vocab", [2, 1000])
+def test_pool_and_own_text_share_the_lanes(count, vocab):
+    rng = np.random.default_rng(count + vocab)
+    toks, off, keys, trunk = _pool(rng, count, vocab)
+    owns = []
+    for reps in (0, 1, 2, 24, 70):
+        own = []
+        for _ in range(reps):
+            own += [7] + trunk[:int(rng.integers(1, 12))].tolist()
+        owns.append(own + [5, 7])
+    compare_own(toks, off, keys, [3, 3, 3, 3, 9], owns, 1, 2, 12)
