@@ -563,7 +563,73 @@ __global__ __launch_bounds__(64) void retrieve_tree_kernel(TreeArgs a) {
             fsize += n_ch;
             __syncthreads();
         };
-        expand(-1, 0);
+        // The same for at most 256 occurrences, four to a lane: each carries a bit per taken node it continues with, so
+        // that a path is not walked again (one token decides the newest bit), and children are counted with a ballot per
+        // distinct token instead of through the vote table: 8 trees of 16 nodes 90 -> 49 us.
+        constexpr int Q = 4;
+        const bool in_lanes = count <= 64u * Q;
+        uint32_t le[Q], lend[Q], lbits[Q];
+#pragma unroll
+        for (int s = 0; s < Q; ++s) {
+            const uint32_t i = (uint32_t)(s * 64 + lane);
+            const bool have = in_lanes && i < count;
+            le[s] = have ? cand[i] : 0u;
+            lend[s] = have ? cand_end[i] : 0u;         // an idle lane has no successor
+            lbits[s] = 0u;
+        }
+        auto expand_lanes = [&](int node, int d) {
+            const int want = a.K - taken;
+            const int par = node >= 0 ? t_par[node] : -1, own_tok = node >= 0 ? t_tok[node] : 0;
+            int tok[Q];
+            uint64_t rest[Q];
+            bool ok[Q];
+            int left = 0;                                            // occurrences not counted yet
+#pragma unroll
+            for (int s = 0; s < Q; ++s) {
+                const bool reach = (par < 0 || ((lbits[s] >> par) & 1u)) && le[s] + (uint32_t)d < lend[s];
+                const int at = node >= 0 && reach ? a.P[le[s] + (uint32_t)d] : 0;
+                const bool more = reach && le[s] + (uint32_t)d + 1u < lend[s];
+                tok[s] = more ? a.P[le[s] + (uint32_t)d + 1u] : 0;
+                const bool in = node < 0 || (reach && at == own_tok);
+                if (node >= 0 && in) lbits[s] |= 1u << node;
+                ok[s] = in && more;
+            }
+#pragma unroll
+            for (int s = 0; s < Q; ++s) { rest[s] = __ballot(ok[s]); left += __popcll(rest[s]); }
+            int n_ch = 0;
+#pragma unroll
+            for (int s = 0; s < Q; ++s)
+                while (rest[s] && (n_ch < want || left >= ch_cnt[want - 1])) {      // an equal count can still enter
+                    const int t = __builtin_amdgcn_readlane(tok[s], __ffsll((unsigned long long)rest[s]) - 1);
+                    int c = 0;
+#pragma unroll
+                    for (int u = s; u < Q; ++u) {
+                        const uint64_t same = __ballot(ok[u] && tok[u] == t);
+                        c += __popcll(same);
+                        rest[u] &= ~same;
+                    }
+                    left -= c;
+                    int pos = n_ch;                                  // as above: count desc, token asc
+                    while (pos > 0 && (ch_cnt[pos - 1] < c || (ch_cnt[pos - 1] == c && ch_tok[pos - 1] > t))) --pos;
+                    __syncthreads();
+                    if (pos < want) {
+                        const int last = n_ch < want ? n_ch : want - 1;
+                        if (lane == 0) {
+                            for (int q = last; q > pos; --q) { ch_tok[q] = ch_tok[q - 1]; ch_cnt[q] = ch_cnt[q - 1]; }
+                            ch_tok[pos] = t; ch_cnt[pos] = c;
+                        }
+                        if (n_ch < want) ++n_ch;
+                    }
+                    __syncthreads();
+                }
+            for (int i = lane; i < n_ch; i += 64) {
+                f_tok[fsize + i] = ch_tok[i]; f_cnt[fsize + i] = ch_cnt[i]; f_par[fsize + i] = node; f_depth[fsize + i] = d + 1;
+            }
+            fsize += n_ch;
+            __syncthreads();
+        };
+        if (in_lanes) expand_lanes(-1, 0);
+        else expand(-1, 0);
         while (taken < a.K && fsize > 0) {
             // best frontier entry: count desc, depth asc, parent asc, token asc
             int bi = -1, bc = 0, bd = 0, bp = 0, bt = 0;
@@ -588,7 +654,10 @@ __global__ __launch_bounds__(64) void retrieve_tree_kernel(TreeArgs a) {
             --fsize;
             ++taken;
             __syncthreads();
-            if (taken < a.K) expand(taken - 1, bd);
+            if (taken < a.K) {
+                if (in_lanes) expand_lanes(taken - 1, bd);
+                else expand(taken - 1, bd);
+            }
         }
         // ---- pseudo-sequence: depth-first, siblings in the order taken ----
         if (lane == 0) {

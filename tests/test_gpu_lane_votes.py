@@ -5,6 +5,7 @@ import pytest
 
 from tests.test_gpu_retrieval import _compare as compare_pool
 from tests.test_gpu_temp_branch import _compare as compare_own
+from tests.test_gpu_tree import _check_trees as compare_trees
 
 pytestmark = pytest.mark.gpu
 
@@ -43,3 +44,13 @@ def test_pool_and_own_text_share_the_lanes(count, vocab):
             own += [7] + trunk[:int(rng.integers(1, 12))].tolist()
         owns.append(own + [5, 7])
     compare_own(toks, off, keys, [3, 3, 3, 3, 9], owns, 1, 2, 12)
+
+
+@pytest.mark.parametrize("count", [1, 63, 64, 65, 255, 256, 257])
+@pytest.mark.parametrize("K", [1, 8, 32])
+@pytest.mark.parametrize("vocab", [2, 1000])
+def test_trees_around_four_waves(count, K, vocab):
+    rng = np.random.default_rng(count * 100 + K + vocab)
+    toks, off, keys, _ = _pool(rng, count, vocab)
+    compare_trees((toks, off, keys), [[1, 7], toks[:2].tolist(), [5]], [3, 3, 3], 1, 2, K)
+    compare_trees((toks, off, keys), [[1, 7]], [3], 1, 2, K, min_tokens=min(K, 5))
