@@ -27,6 +27,7 @@ namespace laser {
 // ------------------------------------------------------------------------------------ kernel
 constexpr int kCand = 512;         // occurrences a wave keeps in LDS (more: streamed from the index, re-checked against the chain)
 constexpr int kVote = 512;         // vote-table slots (power of two; wider votes are partitioned)
+constexpr int kGroups = 4;          // groups of 64 occurrences whose loads a vote has in flight together
 constexpr int kEmptyTok = -1;
 constexpr int kOwnMax = LASER_MAX_OWN_TEXT;   // tokens of a sequence's own text (temporary branch) a lookup can take
 
@@ -235,42 +236,62 @@ __global__ __launch_bounds__(64) void retrieve_kernel(RetrieveArgs a) {
                     __syncthreads();
                     const uint32_t total_pool = in_lds ? m : count;
                     const uint32_t total = total_pool + mo;
-                    for (uint32_t i0 = 0; i0 < total; i0 += 64) {
-                        uint32_t i = i0 + lane;
-                        if (i < total) {
-                            bool ok;
-                            int tok = 0;
-                            if (i < total_pool) {
-                                uint32_t e = in_lds ? cand[i] : a.sa[start + i];
-                                ok = (e + (uint32_t)j) < (in_lds ? cand_end[i] : a.seq_end[e]);
-                                if (ok && !in_lds)
-                                    for (int c = 1; c < j; ++c) ok = ok && (a.P[e + c] == chain[c - 1]);
-                                if (ok) tok = a.P[e + j];
-                                if (in_lds) cand_tok[i] = ok ? tok : -1;
-                            } else {
-                                const uint32_t e = own_cand[OWN ? i - total_pool : 0];
-                                ok = e + (uint32_t)j < own_len;
-                                if (ok) tok = own[e + j];
+                    // Four groups of 64 voters at a time, every kind of load of all four before the first is used: a run that
+                    // is streamed from the index is a chain of round trips per group.
+                    for (uint32_t i0 = 0; i0 < total; i0 += 64 * kGroups) {
+                        uint32_t e[kGroups], end[kGroups];
+                        int tok[kGroups];
+                        bool ok[kGroups];
+#pragma unroll
+                        for (int u = 0; u < kGroups; ++u) {
+                            const uint32_t i = i0 + u * 64 + lane;
+                            e[u] = i < total_pool ? (in_lds ? cand[i] : a.sa[start + i]) : 0u;
+                        }
+#pragma unroll
+                        for (int u = 0; u < kGroups; ++u) {
+                            const uint32_t i = i0 + u * 64 + lane;
+                            end[u] = i < total_pool ? (in_lds ? cand_end[i] : a.seq_end[e[u]]) : 0u;
+                        }
+#pragma unroll
+                        for (int u = 0; u < kGroups; ++u) ok[u] = e[u] + (uint32_t)j < end[u];
+                        if (!in_lds)
+                            for (int c = 1; c < j; ++c) {
+                                int t[kGroups];
+#pragma unroll
+                                for (int u = 0; u < kGroups; ++u) t[u] = ok[u] ? a.P[e[u] + c] : -1;
+#pragma unroll
+                                for (int u = 0; u < kGroups; ++u) ok[u] = ok[u] && t[u] == chain[c - 1];
                             }
-                            if (ok) {
-                                uint32_t hh = fmix32((uint32_t)tok);
+#pragma unroll
+                        for (int u = 0; u < kGroups; ++u) tok[u] = ok[u] ? a.P[e[u] + j] : 0;
+#pragma unroll
+                        for (int u = 0; u < kGroups; ++u) {
+                            const uint32_t i = i0 + u * 64 + lane;
+                            if (in_lds && i < total_pool) cand_tok[i] = ok[u] ? tok[u] : -1;
+                            if (OWN && i >= total_pool && i < total) {
+                                const uint32_t eo = own_cand[OWN ? i - total_pool : 0];
+                                ok[u] = eo + (uint32_t)j < own_len;
+                                if (ok[u]) tok[u] = own[eo + j];
+                            }
+                            if (ok[u]) {
+                                uint32_t hh = fmix32((uint32_t)tok[u]);
                                 if (nparts == 1 || (hh / kVote) % nparts == part) {
                                     uint32_t s = hh & (vsz - 1);
                                     for (int probe = 0; probe < vsz; ++probe) {
                                         int cur = vote_tok[s];
                                         if (cur == kEmptyTok) {
-                                            int prev = atomicCAS(&vote_tok[s], kEmptyTok, tok);
-                                            if (prev == kEmptyTok) { atomicAdd(&sh_distinct, 1); cur = tok; }
+                                            int prev = atomicCAS(&vote_tok[s], kEmptyTok, tok[u]);
+                                            if (prev == kEmptyTok) { atomicAdd(&sh_distinct, 1); cur = tok[u]; }
                                             else cur = prev;
                                         }
-                                        if (cur == tok) { atomicAdd(&vote_cnt[s], 1); break; }
+                                        if (cur == tok[u]) { atomicAdd(&vote_cnt[s], 1); break; }
                                         s = (s + 1) & (vsz - 1);
                                     }
                                 }
                             }
                         }
                         // stop feeding a table that is getting too full; the pass will be split
-                        if ((i0 & 1023u) == 960u) {
+                        if ((i0 & 1023u) == 1024u - 64 * kGroups) {
                             __syncthreads();
                             if (sh_distinct > vfill) break;
                         }
@@ -320,19 +341,29 @@ __global__ __launch_bounds__(64) void retrieve_kernel(RetrieveArgs a) {
                 __syncthreads();
                 if ((uint32_t)win_cnt <= (uint32_t)kCand) {   // few enough now: materialise
                     uint32_t out = 0;
-                    for (uint32_t i0 = 0; i0 < count; i0 += 64) {
-                        uint32_t i = i0 + lane;
-                        uint32_t e = 0, end = 0; bool keep = false;
-                        if (i < count) {
-                            e = a.sa[start + i];
-                            end = a.seq_end[e];
-                            keep = (e + (uint32_t)j) < end;
-                            for (int c = 1; c <= j && keep; ++c) keep = (a.P[e + c] == chain[c - 1]);
+                    for (uint32_t i0 = 0; i0 < count; i0 += 64 * kGroups) {
+                        uint32_t e[kGroups], end[kGroups];
+                        bool keep[kGroups];
+#pragma unroll
+                        for (int u = 0; u < kGroups; ++u) e[u] = i0 + u * 64 + lane < count ? a.sa[start + i0 + u * 64 + lane] : 0u;
+#pragma unroll
+                        for (int u = 0; u < kGroups; ++u) end[u] = i0 + u * 64 + lane < count ? a.seq_end[e[u]] : 0u;
+#pragma unroll
+                        for (int u = 0; u < kGroups; ++u) keep[u] = e[u] + (uint32_t)j < end[u];
+                        for (int c = 1; c <= j; ++c) {
+                            int t[kGroups];
+#pragma unroll
+                            for (int u = 0; u < kGroups; ++u) t[u] = keep[u] ? a.P[e[u] + c] : -1;
+#pragma unroll
+                            for (int u = 0; u < kGroups; ++u) keep[u] = keep[u] && t[u] == chain[c - 1];
                         }
-                        uint64_t mask = __ballot(keep);
-                        uint32_t pos = out + __popcll(mask & ((1ull << lane) - 1ull));
-                        if (keep) { cand[pos] = e; cand_end[pos] = end; }
-                        out += __popcll(mask);
+#pragma unroll
+                        for (int u = 0; u < kGroups; ++u) {
+                            const uint64_t mask = __ballot(keep[u]);
+                            const uint32_t pos = out + __popcll(mask & ((1ull << lane) - 1ull));
+                            if (keep[u]) { cand[pos] = e[u]; cand_end[pos] = end[u]; }
+                            out += __popcll(mask);
+                        }
                     }
                     m = out;
                     in_lds = true;
