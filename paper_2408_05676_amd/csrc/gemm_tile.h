@@ -153,7 +153,11 @@ void gemm_tile_kernel(GemmTileArgs a) {
         if constexpr (!WF16) {
 #pragma unroll
             for (int j = 0; j < WN; ++j) bf16x8_to_f16x8(fw[s][j]);
-            asm volatile("s_nop 1");                         // vector write -> matrix read
+            // Vector write -> matrix read takes two wait states, which the compiler keeps for its own matrix instructions only.
+            // Every fragment is an operand of the statements up to the wait, so no conversion can be moved behind it.
+#pragma unroll
+            for (int j = 0; j + 1 < WN; ++j) asm volatile("" : "+v"(fw[s][j].v4));
+            asm volatile("s_nop 1" : "+v"(fw[s][WN - 1].v4));
         }
         static_for<0, NMUL>([&](auto mc) {
             constexpr int m = decltype(mc)::value;
