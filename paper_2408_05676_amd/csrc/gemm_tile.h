@@ -7,6 +7,7 @@
 
 namespace laser {
 
+typedef unsigned u32x4a2 __attribute__((ext_vector_type(4), aligned(2)));
 typedef float float4a4_t __attribute__((ext_vector_type(4), aligned(4)));   // a caller's buffer may be aligned to its elements only
 
 struct GemmTileArgs {

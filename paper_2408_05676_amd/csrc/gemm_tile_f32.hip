@@ -16,6 +16,7 @@ static int go(const GemmTileArgs& t, int ncu, int want_split, int max_split, hip
 }
 
 int launch_tile_f32(const GemmTileArgs& t, bool f16, int ncu, int want_split, int max_split, hipStream_t stream) {
+    if (!on_16_byte_grid(t.W)) return launch_off_grid_f32(t, ncu, want_split, max_split, stream);
     if (t.Xlo) return f16 ? go<true, true>(t, ncu, want_split, max_split, stream) : go<true, false>(t, ncu, want_split, max_split, stream);
     return f16 ? go<false, true>(t, ncu, want_split, max_split, stream) : go<false, false>(t, ncu, want_split, max_split, stream);
 }

@@ -14,6 +14,7 @@ static void go(const GemmTileArgs& t, int ncu, hipStream_t stream) {
 }
 
 void launch_tile_head(const GemmTileArgs& t, bool f16, int ncu, hipStream_t stream) {
+    if (!on_16_byte_grid(t.W)) return launch_off_grid_head(t, stream);
     if (t.hp.topk <= 2) { if (f16) go<GEPI_HEAD2, true>(t, ncu, stream); else go<GEPI_HEAD2, false>(t, ncu, stream); }
     else { if (f16) go<GEPI_HEAD, true>(t, ncu, stream); else go<GEPI_HEAD, false>(t, ncu, stream); }
 }

@@ -67,5 +67,12 @@ void launch_tile_swiglu(const GemmTileArgs& t, bool f16, int ncu, hipStream_t st
 int launch_few_f32(const GemmTileArgs& t, int ncu, int want_split, int max_split, hipStream_t stream);
 void launch_few_swiglu(const GemmTileArgs& t, int ncu, hipStream_t stream);
 void launch_tile_head(const GemmTileArgs& t, bool f16, int ncu, hipStream_t stream);
+// The same for t.W bf16 off the 16-byte grid, more than 80 rows (gemm_off_grid.hip).
+int launch_off_grid_f32(const GemmTileArgs& t, int ncu, int want_split, int max_split, hipStream_t stream);
+void launch_off_grid_swiglu(const GemmTileArgs& t, hipStream_t stream);
+void launch_off_grid_head(const GemmTileArgs& t, hipStream_t stream);
+
+// Loads into LDS need it: the library's own buffers and copies are on the grid, a caller's weights and rows may not be.
+inline bool on_16_byte_grid(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
 }  // namespace laser

@@ -9,7 +9,8 @@
 //             in registers (chunk = wavefront).
 //   M <= 80   the weight-streaming kernel of gemm_mid.h with its head epilogue (chunk = workgroup, 64 or 128
 //             vocabulary entries): the head matrix is read once.
-//   more      the LDS-tiled matrix-core GEMM of gemm_tile.h with its head epilogue (chunk = a wave's 128 columns).
+//   more      the LDS-tiled matrix-core GEMM of gemm_tile.h with its head epilogue (chunk = a wave's 128 columns); rows off
+//             the 16-byte grid are copied onto it first (1024 rows at a 128 k vocabulary: 1205 us, on the grid 1198).
 // Pass 2: a wavefront per row merges the per-chunk partials. The draft's rank is the number of partial-list entries
 // ordered before it; if a chunk hides an entry that precedes the draft, that chunk already contributes
 // >= LASER_MAX_TOPK >= k listed ones, so "rank < k" is exact. A wavefront per sequence then examines the nodes
@@ -259,6 +260,12 @@ int head_chunks_cap(const Model* m) {
     return std::max(m->head_chunks, std::max(head_chunks_for(m, kHeadMidMaxRows), head_chunks_for(m, kHeadMidMaxRows + 1)));
 }
 
+// Rows off the 16-byte grid onto it, for loads into LDS; n8: groups of eight values.
+__global__ __launch_bounds__(256) void copy_rows_kernel(const uint16_t* __restrict__ src, uint16_t* __restrict__ dst, size_t n8) {
+    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+    if (i < n8) *reinterpret_cast<u32x4*>(dst + i * 8) = *reinterpret_cast<const u32x4a2*>(src + i * 8);
+}
+
 // candidates -> pass 1 -> acceptance. Allocates nothing. tokens / parent / n_nodes: the drafts as a pseudo-sequence
 // (parent == NULL: a chain, n_nodes = draft_len).
 static int run_head_bufs(Model* m, const uint16_t* h, const int32_t* tokens, const int32_t* parent, const int32_t* n_nodes, int B, int K,
@@ -268,7 +275,6 @@ static int run_head_bufs(Model* m, const uint16_t* h, const int32_t* tokens, con
     hipLaunchKernelGGL(head_cands_kernel, dim3(B), dim3(64), 0, stream, tokens, parent, n_nodes, B, K, V,
                        hb.cand_beg, hb.cand_cnt, hb.cand_x, hb.node_cand, hb.cand_lx);
     HeadPart hp{hb.cand_beg, hb.cand_cnt, hb.cand_x, hb.cand_lx, hb.hp_max, hb.hp_sum, hb.hp_arg, hb.hp_topv, hb.hp_topi, 0, topk, logits_dbg};
-    const bool aligned = ((reinterpret_cast<uintptr_t>(h) | (m->f16_copies ? 0 : reinterpret_cast<uintptr_t>(m->d.wlm))) & 15) == 0;
     if (M <= kHeadStreamMaxRows) {
         const int ntiles = V / 16;
         const int tpw = (ntiles + 1023) / 1024;
@@ -276,20 +282,11 @@ static int run_head_bufs(Model* m, const uint16_t* h, const int32_t* tokens, con
         HeadArgs a{m->d.wlm, h, M, V, dm, tpw, hp};
         dim3 grid((unsigned)((m->head_chunks + 3) / 4), 1u);         // at most 16 rows: one row tile
         hipLaunchKernelGGL(lm_head_kernel<1>, grid, dim3(256), 0, stream, a);
-    } else if ((M <= kHeadMidMaxRows || !aligned) && dm % kGemmKStep == 0) {
-        // up to kHeadMidMaxRows rows at a time: all of them, except where more rows or their matrix lie off the 16-byte grid
-        // that loads into LDS need
-        const GemmMidPlan pl = gemm_mid_plan(std::min(M, kHeadMidMaxRows), V, dm, 1, false, 0);
+    } else if (M <= kHeadMidMaxRows && dm % kGemmKStep == 0) {
+        const GemmMidPlan pl = gemm_mid_plan(M, V, dm, 1, false, 0);
         hp.chunks = (V / 16 + pl.NW - 1) / pl.NW;                     // = workgroups of the launch
-        for (int r0 = 0; r0 < M; r0 += kHeadMidMaxRows) {
-            HeadPart part = hp;
-            const size_t rec = (size_t)r0 * hp.chunks;
-            part.cand_beg += r0; part.cand_cnt += r0;
-            part.hp_max += rec; part.hp_sum += rec; part.hp_arg += rec; part.hp_topv += rec * KT; part.hp_topi += rec * KT;
-            if (part.logits_dbg) part.logits_dbg += (size_t)r0 * V;
-            GemmMidArgs t{m->d.wlm, h + (size_t)r0 * dm, nullptr, std::min(M - r0, kHeadMidMaxRows), V, dm, nullptr, nullptr, nullptr, part};
-            launch_gemm_mid<EPI_HEAD, false>(t, pl, stream);
-        }
+        GemmMidArgs t{m->d.wlm, h, nullptr, M, V, dm, nullptr, nullptr, nullptr, hp};
+        launch_gemm_mid<EPI_HEAD, false>(t, pl, stream);
     } else {
         hp.chunks = (V + 127) / 128;
         if (m->f16_copies && !m->wlm16) {          // first many-row head: widen the head matrix to fp16 once
@@ -297,6 +294,11 @@ static int run_head_bufs(Model* m, const uint16_t* h, const int32_t* tokens, con
             const size_t n[1] = {(size_t)V * dm};
             const int rc = widen_copies(src, n, 1, &m->wlm16, stream);
             if (rc) return rc;
+        }
+        if (!on_16_byte_grid(h)) {
+            const size_t n8 = (size_t)M * dm / 8;
+            hipLaunchKernelGGL(copy_rows_kernel, dim3((unsigned)((n8 + 255) / 256)), dim3(256), 0, stream, h, m->xn, n8);
+            h = m->xn;
         }
         int ncu = 0;
         LASER_HIP_CHECK(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, 0));

@@ -293,14 +293,11 @@ template <int EPI>
 static int launch_gemm(GemmArgs& a_in, hipStream_t stream) {
     GemmArgs& a = a_in;
     a.n_part = 0;
-    // Loads into LDS take 16-byte aligned operands; the library's own buffers are, a caller's weights may not be.
-    const uint16_t* const w_tile = a.M > kSkinnyMaxRows && a.W16 ? a.W16 : a.W;
-    const bool aligned = (reinterpret_cast<uintptr_t>(w_tile) & 15) == 0;
-    const bool few = a.M > 16 && a.M <= kSkinnyMaxRows && a.mid_waves == 0 && (EPI != EPI_SWIGLU || a.Xlo);
-    if (aligned && (a.M > kSkinnyMaxRows || few)) {
+    const bool few = a.M > 16 && a.M <= kSkinnyMaxRows && a.mid_waves == 0 && (EPI != EPI_SWIGLU || a.Xlo) && on_16_byte_grid(a.W);
+    if (a.M > kSkinnyMaxRows || few) {
         int ncu = 0;
         LASER_HIP_CHECK(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, 0));
-        GemmTileArgs t{w_tile, a.X, a.Xlo, a.M, a.N, a.Kd, 0, 0, 1, nullptr, a.outh};
+        GemmTileArgs t{!few && a.W16 ? a.W16 : a.W, a.X, a.Xlo, a.M, a.N, a.Kd, 0, 0, 1, nullptr, a.outh};
         if constexpr (EPI == EPI_SWIGLU) {
             if (few) launch_few_swiglu(t, ncu, stream);
             else launch_tile_swiglu(t, a.W16 != nullptr, ncu, stream);
@@ -320,18 +317,13 @@ static int launch_gemm(GemmArgs& a_in, hipStream_t stream) {
     const int ntiles = a.N / 16;
     const int mblocks = (a.M + 15) / 16;
     if (mblocks >= 2 && (a.Xlo || EPI == EPI_RESID) && a.Kd % kGemmKStep == 0) {
-        // option mid_waves, or weights off the 16-byte grid: activations staged through registers, up to 80 rows at a time
-        for (int r0 = 0; r0 < a.M; r0 += kSkinnyMaxRows) {
-            const int M = std::min(a.M - r0, kSkinnyMaxRows);
-            const size_t in = (size_t)r0 * a.Kd, out = (size_t)r0 * a.N;
-            GemmMidArgs t{a.W, a.X + in, a.Xlo ? a.Xlo + in : nullptr, M, a.N, a.Kd, a.outf ? a.outf + out : nullptr, a.outh ? a.outh + out : nullptr, a.part};
-            const bool parts = a.part && a.M <= kSkinnyMaxRows;
-            const GemmMidPlan pl = gemm_mid_plan(M, a.N, a.Kd, a.Xlo ? 2 : 1, EPI == EPI_SWIGLU, parts ? a.part_floats : 0, a.mid_waves);
-            if (a.Xlo) launch_gemm_mid<EPI, true>(t, pl, stream);
-            else if constexpr (EPI == EPI_RESID) launch_gemm_mid<EPI, false>(t, pl, stream);
-            LASER_HIP_CHECK(hipGetLastError());
-            a.n_part = pl.S > 1 ? pl.S : 0;
-        }
+        // option mid_waves, or weights off the 16-byte grid: activations staged in LDS through registers
+        GemmMidArgs t{a.W, a.X, a.Xlo, a.M, a.N, a.Kd, a.outf, a.outh, a.part};
+        const GemmMidPlan pl = gemm_mid_plan(a.M, a.N, a.Kd, a.Xlo ? 2 : 1, EPI == EPI_SWIGLU, a.part ? a.part_floats : 0, a.mid_waves);
+        if (a.Xlo) launch_gemm_mid<EPI, true>(t, pl, stream);
+        else if constexpr (EPI == EPI_RESID) launch_gemm_mid<EPI, false>(t, pl, stream);
+        LASER_HIP_CHECK(hipGetLastError());
+        a.n_part = pl.S > 1 ? pl.S : 0;
         return LASER_OK;
     }
     const int MB = mblocks >= 5 ? 5 : mblocks;
@@ -794,9 +786,8 @@ static int forward(Model* m, KV* kv, const int32_t* ids_dev, const int32_t* pend
         if ((rc = launch_gemm<EPI_RESID>(go, stream))) return rc;
         launch_rmsnorm(M, stream, m->x, d.g2 + (size_t)l * dm, dm, d.eps, m->xn, m->xn_lo, (const float*)m->kpart, go.n_part, (size_t)M * dm);
         // On the tiled many-row path a split operand doubles the matrix work; gate/up (45 % of the layer's
-        // flops) takes the single fp16 rows there unless option "split_ffn" asks for the split (see set_option). The kernel
-        // for weights off the 16-byte grid knows the split form only.
-        const bool split_gu = M <= kSkinnyMaxRows || m->split_ffn || (!many && (reinterpret_cast<uintptr_t>(d.wgu) & 15) != 0);
+        // flops) takes the single fp16 rows there unless option "split_ffn" asks for the split (see set_option).
+        const bool split_gu = M <= kSkinnyMaxRows || m->split_ffn;
         GemmArgs gg{d.wgu + (size_t)l * 2 * F * dm, many ? m->w16[2] + (size_t)l * 2 * F * dm : nullptr, m->xn, split_gu ? m->xn_lo : nullptr, M, F, dm, 1, nullptr, m->act};
         gg.mid_waves = m->mid_waves;
         const bool prof = m->prof_on && m->prof_n < m->prof_cap;
