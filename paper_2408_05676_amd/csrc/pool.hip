@@ -18,6 +18,7 @@
 #include <cstring>
 #include <numeric>
 #include <thread>
+#include <type_traits>
 #include <vector>
 
 #include "pool.h"
@@ -53,10 +54,17 @@ struct RetrieveArgs {
 // with the vote table of retrieve_kernel alone a step was a round trip and four passes over LDS: 4096 lookups of 16 tokens in
 // a pool of 750 k 103 -> 37 us (90 us with one survivor per lane only: the hot keys' lookups, a few hundred occurrences
 // thinned by a tenth per step, decide when the launch ends).
-template <int Q, bool OWN>
+// A ballot counts one token, in 0.13 us at Q = 4: a vote that is still open after kBallots of them goes through the vote
+// table (vote_tok, vote_cnt: kVote slots, more than there are voters). 2048 lookups over 256 occurrences, all with successors of
+// their own, K = 1 / 4 / 16: ballots alone 47.8 / 48.8 / 56.4 us, now 14.6 / 14.3 / 27.4; votes by the table alone 14.1 /
+// 20.1 / 45.0. Occurrences that agree but for a tenth per step: ballots alone 10.1 / 11.1 / 20.0, now 12.5 / 9.6 / 20.3,
+// the table alone 12.0 / 29.4 / 75.2.
+template <int Q, int kAhead, bool OWN>
 __device__ inline int follow_lanes(const RetrieveArgs& a, const uint32_t* cand, const uint32_t* cand_end, uint32_t m, const uint32_t* own_cand,
-                                   const int32_t* own, uint32_t own_len, uint32_t mo, int j0, int* chain, uint32_t& lane_min, uint32_t& lane_own) {
-    constexpr int kAhead = 8;
+                                   const int32_t* own, uint32_t own_len, uint32_t mo, int j0, int* chain, int* vote_tok, int* vote_cnt,
+                                   uint32_t& lane_min, uint32_t& lane_own) {
+    constexpr int kBallots = 8;
+    static_assert(64 * Q < kVote, "every voter may bring a token of its own");
     const int lane = threadIdx.x;
     uint32_t e[Q], end[Q];
     const int32_t* text[Q];
@@ -72,7 +80,9 @@ __device__ inline int follow_lanes(const RetrieveArgs& a, const uint32_t* cand, 
     }
     int len = j0 - 1;
     bool more = true;
-    for (int j = j0; j <= a.K && more; j += kAhead) {
+    for (int j = j0, next; j <= a.K && more; j = next) {
+        next = j + kAhead;
+        int open = 0;                                  // step whose vote the ballots left open
         int tok[Q][kAhead];
 #pragma unroll
         for (int s = 0; s < Q; ++s)
@@ -91,10 +101,11 @@ __device__ inline int follow_lanes(const RetrieveArgs& a, const uint32_t* cand, 
                 win[s] = 0;
                 left += __popcll(rest[s]);
             }
-            int win_tok = 0, win_cnt = 0;
+            int win_tok = 0, win_cnt = 0, ballots = 0;
 #pragma unroll
             for (int s = 0; s < Q; ++s)
                 while (rest[s] && left >= win_cnt) {   // larger count, then smaller token id: an equal count can still win
+                    if (Q > 1 && ballots++ == kBallots) { left = -1; break; }
                     const int t = __builtin_amdgcn_readlane(tok[s][q], __ffsll((unsigned long long)rest[s]) - 1);
                     uint64_t same[Q];
                     int c = 0;
@@ -111,11 +122,47 @@ __device__ inline int follow_lanes(const RetrieveArgs& a, const uint32_t* cand, 
                         for (int u = 0; u < Q; ++u) win[u] = same[u];
                     }
                 }
+            if (Q > 1 && left < 0) { open = j + q; win_cnt = 0; }
             if (win_cnt == 0) { more = false; continue; }          // no survivor has a successor left, or K steps are done
             if (lane == 0) chain[j + q - 1] = win_tok;
             len = j + q;
 #pragma unroll
             for (int s = 0; s < Q; ++s) live[s] = (win[s] >> lane) & 1ull;
+        }
+        if (Q > 1 && open) {
+            int t[Q];
+#pragma unroll
+            for (int s = 0; s < Q; ++s) t[s] = live[s] && e[s] + (uint32_t)open < end[s] ? text[s][e[s] + (uint32_t)open] : -1;
+            for (int i = lane; i < kVote; i += 64) { vote_tok[i] = kEmptyTok; vote_cnt[i] = 0; }
+            __syncthreads();
+#pragma unroll
+            for (int s = 0; s < Q; ++s)
+                if (t[s] >= 0) {
+                    uint32_t at = fmix32((uint32_t)t[s]) & (kVote - 1);
+                    for (;;) {
+                        const int was = atomicCAS(&vote_tok[at], kEmptyTok, t[s]);
+                        if (was == kEmptyTok || was == t[s]) break;
+                        at = (at + 1) & (kVote - 1);
+                    }
+                    atomicAdd(&vote_cnt[at], 1);
+                }
+            __syncthreads();
+            int bt = 0, bc = 0;
+            for (int i = lane; i < kVote; i += 64) {
+                const int c = vote_cnt[i], tk = vote_tok[i];
+                if (c > bc || (c == bc && c > 0 && tk < bt)) { bc = c; bt = tk; }
+            }
+            for (int off = 32; off > 0; off >>= 1) {
+                const int oc = __shfl_xor(bc, off), ot = __shfl_xor(bt, off);
+                if (oc > bc || (oc == bc && oc > 0 && ot < bt)) { bc = oc; bt = ot; }
+            }
+            __syncthreads();
+            if (lane == 0) chain[open - 1] = bt;
+            len = open;
+#pragma unroll
+            for (int s = 0; s < Q; ++s) live[s] = t[s] == bt;
+            next = open + 1;
+            more = true;
         }
     }
     lane_min = lane_own = 0xFFFFFFFFu;
@@ -210,13 +257,22 @@ __global__ __launch_bounds__(64) void retrieve_kernel(RetrieveArgs a) {
         bool in_lanes = false;                     // the survivors ended up one to a lane
         uint32_t lane_min = 0xFFFFFFFFu, lane_own = 0xFFFFFFFFu;      // ... their smallest positions, pool and own text
         for (int j = 1; j <= a.K; ++j) {
-            // At most 256 survivors: each lane follows one, or up to four, to the end. Their next tokens are requested
-            // eight at a time (neighbours in memory), a vote is a ballot per distinct token, ended when no other token can
-            // win, and the filter is the winner's lane masks: no table, no LDS pass, one memory round trip for eight steps.
-            if (in_lds && m + mo <= 256u) {
+            // At most 256 survivors: each lane follows one, or up to four, to the end. Their next tokens are requested eight at
+            // a time (neighbours in memory; one at a time where four lanes' worth have four steps or fewer to go: a vote may
+            // end most of them), a vote is a ballot per distinct token, ended when no other token can win, and the filter
+            // is the winner's lane masks: no LDS pass, one memory round trip for eight steps. With one or two steps to go
+            // ballots pay off for fewer: 64 occurrences that all differ, 2048 lookups, K = 1 / 2: 12.7 / 12.8 us, by the
+            // vote table 9.5 / 10.4.
+            const int steps = a.K - j + 1;
+            if (in_lds && m + mo <= (steps > 1 ? 256u : 32u)) {
                 in_lanes = true;
-                if (m + mo <= 64u) len = follow_lanes<1, OWN>(a, cand, cand_end, m, own_cand, own, own_len, mo, j, chain, lane_min, lane_own);
-                else len = follow_lanes<4, OWN>(a, cand, cand_end, m, own_cand, own, own_len, mo, j, chain, lane_min, lane_own);
+                auto follow = [&](auto q, auto ahead) {
+                    len = follow_lanes<decltype(q)::value, decltype(ahead)::value, OWN>(a, cand, cand_end, m, own_cand, own, own_len, mo, j, chain, vote_tok, vote_cnt, lane_min, lane_own);
+                };
+                using std::integral_constant;
+                if (m + mo <= (steps > 2 ? 64u : 32u)) follow(integral_constant<int, 1>{}, integral_constant<int, 8>{});
+                else if (steps <= 4) follow(integral_constant<int, 4>{}, integral_constant<int, 1>{});
+                else follow(integral_constant<int, 4>{}, integral_constant<int, 8>{});
                 break;
             }
             int win_tok = -1, win_cnt = 0;

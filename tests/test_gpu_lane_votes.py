@@ -54,3 +54,54 @@ def test_trees_around_four_waves(count, K, vocab):
     toks, off, keys, _ = _pool(rng, count, vocab)
     compare_trees((toks, off, keys), [[1, 7], toks[:2].tolist(), [5]], [3, 3, 3], 1, 2, K)
     compare_trees((toks, off, keys), [[1, 7]], [3], 1, 2, K, min_tokens=min(K, 5))
+
+
+def _flat_pool(rng, count, agree, spread):
+    """`count` texts after the token 7 that agree for `agree` tokens, then fan out over about `spread` tokens, then agree again."""
+    trunk = rng.integers(8, 40, 12)
+    seqs = []
+    for i in range(count):
+        t = trunk.tolist()
+        t[agree] = 100 + int(rng.integers(0, spread)) if spread < count else 100 + i
+        seqs.append([7] + t[:12 - i % 3])
+    return np.concatenate(seqs).astype(np.int32), np.cumsum([0] + [len(s) for s in seqs]).astype(np.int64), np.full(count, 3, np.int64), trunk
+
+
+@pytest.mark.parametrize("count", [64, 65, 200, 256, 257])
+@pytest.mark.parametrize("agree,spread", [(0, 8), (0, 9), (0, 10), (0, 1000), (1, 60), (2, 1000), (7, 40), (8, 1000), (9, 9)])
+def test_votes_over_many_tokens(count, agree, spread):
+    """Votes that stay open after eight ballots, at the first step, inside, at the end and behind the tokens requested at a time."""
+    rng = np.random.default_rng(count * 10 + agree + spread)
+    toks, off, keys, trunk = _flat_pool(rng, count, agree, spread)
+    for K in (1, 2, 4, 5, 9, 11):
+        compare_pool(toks, off, keys, [3, 3], [[1, 7], [7, trunk[0]]], 1, 2, K)
+    own = [7] + trunk[:6].tolist() + [7] + trunk[:agree].tolist() + [101, 5, 7]
+    compare_own(toks, off, keys, [3, 3, 3], [own, own[8:], [7]], 1, 2, 10)
+
+
+def test_a_vote_over_many_tokens_takes_no_longer_in_the_lanes():
+    """256 occurrences with successors of their own (the lanes) against 257 (the vote table): ballots alone took three times as long."""
+    import time
+
+    import torch
+
+    import paper_2408_05676_amd as laser
+    took = []
+    for count in (256, 257):
+        toks, off, keys, _ = _flat_pool(np.random.default_rng(1), count, 0, 1000)
+        pool = laser.Pool(toks, off, keys, 2)
+        B, K = 2048, 2
+        i32 = dict(dtype=torch.int32, device="cuda")
+        args = (pool, torch.full((B,), 3, dtype=torch.int64, device="cuda"), torch.tensor([[1, 7]] * B, **i32), 1, 2, K, 1)
+        out = (torch.empty((B, K), **i32), torch.empty(B, **i32), torch.empty(B, **i32), torch.empty(B, dtype=torch.int64, device="cuda"))
+        best = 1e9
+        for _ in range(6):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            for _ in range(40):
+                laser.retrieve_drafts(*args, out=out)
+            torch.cuda.synchronize()
+            best = min(best, time.perf_counter() - t)
+        took.append(best)
+        pool.close()
+    assert took[0] <= 1.6 * took[1], took
