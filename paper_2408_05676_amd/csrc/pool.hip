@@ -28,7 +28,11 @@ namespace laser {
 // ------------------------------------------------------------------------------------ kernel
 constexpr int kCand = 512;         // occurrences a wave keeps in LDS (more: streamed from the index, re-checked against the chain)
 constexpr int kVote = 512;         // vote-table slots (power of two; wider votes are partitioned)
-constexpr int kGroups = 4;          // groups of 64 occurrences whose loads a vote has in flight together
+// Groups of 64 occurrences whose loads a vote over a streamed run has in flight together. A wave alone waits for memory: four.
+// Beyond 1024 contexts the waves of a compute unit cover each other's waits and four groups each outgrow its cache: one. A run
+// of 10000 occurrences, chains of 16, one group / four, us: 8 contexts 12075 / 9417, 1024 contexts 12278 / 10199, 2048
+// contexts 12590 / 19220.
+constexpr int kFourGroupsMax = 1024;
 constexpr int kEmptyTok = -1;
 constexpr int kOwnMax = LASER_MAX_OWN_TEXT;   // tokens of a sequence's own text (temporary branch) a lookup can take
 
@@ -60,7 +64,7 @@ struct RetrieveArgs {
 // 20.1 / 45.0. Occurrences that agree but for a tenth per step: ballots alone 10.1 / 11.1 / 20.0, now 12.5 / 9.6 / 20.3,
 // the table alone 12.0 / 29.4 / 75.2.
 template <int Q, int kAhead, bool OWN>
-__device__ inline int follow_lanes(const RetrieveArgs& a, const uint32_t* cand, const uint32_t* cand_end, uint32_t m, const uint32_t* own_cand,
+__device__ __forceinline__ int follow_lanes(const RetrieveArgs& a, const uint32_t* cand, const uint32_t* cand_end, uint32_t m, const uint32_t* own_cand,
                                    const int32_t* own, uint32_t own_len, uint32_t mo, int j0, int* chain, int* vote_tok, int* vote_cnt,
                                    uint32_t& lane_min, uint32_t& lane_own) {
     constexpr int kBallots = 8;
@@ -177,7 +181,7 @@ __device__ inline int follow_lanes(const RetrieveArgs& a, const uint32_t* cand, 
 // One wavefront (= one workgroup of 64 lanes) per context. OWN: with the temporary branch. Occurrences in the own
 // text are found by a scan of it (it is at most kOwnMax tokens and the wave has it in L2 anyway), always kept
 // in LDS (own_cand, position-ascending) and take part in every vote and filter next to the pool's.
-template <bool OWN>
+template <bool OWN, int kGroups>
 __global__ __launch_bounds__(64) void retrieve_kernel(RetrieveArgs a) {
     __shared__ uint32_t cand[kCand];
     // Beside each occurrence kept in LDS: the end of its sequence, and the successor token the current vote read for
@@ -292,8 +296,8 @@ __global__ __launch_bounds__(64) void retrieve_kernel(RetrieveArgs a) {
                     __syncthreads();
                     const uint32_t total_pool = in_lds ? m : count;
                     const uint32_t total = total_pool + mo;
-                    // Four groups of 64 voters at a time, every kind of load of all four before the first is used: a run that
-                    // is streamed from the index is a chain of round trips per group.
+                    // kGroups groups of 64 voters at a time, every kind of load of all of them before the first is used: a run
+                    // that is streamed from the index is a chain of round trips per group.
                     for (uint32_t i0 = 0; i0 < total; i0 += 64 * kGroups) {
                         uint32_t e[kGroups], end[kGroups];
                         int tok[kGroups];
@@ -1056,8 +1060,9 @@ static int retrieve_impl(const laser_pool* pool, const int64_t* keys, const int3
     RetrieveArgs a{p->P, p->seq_end, p->sa, p->table, p->cap_mask, keys, ctx_tail,
                    B, n_min, n_max, K, min_tokens < 1 ? 1 : min_tokens, drafts, draft_len, match_n, pool_index,
                    own, own_len, own_cap};
-    if (own) hipLaunchKernelGGL(retrieve_kernel<true>, dim3(B), dim3(64), 0, (hipStream_t)stream, a);
-    else hipLaunchKernelGGL(retrieve_kernel<false>, dim3(B), dim3(64), 0, (hipStream_t)stream, a);
+    const bool four = B <= kFourGroupsMax;
+    const auto kernel = own ? (four ? retrieve_kernel<true, 4> : retrieve_kernel<true, 1>) : (four ? retrieve_kernel<false, 4> : retrieve_kernel<false, 1>);
+    hipLaunchKernelGGL(kernel, dim3(B), dim3(64), 0, (hipStream_t)stream, a);
     LASER_HIP_CHECK(hipGetLastError());
     return LASER_OK;
 }

@@ -105,3 +105,59 @@ def test_a_vote_over_many_tokens_takes_no_longer_in_the_lanes():
         took.append(best)
         pool.close()
     assert took[0] <= 1.6 * took[1], took
+
+
+def test_long_runs_of_more_than_1024_contexts():
+    """Beyond 1024 contexts a streamed run is voted on in groups of 64: the same results as for few contexts, chains and own text."""
+    import torch
+
+    import paper_2408_05676_amd as laser
+    rng = np.random.default_rng(4)
+    count, K = 700, 12
+    toks, off, keys, trunk = _pool(rng, count, 3)
+    pool = laser.Pool(toks, off, keys, 2)
+    tails = np.array([[1, 7], [7, trunk[0]], [1, 5], [7, int(toks[1])]], np.int32)
+    own = np.full((4, 64), 7, np.int32)
+    own[:, 1::2] = rng.integers(8, 12, (4, 32))
+    got = []
+    for reps in (1, 257):                                       # 4 and 1028 contexts
+        dev = lambda a: torch.tensor(np.tile(a, (reps,) + (1,) * (a.ndim - 1)), device="cuda")
+        qk, tail = dev(np.full(4, 3, np.int64)), dev(tails)
+        got.append([[t.cpu().numpy() for t in laser.retrieve_drafts(pool, qk, tail, 1, 2, K, 1)],
+                    [t.cpu().numpy() for t in laser.retrieve_drafts_temp(pool, qk, tail, dev(own), dev(np.full(4, 64, np.int32)), 1, 2, K, 1)]])
+    for few, many in zip(*got):
+        for x, y in zip(few, many):
+            assert (np.tile(x, (257,) + (1,) * (x.ndim - 1)) == y).all()
+    compare_pool(toks, off, keys, [3] * 4, tails.tolist(), 1, 2, K)
+    pool.close()
+
+
+def test_many_contexts_over_a_long_run_take_no_longer_together():
+    """2048 contexts over a run of 10000 occurrences against twice 1024: four groups in flight took 1.9 times as long, one takes as long."""
+    import time
+
+    import torch
+
+    import paper_2408_05676_amd as laser
+    rng = np.random.default_rng(0)
+    trunk, count, K = rng.integers(8, 30000, 40), 10000, 16
+    text = np.tile(np.concatenate([[7], trunk]), (count, 1))
+    hit = rng.random(text.shape) < 0.1
+    hit[:, 0] = False
+    text[hit] = rng.integers(8, 30000, int(hit.sum()))
+    pool = laser.Pool(text.reshape(-1).astype(np.int32), np.arange(count + 1, dtype=np.int64) * 41, np.zeros(count, np.int64), 2)
+    took = []
+    for B in (1024, 2048):
+        i32 = dict(dtype=torch.int32, device="cuda")
+        qk, tail = torch.zeros(B, dtype=torch.int64, device="cuda"), torch.tensor([[1, 7]] * B, **i32)
+        out = (torch.empty((B, K), **i32), torch.empty(B, **i32), torch.empty(B, **i32), torch.empty(B, dtype=torch.int64, device="cuda"))
+        best = 1e9
+        for _ in range(5):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            laser.retrieve_drafts(pool, qk, tail, 1, 2, K, 1, out=out)
+            torch.cuda.synchronize()
+            best = min(best, time.perf_counter() - t)
+        took.append(best)
+    pool.close()
+    assert took[1] <= 1.5 * took[0], took
