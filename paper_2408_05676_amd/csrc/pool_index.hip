@@ -263,9 +263,26 @@ __global__ __launch_bounds__(256) void run_insert_kernel(IndexArgs a, const uint
     }
 }
 
-struct Buffers {                     // what the build allocates; freed on every way out unless handed over
-    void* p[5] = {};
-    ~Buffers() { for (void* q : p) if (q) (void)hipFree(q); }
+// What the build allocates; freed on every way out unless handed over. The working arrays are the stream's (hipFree waits for
+// all streams of the device: a build beside other work would end when that work does). Given back, they leave the device's
+// memory pool at once: by itself it keeps them until a later wait.
+struct Buffers {
+    hipStream_t stream;
+    void* work = nullptr;
+    void* p[4] = {};
+    ~Buffers() {
+        if (work) {
+            int dev = 0;
+            hipMemPool_t pool;
+            uint64_t keep = 0;
+            (void)hipFreeAsync(work, stream);
+            (void)hipStreamSynchronize(stream);
+            if (hipGetDevice(&dev) == hipSuccess && hipDeviceGetMemPool(&pool, dev) == hipSuccess &&
+                hipMemPoolGetAttribute(pool, hipMemPoolAttrReleaseThreshold, &keep) == hipSuccess)
+                (void)hipMemPoolTrimTo(pool, keep);
+        }
+        for (void* q : p) if (q) (void)hipFree(q);
+    }
 };
 
 }  // namespace
@@ -291,17 +308,17 @@ int build_index_device(const int32_t* tokens, const PoolLayout& lay, int n_max, 
     std::memcpy(pack.data(), lay.dst_off.data(), (n_seq + 1) * 4);
     std::memcpy(pack.data() + n_seq + 1, lay.src_off.data(), n_seq * 4);
     std::memcpy(pack.data() + 2 * n_seq + 1, lay.sub.data(), n_seq * 4);
-    Buffers buf;                     // P, seq_end, sa, table, working arrays
-    auto take = [&](int i, size_t n) {
-        const hipError_t e = hipMalloc(&buf.p[i], n);
+    Buffers buf{stream};             // P, seq_end, sa, table; working arrays
+    auto judge = [&](hipError_t e) {
         if (e == hipErrorOutOfMemory) { *no_memory = true; (void)hipGetLastError(); }
         return e;
     };
+    auto take = [&](int i, size_t n) { return judge(hipMalloc(&buf.p[i], n)); };
     LASER_HIP_CHECK(take(0, n_tok * 4));
     LASER_HIP_CHECK(take(1, n_tok * 4));
     LASER_HIP_CHECK(take(2, n_sa * 4));
-    LASER_HIP_CHECK(take(4, bytes));
-    char* const ws = (char*)buf.p[4];
+    LASER_HIP_CHECK(judge(hipMallocAsync(&buf.work, bytes, stream)));
+    char* const ws = (char*)buf.work;
     a.P = (int32_t*)buf.p[0];
     a.seq_end = (uint32_t*)buf.p[1];
     a.src = (const int32_t*)(ws + o_src);

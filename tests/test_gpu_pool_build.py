@@ -101,3 +101,27 @@ def test_refusals_stay():
         laser.Pool(toks, off, np.zeros(2, np.int64), 3)
     with pytest.raises(laser.LaserError, match="not ascending"):
         laser.Pool(np.ones(40000, np.int32), np.array([0, 41000, 40000], np.int64), np.zeros(2, np.int64), 3)
+
+
+def test_a_build_does_not_wait_for_other_streams_and_keeps_no_working_memory():
+    """The working arrays (20 MiB here) are allocated and given back in the order of the caller's stream: the build ends while another
+    stream is still at work, and only the pool's own memory stays taken."""
+    import paper_2408_05676_amd as laser
+    rng = np.random.default_rng(2)
+    lens = np.full(10000, 120)
+    toks, off = _texts(rng, lens, 32000)
+    keys = rng.integers(0, 50, 10000).astype(np.int64)
+    laser.Pool(toks, off, keys, 2).close()                      # first use of the kernels
+    other = torch.cuda.Stream()
+    with torch.cuda.stream(other):
+        torch.cuda._sleep(1)
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    with torch.cuda.stream(other):
+        torch.cuda._sleep(1_000_000_000)                        # some hundred ms on one compute unit
+    pool = laser.Pool(toks, off, keys, 2)
+    assert not other.query(), "the build waited for the other stream"
+    taken = free - torch.cuda.mem_get_info()[0]
+    assert taken <= pool.info()["device_bytes"] + (12 << 20), taken    # (allocations are rounded up to 2 MiB)
+    torch.cuda.synchronize()
+    pool.close()
