@@ -818,7 +818,11 @@ namespace {
 
 struct SubPool { int64_t key; uint32_t begin, end; };
 
-constexpr int64_t kDeviceBuildMin = 4096;   // at 5000 tokens 190 .. 420 us against the host's 300 .. 570, at 2500 180 .. 360 against 120 .. 450, at 20000 210 .. 530 against 600 .. 2700
+// Occurrences from which the device builds. It takes three launches per byte of a token and n, whatever the size, the host
+// a comparison sort. us, device / host, for n_max 1 / 4 / 8: two bytes, 4096 occurrences 250 / 467 / 750 against 359 / 496
+// / 792; three bytes, 4096: 272 / 562 / 937 against 325 / 480 / 846, 8192: 274 / 600 / 1068 against 322 / 763 / 1680;
+// four bytes, 4096: 299 / 652 / 1083 against 243 / 416 / 817, 8192: 311 / 709 / 1248 against 385 / 778 / 1614.
+constexpr int64_t kDeviceBuildMin = 4096, kDeviceBuildMinWide = 8192;
 
 }  // namespace
 
@@ -836,10 +840,12 @@ static int build_pool(const int32_t* tokens, const int64_t* seq_off, const int64
 
     // Many occurrences: the rest happens on the device, unless it cannot hold the working arrays (17 bytes per token
     // besides the pool itself). Few: the host is done before the device's ~40 dependent launches are.
-    if (n_tok - n_seq >= kDeviceBuildMin) {
-        PoolLayout lay;
-        uint32_t bits = 0, pos = 0;
+    uint32_t bits = 0;                                // all tokens or-ed together
+    if (n_tok - n_seq >= kDeviceBuildMin)
         for (int64_t i = 0; i < n_tok; ++i) bits |= (uint32_t)tokens[i];
+    if (n_tok - n_seq >= (bits + 1u < 1u << 16 ? kDeviceBuildMin : kDeviceBuildMinWide)) {
+        PoolLayout lay;
+        uint32_t pos = 0;
         for (int64_t i = 0; i < n_seq; ++i) {
             const int64_t s = order[i];
             const uint32_t len = (uint32_t)(seq_off[s + 1] - seq_off[s]);

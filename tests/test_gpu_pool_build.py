@@ -83,6 +83,19 @@ def test_token_widths_and_ngrams(vocab, n_max):
     _check(toks, off, rng.integers(0, 5, 500).astype(np.int64), n_max, vocab % 1000, K=3)
 
 
+@pytest.mark.parametrize("vocab", [65535, 65536, 2**31 - 1])
+@pytest.mark.parametrize("n_sa", [4095, 4096, 8191, 8192])
+def test_sizes_around_the_rule_by_token_width(n_sa, vocab):
+    """Tokens of more than two bytes go to the device from twice the size on."""
+    rng = np.random.default_rng(n_sa + vocab % 1000)
+    lens = np.full(100, 1)
+    lens += rng.multinomial(n_sa, np.ones(100) / 100)
+    toks, off = _texts(rng, lens, vocab)
+    toks[rng.random(toks.size) < 0.4] = vocab - 1
+    toks[0] = vocab - 1
+    _check(toks, off, rng.integers(0, 3, 100).astype(np.int64), 3, n_sa)
+
+
 @pytest.mark.parametrize("n_keys", [1, 255, 257, 9000])
 def test_sub_pools(n_keys):
     rng = np.random.default_rng(n_keys)
