@@ -68,12 +68,23 @@ const char* laser_version(void);
  *   seq_off [host] int64[n_seq+1]          start of each sequence, ascending, seq_off[0] = 0
  *   seq_key [host] int64[n_seq]            opaque key (user / item / group id) of each sequence
  *   n_max   1..LASER_MAX_NGRAM
- * Host work (sorting, hashing) runs inside the call; device copies are enqueued on `stream` and the
- * call synchronises that stream before returning. Total tokens must stay below 2^32 - 1.
+ * Small pools (fewer than 4096 occurrences, i.e. tokens minus sequences, or 8192 where a token id needs more than two
+ * bytes) are sorted and hashed by the host inside the call. Larger ones are indexed by kernels on `stream`, which take
+ * about 17 bytes of device memory per token beside the pool itself until the call returns; if the device does not have
+ * that memory, the host builds after all (about 40 times slower at a million tokens). The call synchronises `stream`,
+ * with device builds also in between, and waits for no other stream; beside work that fills every compute unit a device
+ * build takes its turns (13 to 18 ms measured). Total tokens must stay below 2^32 - 1.
  * The pool is immutable afterwards. *out is written only on success.
  */
 int laser_pool_build(const int32_t* tokens, const int64_t* seq_off, const int64_t* seq_key,
                      int64_t n_seq, int n_max, void* stream, laser_pool** out);
+/* The same by a builder of the caller's choice, for tests and comparisons; all give the same pool. mem_limit: device bytes
+ * a device build may hold (< 0: what there is); beyond it the call goes on as if the device had no more. */
+#define LASER_BUILDER_AUTO   0
+#define LASER_BUILDER_HOST   1
+#define LASER_BUILDER_DEVICE 2 /* the host where no token has a successor */
+int laser_pool_build_with(const int32_t* tokens, const int64_t* seq_off, const int64_t* seq_key,
+                          int64_t n_seq, int n_max, int builder, int64_t mem_limit, void* stream, laser_pool** out);
 int laser_pool_destroy(laser_pool* pool);
 
 /* Sizes of a built pool; any out pointer may be NULL. */

@@ -53,6 +53,7 @@ def lib():
     L.laser_version.restype = C.c_char_p
     protos = {
         "laser_pool_build": [vp, vp, vp, i64, i32, vp, C.POINTER(vp)],
+        "laser_pool_build_with": [vp, vp, vp, i64, i32, i32, i64, vp, C.POINTER(vp)],
         "laser_pool_destroy": [vp],
         "laser_pool_info": [vp, C.POINTER(i64), C.POINTER(i64), C.POINTER(i64), C.POINTER(i64)],
         "laser_pool_read_tokens": [vp, i64, i64, vp],
@@ -120,9 +121,9 @@ def _host_i32(a, name: str) -> np.ndarray:
 
 
 class Pool:
-    """laser_pool_build / laser_pool_destroy."""
+    """laser_pool_build / laser_pool_destroy. builder ("auto", "host" or "device") and mem_limit are laser_pool_build_with's."""
 
-    def __init__(self, tokens, seq_off, seq_key, n_max: int, stream=None):
+    def __init__(self, tokens, seq_off, seq_key, n_max: int, stream=None, builder: str = "auto", mem_limit: int = -1):
         tokens = np.ascontiguousarray(tokens, dtype=np.int32)
         seq_off = np.ascontiguousarray(seq_off, dtype=np.int64)
         seq_key = np.ascontiguousarray(seq_key, dtype=np.int64)
@@ -132,8 +133,8 @@ class Pool:
             raise LaserError("seq_off[-1] must equal the number of tokens")
         self._h = C.c_void_p()
         self.n_max = n_max
-        _check(lib().laser_pool_build(tokens.ctypes.data, seq_off.ctypes.data, seq_key.ctypes.data,
-                                      seq_key.size, n_max, _stream(stream), C.byref(self._h)),
+        _check(lib().laser_pool_build_with(tokens.ctypes.data, seq_off.ctypes.data, seq_key.ctypes.data, seq_key.size, n_max,
+                                           ("auto", "host", "device").index(builder), mem_limit, _stream(stream), C.byref(self._h)),
                "laser_pool_build")
 
     def info(self) -> dict:

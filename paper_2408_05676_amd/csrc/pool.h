@@ -26,7 +26,8 @@ struct PoolLayout {
     uint32_t token_bits = 0;            // all tokens or-ed together
 };
 
-// Fills p (arrays and counts; nothing is kept on failure). *no_memory: the device could not hold the working arrays.
-int build_index_device(const int32_t* tokens, const PoolLayout& lay, int n_max, hipStream_t stream, Pool* p, bool* no_memory);
+// Fills p (arrays and counts; nothing is kept on failure). *no_memory: the device could not hold the pool and the working
+// arrays, or they exceed mem_limit bytes (< 0: no limit).
+int build_index_device(const int32_t* tokens, const PoolLayout& lay, int n_max, int64_t mem_limit, hipStream_t stream, Pool* p, bool* no_memory);
 
 }  // namespace laser

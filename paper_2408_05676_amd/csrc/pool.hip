@@ -1,5 +1,6 @@
-// Retrieval pool: host-side construction of the regrouped pool and its suffix index, and the
-// per-context lookup + frequency-greedy chain kernel (Sec. 3.2 pool construction, Sec. 3.3 Eq. 5).
+// Retrieval pool: construction of the regrouped pool and its suffix index on the host (few occurrences, or no memory on the
+// device; pool_index.hip builds the others), and the per-context lookup + frequency-greedy chain kernel (Sec. 3.2 pool
+// construction, Sec. 3.3 Eq. 5).
 //
 // Index layout (all device resident, immutable after the build):
 //   P[N]        int32   tokens, sub-pools laid out by ascending key
@@ -827,7 +828,7 @@ constexpr int64_t kDeviceBuildMin = 4096, kDeviceBuildMinWide = 8192;
 }  // namespace
 
 static int build_pool(const int32_t* tokens, const int64_t* seq_off, const int64_t* seq_key,
-                      int64_t n_seq, int n_max, hipStream_t stream, Pool** out) {
+                      int64_t n_seq, int n_max, int builder, int64_t mem_limit, hipStream_t stream, Pool** out) {
     const int64_t n_tok = n_seq > 0 ? seq_off[n_seq] : 0;
     LASER_REQUIRE(n_tok < 0xFFFFFFFFll, LASER_E_LIMIT, "pool of %lld tokens exceeds 2^32-2", (long long)n_tok);
     for (int64_t s = 0; s < n_seq; ++s)
@@ -841,9 +842,11 @@ static int build_pool(const int32_t* tokens, const int64_t* seq_off, const int64
     // Many occurrences: the rest happens on the device, unless it cannot hold the working arrays (17 bytes per token
     // besides the pool itself). Few: the host is done before the device's ~40 dependent launches are.
     uint32_t bits = 0;                                // all tokens or-ed together
-    if (n_tok - n_seq >= kDeviceBuildMin)
+    const int64_t least = builder == LASER_BUILDER_DEVICE ? 1 : kDeviceBuildMin;
+    if (builder != LASER_BUILDER_HOST && n_tok - n_seq >= least)
         for (int64_t i = 0; i < n_tok; ++i) bits |= (uint32_t)tokens[i];
-    if (n_tok - n_seq >= (bits + 1u < 1u << 16 ? kDeviceBuildMin : kDeviceBuildMinWide)) {
+    const bool wide = builder == LASER_BUILDER_AUTO && bits + 1u >= 1u << 16;
+    if (builder != LASER_BUILDER_HOST && n_tok - n_seq >= (wide ? kDeviceBuildMinWide : least)) {
         PoolLayout lay;
         uint32_t pos = 0;
         for (int64_t i = 0; i < n_seq; ++i) {
@@ -863,7 +866,7 @@ static int build_pool(const int32_t* tokens, const int64_t* seq_off, const int64
         lay.token_bits = bits;
         Pool* p = new Pool();
         bool no_memory = false;
-        const int rc = build_index_device(tokens, lay, n_max, stream, p, &no_memory);
+        const int rc = build_index_device(tokens, lay, n_max, mem_limit, stream, p, &no_memory);
         if (rc == LASER_OK) { *out = p; return rc; }
         delete p;
         if (!no_memory) return rc;
@@ -1012,13 +1015,19 @@ using namespace laser;
 
 extern "C" int laser_pool_build(const int32_t* tokens, const int64_t* seq_off, const int64_t* seq_key,
                                 int64_t n_seq, int n_max, void* stream, laser_pool** out) {
+    return laser_pool_build_with(tokens, seq_off, seq_key, n_seq, n_max, LASER_BUILDER_AUTO, -1, stream, out);
+}
+
+extern "C" int laser_pool_build_with(const int32_t* tokens, const int64_t* seq_off, const int64_t* seq_key, int64_t n_seq,
+                                     int n_max, int builder, int64_t mem_limit, void* stream, laser_pool** out) {
     LASER_REQUIRE(out != nullptr, LASER_E_INVALID_ARG, "out is NULL");
     LASER_REQUIRE(n_seq >= 0, LASER_E_INVALID_ARG, "n_seq < 0");
     LASER_REQUIRE(n_seq == 0 || (tokens && seq_off && seq_key), LASER_E_INVALID_ARG, "NULL input array");
     LASER_REQUIRE(n_max >= 1 && n_max <= LASER_MAX_NGRAM, LASER_E_INVALID_ARG, "n_max %d outside 1..%d", n_max, LASER_MAX_NGRAM);
     LASER_REQUIRE(n_seq == 0 || seq_off[0] == 0, LASER_E_INVALID_ARG, "seq_off[0] != 0");
+    LASER_REQUIRE(builder >= LASER_BUILDER_AUTO && builder <= LASER_BUILDER_DEVICE, LASER_E_INVALID_ARG, "unknown builder %d", builder);
     Pool* p = nullptr;
-    int rc = build_pool(tokens, seq_off, seq_key, n_seq, n_max, (hipStream_t)stream, &p);
+    int rc = build_pool(tokens, seq_off, seq_key, n_seq, n_max, builder, mem_limit, (hipStream_t)stream, &p);
     if (rc == LASER_OK) *out = reinterpret_cast<laser_pool*>(p);
     return rc;
 }

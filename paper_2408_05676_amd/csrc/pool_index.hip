@@ -287,7 +287,7 @@ struct Buffers {
 
 }  // namespace
 
-int build_index_device(const int32_t* tokens, const PoolLayout& lay, int n_max, hipStream_t stream, Pool* p, bool* no_memory) {
+int build_index_device(const int32_t* tokens, const PoolLayout& lay, int n_max, int64_t mem_limit, hipStream_t stream, Pool* p, bool* no_memory) {
     *no_memory = false;
     IndexArgs a{};
     a.n_seq = (uint32_t)lay.sub.size();
@@ -309,15 +309,18 @@ int build_index_device(const int32_t* tokens, const PoolLayout& lay, int n_max, 
     std::memcpy(pack.data() + n_seq + 1, lay.src_off.data(), n_seq * 4);
     std::memcpy(pack.data() + 2 * n_seq + 1, lay.sub.data(), n_seq * 4);
     Buffers buf{stream};             // P, seq_end, sa, table; working arrays
-    auto judge = [&](hipError_t e) {
+    size_t taken = 0;
+    auto take = [&](void** at, size_t n, bool work) {
+        taken += n;
+        hipError_t e = hipErrorOutOfMemory;
+        if (mem_limit < 0 || taken <= (uint64_t)mem_limit) e = work ? hipMallocAsync(at, n, stream) : hipMalloc(at, n);
         if (e == hipErrorOutOfMemory) { *no_memory = true; (void)hipGetLastError(); }
         return e;
     };
-    auto take = [&](int i, size_t n) { return judge(hipMalloc(&buf.p[i], n)); };
-    LASER_HIP_CHECK(take(0, n_tok * 4));
-    LASER_HIP_CHECK(take(1, n_tok * 4));
-    LASER_HIP_CHECK(take(2, n_sa * 4));
-    LASER_HIP_CHECK(judge(hipMallocAsync(&buf.work, bytes, stream)));
+    LASER_HIP_CHECK(take(&buf.p[0], n_tok * 4, false));
+    LASER_HIP_CHECK(take(&buf.p[1], n_tok * 4, false));
+    LASER_HIP_CHECK(take(&buf.p[2], n_sa * 4, false));
+    LASER_HIP_CHECK(take(&buf.work, bytes, true));
     char* const ws = (char*)buf.work;
     a.P = (int32_t*)buf.p[0];
     a.seq_end = (uint32_t*)buf.p[1];
@@ -369,7 +372,7 @@ int build_index_device(const int32_t* tokens, const PoolLayout& lay, int n_max, 
     uint64_t cap = 16;
     while (cap < 2 * n_runs) cap <<= 1;
     a.cap_mask = cap - 1;
-    LASER_HIP_CHECK(take(3, cap * sizeof(IndexEntry)));
+    LASER_HIP_CHECK(take(&buf.p[3], cap * sizeof(IndexEntry), false));
     a.table = (IndexEntry*)buf.p[3];
     LASER_HIP_CHECK(hipMemsetAsync(a.table, 0, cap * sizeof(IndexEntry), stream));
     hipLaunchKernelGGL(run_insert_kernel, dim3(a.n_chunks), dim3(256), 0, stream, a, sa);

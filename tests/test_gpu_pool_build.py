@@ -138,3 +138,55 @@ def test_a_build_does_not_wait_for_other_streams_and_keeps_no_working_memory():
     assert taken <= pool.info()["device_bytes"] + (12 << 20), taken    # (allocations are rounded up to 2 MiB)
     torch.cuda.synchronize()
     pool.close()
+
+
+def _everything(pool, toks, keys, n_max):
+    """Counts, tokens, and lookups of all kinds of contexts in a pool."""
+    import paper_2408_05676_amd as laser
+    rng = np.random.default_rng(1)
+    at = rng.integers(0, toks.size - n_max, 300)
+    tails = np.stack([toks[a:a + n_max] for a in at]).astype(np.int32)
+    tails[::5] = rng.integers(0, int(toks.max()) + 1, tails[::5].shape)
+    qk = keys[rng.integers(0, keys.size, 300)]
+    dev = [torch.tensor(x, device="cuda") for x in (qk, tails)]
+    found = [t.cpu().numpy() for t in laser.retrieve_drafts(pool, *dev, 1, n_max, 9, 1)]
+    return [np.array(sorted(pool.info().items())), pool.read_tokens(0, toks.size)] + found
+
+
+# The pool and the working arrays in the order in which they are allocated: the tokens, their ends, the occurrences, the
+# working arrays, and after the kernels the table.
+@pytest.mark.parametrize("share", [0.0, 0.3, 0.5, 0.9, 0.999])
+def test_a_build_that_finds_no_memory_goes_on_on_the_host(share):
+    import paper_2408_05676_amd as laser
+    rng = np.random.default_rng(7)
+    lens = rng.integers(0, 90, 700)
+    toks, off = _texts(rng, lens, 40)
+    keys = rng.integers(0, 9, 700).astype(np.int64)
+    host = laser.Pool(toks, off, keys, 3, builder="host")
+    want = _everything(host, toks, keys, 3)
+    whole = laser.Pool(toks, off, keys, 3, builder="device")
+    n_blk = -(-toks.size // 4096)
+    work = 17 * toks.size + 1024 * n_blk                        # at least; the pool's own arrays come on top
+    limit = int(share * (whole.info()["device_bytes"] + work))
+    short = laser.Pool(toks, off, keys, 3, mem_limit=limit)
+    for pool in (whole, short):
+        for x, y in zip(_everything(pool, toks, keys, 3), want):
+            assert (x == y).all()
+    for pool in (host, whole, short):
+        pool.close()
+
+
+@pytest.mark.parametrize("builder", ["host", "device"])
+@pytest.mark.parametrize("lens", [[2], [0, 3, 1, 0], [1, 1], [5000], [70] * 100])
+def test_either_builder_takes_any_size(builder, lens):
+    import paper_2408_05676_amd as laser
+    rng = np.random.default_rng(len(lens))
+    toks, off = _texts(rng, lens, 6)
+    keys = rng.integers(0, 2, len(lens)).astype(np.int64)
+    pool, ora = laser.Pool(toks, off, keys, 2, builder=builder), RegroupedPool(toks, off, keys)
+    assert pool.info()["n_index_entries"] == _entries((toks, off, keys), 2)
+    qk, tails = np.repeat(keys[:1], 36), np.array([[a, b] for a in range(6) for b in range(6)], np.int32)
+    got = laser.retrieve_drafts(pool, torch.tensor(qk, device="cuda"), torch.tensor(tails, device="cuda"), 1, 2, 4, 1)
+    for x, y in zip(got, retrieve(ora, qk, tails, 1, 2, 4, 1)):
+        assert (x.cpu().numpy() == y).all()
+    pool.close()
