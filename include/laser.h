@@ -355,6 +355,8 @@ int laser_generate(laser_model* model, laser_kv* kv, const laser_pool* pool, con
  * "f16_copies" = 1 (default) or 0: see laser_model_create.
  * "mid_waves" = 0 (default): 17..80 rows take the tiled GEMM; 4 or 8: the one that stages rows through
  * registers, with that many waves per workgroup.
+ * "tile" = 0 (default: chosen from the launch shape) or i: with more than 16 rows every tiled product takes the i-th entry
+ * of its own table of tiles (a number beyond a table's end: chosen).
  * "attn_whole_min" = 0 (default: half the number of compute units) or a count: from this many (sequence, head,
  * 16-row query tile) triples on, the general path's attention walks a context in one workgroup instead of
  * splitting it into 256-token parts that a second kernel merges.

@@ -22,6 +22,7 @@ struct GemmTileArgs {
     float* outf;            // GEPI_F32: [ksplit][M][N]
     uint16_t* outh;         // GEPI_SWIGLU: [M][N] fp16
     HeadPart hp{};          // GEPI_HEAD*: where the per-(row, chunk) statistics go (chunk = the WN * 16 columns of a wave)
+    int want_tile = 0;      // for the host: 1 + the entry of the tile table to take, 0: chosen by the rule
 };
 
 // GEPI_HEAD: the output head. Logits are not stored: each row's columns of a wave are reduced to one record of partial

@@ -36,6 +36,7 @@ GemmTilePlan few_plan(const FewShape (&shapes)[N], const GemmTileArgs& t, bool s
     const int nk = t.Kd / GT_BK, bm = (t.M + 15) / 16 * 16;
     if (want_split > 0 && (nk % want_split || want_split > max_split)) want_split = 1;
     for (int v = 0; v < N; ++v) {
+        if (t.want_tile > 0 && t.want_tile <= N && v != t.want_tile - 1) continue;
         const int bn = shapes[v].wn * 16 * shapes[v].nwn, bf = swiglu ? bn / 2 : bn;
         const long tiles = (t.N + bf - 1) / bf;
         const double stage = 0.02 * (gemm_tile_lds(bm, bn, 1, t.Xlo != nullptr) / 1024);

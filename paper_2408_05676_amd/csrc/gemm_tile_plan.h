@@ -37,6 +37,7 @@ inline GemmTilePlan gemm_tile_plan(const GemmTileShape (&shapes)[NV], int nv, co
     const int nk = t.Kd / GT_BK;
     if (want_split > 0 && (nk % want_split || want_split > max_split)) want_split = 1;
     for (int v = 0; v < nv; ++v) {
+        if (t.want_tile > 0 && t.want_tile <= nv && v != t.want_tile - 1) continue;
         const int bm = shapes[v].wm * 32, bn = shapes[v].wn * 32, bf = swiglu ? bn / 2 : bn;
         const long tiles = (long)((t.M + bm - 1) / bm) * ((t.N + bf - 1) / bf);
         const double step = 2.0 * shapes[v].wm * shapes[v].wn * 16 * (split ? 2 : 1) + 17.0 * (gemm_tile_lds(bm, bn, 1, split) / 1024);

@@ -303,6 +303,7 @@ static int run_head_bufs(Model* m, const uint16_t* h, const int32_t* tokens, con
         int ncu = 0;
         LASER_HIP_CHECK(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, 0));
         GemmTileArgs t{m->wlm16 ? m->wlm16 : m->d.wlm, h, nullptr, M, V, dm, 0, 0, 1, nullptr, nullptr, hp};
+        t.want_tile = m->tile;
         launch_tile_head(t, m->wlm16 != nullptr, ncu, stream);
     }
     AcceptArgs aa{hb.hp_max, hb.hp_sum, hb.hp_arg, hb.hp_topv, hb.hp_topi, hb.cand_beg, hb.cand_cnt, hb.cand_x, hb.cand_lx, hb.node_cand,

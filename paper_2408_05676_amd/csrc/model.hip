@@ -167,6 +167,7 @@ struct GemmArgs {
     size_t part_floats = 0;
     int want_split = 0;     // 0: choose; 1, 2, 4: force this many reduction parts
     int n_part = 0;         // out: parts left in `part` for the consumer to add up (0: the result is complete)
+    int want_tile = 0;      // tiled kernels: see GemmTileArgs
     int mid_waves = 0;      // 17..80 rows: 4 or 8 = the register-staged kernel with that many waves per workgroup
 };
 
@@ -298,6 +299,7 @@ static int launch_gemm(GemmArgs& a_in, hipStream_t stream) {
         int ncu = 0;
         LASER_HIP_CHECK(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, 0));
         GemmTileArgs t{!few && a.W16 ? a.W16 : a.W, a.X, a.Xlo, a.M, a.N, a.Kd, 0, 0, 1, nullptr, a.outh};
+        t.want_tile = a.want_tile;
         if constexpr (EPI == EPI_SWIGLU) {
             if (few) launch_few_swiglu(t, ncu, stream);
             else launch_tile_swiglu(t, a.W16 != nullptr, ncu, stream);
@@ -749,7 +751,7 @@ static int forward(Model* m, KV* kv, const int32_t* ids_dev, const int32_t* pend
         pend = 0;
         const bool many = M > kSkinnyMaxRows && m->w16[0];      // tiled path: weights from the fp16 copy (if kept)
         GemmArgs g{d.wqkv + (size_t)l * 3 * dm * dm, many ? m->w16[0] + (size_t)l * 3 * dm * dm : nullptr, m->xn, m->xn_lo, M, 3 * dm, dm, 1, m->qkv, nullptr};
-        g.part = m->kpart; g.part_floats = m->kpart_floats; g.want_split = m->ksplit_opt[0]; g.mid_waves = m->mid_waves;
+        g.part = m->kpart; g.part_floats = m->kpart_floats; g.want_split = m->ksplit_opt[0]; g.mid_waves = m->mid_waves; g.want_tile = m->tile;
         if ((rc = launch_gemm<EPI_F32>(g, stream))) return rc;
         RopeArgs ra{g.n_part ? m->kpart : m->qkv, m->row_pos, m->row_slot, ids_dev, kv->block_table, m->rope, m->q, m->q_lo, kv->kpages, kv->klpages, kv->vpages,
                     R, dm, d.n_heads, m->dh, kv->d.max_pages_per_seq, l, kv->d.n_pages,
@@ -782,20 +784,20 @@ static int forward(Model* m, KV* kv, const int32_t* ids_dev, const int32_t* pend
             else hipLaunchKernelGGL(attn_combine_kernel<64>, cg, dim3(256), 0, stream, aa);
         }
         GemmArgs go{d.wo + (size_t)l * dm * dm, many ? m->w16[1] + (size_t)l * dm * dm : nullptr, m->attn, m->attn_lo, M, dm, dm, 1, m->x, nullptr};
-        go.part = m->kpart; go.part_floats = m->kpart_floats; go.want_split = m->ksplit_opt[1]; go.mid_waves = m->mid_waves;
+        go.part = m->kpart; go.part_floats = m->kpart_floats; go.want_split = m->ksplit_opt[1]; go.mid_waves = m->mid_waves; go.want_tile = m->tile;
         if ((rc = launch_gemm<EPI_RESID>(go, stream))) return rc;
         launch_rmsnorm(M, stream, m->x, d.g2 + (size_t)l * dm, dm, d.eps, m->xn, m->xn_lo, (const float*)m->kpart, go.n_part, (size_t)M * dm);
         // On the tiled many-row path a split operand doubles the matrix work; gate/up (45 % of the layer's
         // flops) takes the single fp16 rows there unless option "split_ffn" asks for the split (see set_option).
         const bool split_gu = M <= kSkinnyMaxRows || m->split_ffn;
         GemmArgs gg{d.wgu + (size_t)l * 2 * F * dm, many ? m->w16[2] + (size_t)l * 2 * F * dm : nullptr, m->xn, split_gu ? m->xn_lo : nullptr, M, F, dm, 1, nullptr, m->act};
-        gg.mid_waves = m->mid_waves;
+        gg.mid_waves = m->mid_waves; gg.want_tile = m->tile;
         const bool prof = m->prof_on && m->prof_n < m->prof_cap;
         if (prof) LASER_HIP_CHECK(hipEventRecord(m->prof_ev[2 * m->prof_n], stream));
         if ((rc = launch_gemm<EPI_SWIGLU>(gg, stream))) return rc;
         if (prof) { LASER_HIP_CHECK(hipEventRecord(m->prof_ev[2 * m->prof_n + 1], stream)); ++m->prof_n; }
         GemmArgs gd{d.wdown + (size_t)l * dm * F, many ? m->w16[3] + (size_t)l * dm * F : nullptr, m->act, nullptr, M, dm, F, 1, m->x, nullptr};
-        gd.part = m->kpart; gd.part_floats = m->kpart_floats; gd.want_split = m->ksplit_opt[2]; gd.mid_waves = m->mid_waves;
+        gd.part = m->kpart; gd.part_floats = m->kpart_floats; gd.want_split = m->ksplit_opt[2]; gd.mid_waves = m->mid_waves; gd.want_tile = m->tile;
         if ((rc = launch_gemm<EPI_RESID>(gd, stream))) return rc;
         pend = gd.n_part;        // added to the residual by the next norm (next layer's, or the final one)
     }
@@ -1032,6 +1034,11 @@ extern "C" int laser_model_set_option(laser_model* mh, const char* name, int val
     if (std::string(name) == "mid_waves") {
         LASER_REQUIRE(value == 0 || value == 4 || value == 8, LASER_E_INVALID_ARG, "mid_waves must be 0 (choose), 4 or 8");
         m->mid_waves = value;
+        return LASER_OK;
+    }
+    if (std::string(name) == "tile") {
+        LASER_REQUIRE(value >= 0, LASER_E_INVALID_ARG, "tile must be >= 0");
+        m->tile = value;
         return LASER_OK;
     }
     if (std::string(name) == "attn_whole_min") {

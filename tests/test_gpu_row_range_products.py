@@ -15,7 +15,8 @@ pytestmark = pytest.mark.gpu
 TOL = 1.6e-3
 
 
-def _step(model, sh, B, K, ctx=37):
+def _step(model, sh, B, K, ctx=37, only=None):
+    """Logits of one step of B sequences made from a fixed seed (of the sequences `only`)."""
     import paper_2408_05676_amd as laser
     kv = gu.make_kv(sh, n_pages=B * 8, max_seqs=B, max_pages_per_seq=8)
     ids = list(range(B))
@@ -30,6 +31,8 @@ def _step(model, sh, B, K, ctx=37):
         kv.set_len(s, ctx)
     tok = torch.randint(0, sh.vocab, (B, K + 1), generator=gen, device="cuda", dtype=torch.int32)
     n = torch.full((B,), K, dtype=torch.int32, device="cuda")
+    if only is not None:
+        ids, tok, n = list(only), tok[list(only)], n[list(only)]
     _, _, logits = laser.verify_step(model, kv, ids, tok[:, 0].contiguous(), tok[:, 1:].contiguous(), n, 2, 0.1, 0, want_logits=True)
     return logits.double()
 
@@ -71,3 +74,70 @@ def test_weights_off_the_16_byte_grid(B, K, copies):
         model.set_option("f16_copies", copies)
         out.append(_step(model, sh, B, K))
     _close(out[1], out[0])
+
+
+# (entries of the tables: 17..80 rows 3; above 13 plain, 9 split, 4 head, 5, 4 and 2 of them also with bf16 weights)
+def _tile_shape(**kw):
+    # columns that leave a part of every tile over, reductions of four and five stages
+    return synth.SHAPES["tiny"].with_(d=256, n_heads=4, ffn=640, vocab=1040, **kw)
+
+
+@pytest.mark.parametrize("tile", range(1, 14))
+@pytest.mark.parametrize("B,K", [(7, 12), (15, 12), (16, 25), (11, 63)])
+@pytest.mark.parametrize("copies", [1, 0])
+def test_every_tile_above_80_rows(tile, B, K, copies):
+    """Each entry of the tile tables, with fp16 and bf16 weights, one and two planes at gate/up, one and several parts of the
+    reduction: less than a tile, a tile and some, several tiles of rows; against the register-staged kernel, 78 rows at most in a call."""
+    import paper_2408_05676_amd as laser
+    sh = _tile_shape()
+    w = gu.gpu_weights(sh)
+    mk = lambda rows: laser.Model(sh.n_layers, sh.d, sh.n_heads, sh.ffn, sh.vocab, w, rows, 64, 256, eps=sh.eps, rope_base=sh.rope_base)
+    few = mk(80)
+    few.set_option("mid_waves", 4)
+    per = max(1, 80 // (K + 1))
+    want = torch.cat([_step(few, sh, B, K, only=range(b, min(b + per, B))) for b in range(0, B, per)])
+    model = mk(B * (K + 1))
+    model.set_option("f16_copies", copies)
+    model.set_option("tile", tile)
+    for split_ffn, parts in ((0, 0), (1, 1), (0, 2)):
+        model.set_option("split_ffn", split_ffn)
+        for name in ("ksplit_qkv", "ksplit_o", "ksplit_down"):
+            model.set_option(name, parts)
+        _close(_step(model, sh, B, K), want)
+
+
+@pytest.mark.parametrize("tile", [1, 2, 3])
+@pytest.mark.parametrize("B,K", [(1, 16), (4, 7), (3, 10), (4, 11), (7, 8), (5, 12), (8, 8), (10, 7)])
+def test_every_tile_of_17_to_80_rows(tile, B, K):
+    sh = _tile_shape()
+    model = gu.make_model(sh, max_rows=80, max_batch=16, max_pos=256)
+    model.set_option("tile", tile)
+    got = _step(model, sh, B, K)
+    model.set_option("mid_waves", 4)
+    _close(got, _step(model, sh, B, K))
+
+
+@pytest.mark.parametrize("tile", [1, 2, 3, 4])
+@pytest.mark.parametrize("topk", [2, 5])
+@pytest.mark.parametrize("copies", [1, 0])
+@pytest.mark.parametrize("B,K", [(9, 8), (16, 12), (12, 40)])
+def test_every_tile_of_the_head(tile, topk, copies, B, K):
+    """Logits against a float64 product, and the acceptance against the rule on those logits."""
+    import paper_2408_05676_amd as laser
+    d, V = 256, 1040
+    gen = torch.Generator(device="cuda").manual_seed(B + tile)
+    w = torch.empty((V, d), dtype=torch.bfloat16, device="cuda").normal_(0.0, 0.1, generator=gen)
+    h = torch.empty((B, K + 1, d), dtype=torch.float16, device="cuda").normal_(generator=gen)
+    want = h.double().flatten(0, 1) @ w.double().t()
+    drafts = want.view(B, K + 1, V)[:, :K].topk(topk, dim=-1).indices[..., -1].to(torch.int32)      # rank topk - 1: just inside
+    drafts[:, K // 2] = want.view(B, K + 1, V)[:, K // 2].topk(topk + 1, dim=-1).indices[:, topk].to(torch.int32)   # just outside
+    n = torch.full((B,), K, dtype=torch.int32, device="cuda")
+    model = laser.Model(0, d, 2, 128, V, {"wlm": w}, B * (K + 1), B, 0)
+    model.set_option("f16_copies", copies)
+    model.set_option("tile", tile)
+    acc, out, logits = laser.verify_head(model, h, drafts, n, topk, -1.0, 2, want_logits=True)
+    # products of fp16 and bf16 are exact in float32, 256 of them are added in float32
+    assert float((logits.double().flatten(0, 1) - want).norm() / want.norm()) <= 1e-5
+    assert (acc == K // 2).all()
+    assert torch.equal(out[:, :K // 2], drafts[:, :K // 2])
+    assert torch.equal(out[:, K // 2], want.view(B, K + 1, V)[:, K // 2].argmax(-1).to(torch.int32))
