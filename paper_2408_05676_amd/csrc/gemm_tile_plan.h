@@ -9,7 +9,7 @@ struct GemmTileShape { int wm, wn; };                   // 16-row and 16-column 
 // Tiles of 96 .. 352 rows and 64 .. 256 columns: for most row counts one of them covers the rows with little padding AND
 // gives a number of units that fills the compute units evenly. Entries marked `common` also exist for bf16 weights.
 constexpr GemmTileShape kTilePlain[] = {{3, 4}, {4, 4}, {5, 4}, {6, 6}, {11, 6}, {5, 2}, {3, 8}, {4, 8}, {5, 8}, {6, 4}, {8, 4}, {8, 8}, {11, 4}};
-constexpr GemmTileShape kTileSplit[] = {{3, 4}, {4, 4}, {5, 4}, {6, 6}, {5, 2}, {3, 6}, {4, 6}, {5, 6}, {6, 4}, {8, 4}};
+constexpr GemmTileShape kTileSplit[] = {{3, 4}, {4, 4}, {5, 4}, {6, 6}, {3, 6}, {4, 6}, {5, 6}, {6, 4}, {8, 4}};
 constexpr GemmTileShape kTileHead[] = {{4, 8}, {6, 8}, {3, 8}, {8, 8}};       // the head's record is 128 columns: wn = 8
 constexpr int kTilePlainCommon = 5, kTileSplitCommon = 4, kTileHeadCommon = 2;
 
