@@ -192,7 +192,9 @@ typedef struct laser_model_desc {
  * with more than 80 rows fp16 copies of the four projection matrices and of the head matrix (2 bytes per parameter:
  * the weight memory doubles) for the tiled many-row kernels. That call synchronises the stream; it fails with
  * LASER_E_HIP if the memory is not there and with LASER_E_LIMIT if a weight exceeds the fp16 range (|w| > 65280).
- * Option "f16_copies" = 0 makes no copies: the tiled kernels then widen the bf16 weights on the fly (slower). */
+ * Option "f16_copies" = 0 makes no copies: the tiled kernels then widen the bf16 weights on the fly (slower).
+ * Weights need the alignment of their elements only; off the 16-byte grid, products of 17 to 80 rows and, with
+ * f16_copies = 0, of more take kernels that stage them through registers (slower). */
 int laser_model_create(const laser_model_desc* desc, void* stream, laser_model** out);
 int laser_model_destroy(laser_model* model);
 
@@ -360,7 +362,7 @@ int laser_generate(laser_model* model, laser_kv* kv, const laser_pool* pool, con
  * "attn_whole_min" = 0 (default: half the number of compute units) or a count: from this many (sequence, head,
  * 16-row query tile) triples on, the general path's attention walks a context in one workgroup instead of
  * splitting it into 256-token parts that a second kernel merges.
- * "attn_waves" = 0 (default: eight when an unsplit launch has fewer than two workgroups per compute unit, else four),
+ * "attn_waves" = 0 (default: eight when an unsplit launch has fewer than 16 workgroups per compute unit, else four),
  * 4 or 8: waves of a workgroup that share the pages of an unsplit context.
  * Unknown names and out-of-range values return LASER_E_INVALID_ARG. */
 int laser_model_set_option(laser_model* model, const char* name, int value);

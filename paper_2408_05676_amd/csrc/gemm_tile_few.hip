@@ -5,10 +5,11 @@
 // weights, and loads into LDS pass about 50 bytes per ns and compute unit, whatever the tile (taking the matrix
 // instructions out changes nothing, taking out the rows' loads gives 30 % at 96 workgroups). With 256 workgroups the
 // weights of QKV at the 7B width stream at 4.4 TB/s between start and end. Against the kernel of gemm_mid.h, which stages
-// the rows through registers with a barrier per step, us at 72 rows (N x K): 12288 x 4096 39.7 -> 28.7, 4096 x 4096
-// 14.9 -> 12.2, 4096 x 11008 25.7 -> 22.8, gate/up 2 x 11008 x 4096 68.9 -> 48.3; 6144 x 2048 14.3 -> 10.9, 2048 x 2048
-// 6.7 -> 6.1, 2048 x 5632 9.6 -> 8.4, gate/up 2 x 5632 x 2048 23.6 -> 23.2. Tried beside it: two waves sharing columns and
-// two the reduction (a third less LDS reading) was within 2 % of this everywhere but the last (21.8).
+// the rows through registers with a barrier per step, us at 72 rows (N x K) inside a step: 12288 x 4096 39.9 -> 30.9,
+// 4096 x 4096 15.1 -> 13.5, 4096 x 11008 26.0 -> 23.0, gate/up 2 x 11008 x 4096 68.3 -> 50.6; 6144 x 2048 14.8 -> 12.9,
+// 2048 x 2048 7.9 -> 7.8, 2048 x 5632 9.4 -> 8.9, gate/up 2 x 5632 x 2048 24.2 -> 23.3. Tried beside it, alone in a loop: two
+// waves sharing columns and two the reduction (a third less LDS reading) was within 2 % of this everywhere but the last
+// (21.8 against 23.2).
 #include <algorithm>
 
 #include "gemm_tile_plan.h"
@@ -27,7 +28,8 @@ constexpr int few_stages(int wm, FewShape s, bool split) {
     return ns;
 }
 
-// Microseconds of a launch, as measured: 0.02 per kilobyte a workgroup stages and 4 for its start and end, one workgroup
+// Of three tiles the best or within 7 % of it at 72 and 80 rows of both widths; with 24 rows the narrowest is up to 22 % better
+// than the one taken (O 8.8 against 10.7 us, down 18.8 against 21.3). Microseconds of a launch: 0.02 per kilobyte a workgroup stages and 4 for its start and end, one workgroup
 // per compute unit at a time, never less than the weights take from memory; a reduction part is written and read again.
 template <int N>
 GemmTilePlan few_plan(const FewShape (&shapes)[N], const GemmTileArgs& t, bool swiglu, int ncu, int want_split, int max_split) {
