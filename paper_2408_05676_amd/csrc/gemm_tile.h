@@ -203,9 +203,11 @@ void gemm_tile_kernel(GemmTileArgs a) {
         pslot = slot;
         slot = nslot;
     }
-    // the surplus requests must not land in a later workgroup's LDS; the last matrix instructions must have written
+    // The surplus requests must not land in a later workgroup's LDS; the last matrix instructions must have written. Reads of
+    // the results in the source stay behind the wait; register copies of the compiler's own might not, which
+    // test_matrix_waits.py looks for in the code as built.
     asm volatile("s_waitcnt vmcnt(0)\n\ts_nop 15\n\ts_nop 15" ::: "memory");
-    static_for<0, NMUL>([&](auto mc) {                       // (reads of the results cannot move ahead of that wait)
+    static_for<0, NMUL>([&](auto mc) {
         constexpr int m = decltype(mc)::value;
         constexpr int i = m / (WN * (SPLIT ? 2 : 1)), q = m % (WN * (SPLIT ? 2 : 1)), j = q % WN;
         float4_t& c = (SPLIT && q >= WN) ? acl[SPLIT ? i : 0][SPLIT ? j : 0] : acc[i][j];
