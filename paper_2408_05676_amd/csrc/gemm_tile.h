@@ -11,8 +11,8 @@ typedef unsigned u32x4a2 __attribute__((ext_vector_type(4), aligned(2)));
 typedef float float4a4_t __attribute__((ext_vector_type(4), aligned(4)));   // a caller's buffer may be aligned to its elements only
 
 struct GemmTileArgs {
-    const uint16_t* W;      // [N][Kd] bf16, or the same values already widened to fp16 (WF16 kernels)
-                            // (SwiGLU: [2F][Kd], gate rows then up rows; N = F)
+    const uint16_t* W;      // [N][Kd] bf16, or (WF16 kernels) the same values widened to fp16, one reduction step after the
+                            // other: [Kd / 64][N][64] (SwiGLU: 2F rows, gate rows then up rows; N = F)
     const uint16_t* X;      // [M][Kd] fp16
     const uint16_t* Xlo;    // [M][Kd] low plane of split activations (x = X + Xlo / 4096), SPLIT kernels only
     int M, N, Kd;
@@ -22,6 +22,7 @@ struct GemmTileArgs {
     float* outf;            // GEPI_F32: [ksplit][M][N]
     uint16_t* outh;         // GEPI_SWIGLU: [M][N] fp16
     HeadPart hp{};          // GEPI_HEAD*: where the per-(row, chunk) statistics go (chunk = the WN * 16 columns of a wave)
+    uint32_t lo_off = 0;    // Xlo - X in bytes, for the tiles of 17..80 rows
     int want_tile = 0;      // for the host: 1 + the entry of the tile table to take, 0: chosen by the rule
 };
 
@@ -75,41 +76,64 @@ void gemm_tile_kernel(GemmTileArgs a) {
     // Rows are unpadded; chunk c of row r sits at c ^ swz(r), so that the 16 rows a fragment read touches at one logical
     // chunk lie in 16 distinct 16-byte bank groups.
     auto swz = [](int row) { return (row / (16 / CH)) & (CH - 1); };
+    // Steps of a weight row are next to each other in a row-major matrix; in the widened copy a step's rows are, so that the
+    // workgroups, which walk the steps together, read one stretch of memory at a time: alone, 256 workgroups with 96 rows
+    // each read 5.0 TB/s of a row-major matrix in pieces of 128 bytes and 6.2 TB/s of the copy.
+    const uint32_t ldw = WF16 ? BK * 2 : ldb;
+    const uint32_t wstep = WF16 ? (uint32_t)a.N * (EPI == GEPI_SWIGLU ? 2 : 1) * (BK * 2) : BK * 2;
+    constexpr int WPW = BN / RPP / NW;                       // weight pieces per wave: load j of a wave is a weight piece iff j < WPW
+    static_assert(WPW * RPP * NW == BN, "every wave's loads change from weights to rows at the same j");
+    // likewise from rows to their low plane, where the rows' pieces divide by the waves; else the plane is reached by an offset
+    constexpr bool LOWB = SPLIT && BM / RPP % NW == 0;
+    constexpr int XPW = LOWB ? WPW + BM / RPP / NW : LPS;
     uint32_t voff[LPS];
-    const char* sbase[LPS];
-    uint32_t ldst[LPS];
-    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
 #pragma unroll
     for (int j = 0; j < LPS; ++j) {
         int p = wave + j * NW;
         p = p < PIECES ? p : PIECES - 1;                     // surplus requests repeat the last piece (same bytes, same place)
         const int row = p * RPP + lane / CH;
         const int c = (lane % CH) ^ swz(row);                // the chunk that lives in this slot of the swizzled row
-        ldst[j] = lds0 + p * 1024;
-        if (p * RPP < BN) {
+        if (j < WPW) {
             // SwiGLU: the 16-row fragments alternate gate, up of the same 16 features
-            const int f = p * RPP / 16;
-            int r0 = tn * BN, r = row;
-            if (EPI == GEPI_SWIGLU) { r0 = tn * (BN / 2) + (f >> 1) * 16; r = row & 15; }
-            const int st = r0 < a.N ? r0 : a.N - 1, wr = r0 + r < a.N ? r0 + r : a.N - 1;
-            const size_t up = (EPI == GEPI_SWIGLU && (f & 1)) ? (size_t)a.N : 0;
-            sbase[j] = reinterpret_cast<const char*>(a.W + (up + st) * a.Kd + k0);
-            voff[j] = (uint32_t)(wr - st) * ldb + c * 16;
+            int r0 = 0, r = row;
+            if (EPI == GEPI_SWIGLU) { r0 = (row >> 5) * 16; r = row & 15; }
+            const int left = a.N - 1 - tn * (EPI == GEPI_SWIGLU ? BN / 2 : BN);
+            r = r0 + r < left ? r0 + r : left;               // (rows past the last repeat it)
+            const uint32_t up = EPI == GEPI_SWIGLU && (row & 16) ? (uint32_t)a.N * ldw : 0;
+            voff[j] = up + (uint32_t)r * ldw + c * 16;
         } else {
             const bool low = SPLIT && p * RPP >= BN + BM;
-            int xr = tm * BM + row - BN - (low ? BM : 0);
-            xr = xr < a.M ? xr : a.M - 1;
-            sbase[j] = reinterpret_cast<const char*>((low ? a.Xlo : a.X) + (size_t)tm * BM * a.Kd + k0);
-            voff[j] = (uint32_t)(xr - tm * BM) * ldb + c * 16;
+            int xr = row - BN - (low ? BM : 0);
+            xr = tm * BM + xr < a.M ? xr : a.M - 1 - tm * BM;
+            voff[j] = (uint32_t)xr * ldb + c * 16 + (low && !LOWB ? a.lo_off : 0);
         }
     }
-    // Load j of the stage of reduction step kt. Requests past the last step are clamped: nobody reads what they bring, but
-    // the counts stay uniform.
-    auto issue = [&](auto jc, int kt, int slot) {
+    // Addresses of the stage being requested (moved on by a step once per stage), and the place of the wave's first piece in
+    // LDS. A request is then four instructions; with a 64-bit address and an LDS address made for each it was about fourteen,
+    // and the matrix instructions behind it waited. Both together, us inside a step at the 7B width: 704 rows QKV 119 -> 109,
+    // gate/up 108 -> 100, down 68 -> 63, O 49 -> 45; 256 rows QKV 49 -> 45.5, down 36.7 -> 33.6.
+    uint64_t wbase = (uint64_t)(uintptr_t)a.W + (uint64_t)tn * (EPI == GEPI_SWIGLU ? BN / 2 : BN) * ldw + (uint64_t)kpart * nk * wstep;
+    uint64_t xbase = (uint64_t)(uintptr_t)(a.X + (size_t)tm * BM * a.Kd + k0);
+    uint64_t lbase = LOWB ? (uint64_t)(uintptr_t)(a.Xlo + (size_t)tm * BM * a.Kd + k0) : 0;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds + wave * 1024;
+    const uint32_t last = lds0 + (PIECES - 1 - wave) * 1024;                 // (p = PIECES - 1)
+    uint32_t lslot = 0;                                                     // LDS offset of the slot being filled
+    // Load j of the stage being requested.
+    auto issue = [&](auto jc) {
         constexpr int j = decltype(jc)::value;
-        const char* g = sbase[j] + (size_t)(kt < nk ? kt : nk - 1) * (BK * 2);
-        const uint32_t vo = voff[j], at = ldst[j] + slot * SBYTES;
-        asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %2" ::"v"(vo), "s"(at), "s"(g) : "memory", "m0");
+        const uint64_t base = j < WPW ? wbase : j < XPW ? xbase : lbase;
+        const u32x4 srd{(uint32_t)base, (uint32_t)(base >> 32), 0xFFFFFFFFu, 0x00020000u};
+        const uint32_t vo = voff[j], at = (PIECES % NW != 0 && j == LPS - 1 && wave + j * NW >= PIECES ? last : lds0 + j * NW * 1024) + lslot;
+        asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %2, 0 offen lds" ::"v"(vo), "s"(at), "s"(srd) : "memory");
+    };
+    // On to the next stage. Requests past the last step repeat it: nobody reads what they bring, but the counts stay uniform.
+    int kreq = 0;
+    auto next_stage = [&] {
+        ++kreq;
+        wbase += kreq < nk ? wstep : 0;
+        xbase += kreq < nk ? BK * 2 : 0;
+        if constexpr (LOWB) lbase += kreq < nk ? BK * 2 : 0;
+        lslot = lslot + SBYTES < SBYTES * NS ? lslot + SBYTES : 0;
     };
 
     float4_t acc[WM][WN];
@@ -150,7 +174,7 @@ void gemm_tile_kernel(GemmTileArgs a) {
     // the compiler moves them back and forth between the register files inside the loop.
     // The loads L0 .. L1-1 of another stage are spread over the same instructions: in a burst they hold up the matrix
     // instructions behind them, about 32 cycles each.
-    auto multiply_read = [&](auto sc, auto rsc, int rslot, auto l0c, auto l1c, int lkt, int lslot) {
+    auto multiply_read = [&](auto sc, auto rsc, int rslot, auto l0c, auto l1c) {
         constexpr int s = decltype(sc)::value, L0 = decltype(l0c)::value, L1 = decltype(l1c)::value;
         if constexpr (!WF16) {
 #pragma unroll
@@ -166,8 +190,8 @@ void gemm_tile_kernel(GemmTileArgs a) {
             constexpr int i = m / (WN * (SPLIT ? 2 : 1)), q = m % (WN * (SPLIT ? 2 : 1)), j = q % WN;
             constexpr int r0 = m * NREAD / NMUL, r1 = (m + 1) * NREAD / NMUL;
             static_for<r0, r1>([&](auto rc) { read_frag(rsc, rc, rslot); });
-            constexpr int l0 = L0 + m * (L1 - L0) / NMUL, l1 = L0 + (m + 1) * (L1 - L0) / NMUL;
-            static_for<l0, l1>([&](auto jc) { issue(jc, lkt, lslot); });
+            constexpr int l0 = L0 + (2 * m * (L1 - L0) + NMUL) / (2 * NMUL), l1 = L0 + (2 * (m + 1) * (L1 - L0) + NMUL) / (2 * NMUL);   // between the reads
+            static_for<l0, l1>([&](auto jc) { issue(jc); });
             constexpr bool inv = i * WN * (SPLIT ? 2 : 1) + q >= 64;      // there are 256 accumulation registers: the rest sit in vector registers
             if constexpr (SPLIT && q >= WN) { if constexpr (inv) mfma_acc_v(fw[s][j], fl[s][i], acl[i][j]); else mfma_acc(fw[s][j], fl[s][i], acl[i][j]); }
             else { if constexpr (inv) mfma_acc_v(fw[s][j], fx[s][i], acc[i][j]); else mfma_acc(fw[s][j], fx[s][i], acc[i][j]); }
@@ -188,19 +212,19 @@ void gemm_tile_kernel(GemmTileArgs a) {
     // requests over both halves, a ring of two takes the half right after the wait (the other half would be too late).
     using LH = std::integral_constant<int, NS >= 3 ? (LPS + 1) / 2 : LPS>;
 #pragma unroll
-    for (int s = 0; s < NS - 1; ++s) static_for<0, LPS>([&](auto jc) { issue(jc, s, s); });
-    static_for<0, LH::value>([&](auto jc) { issue(jc, NS - 1, NS - 1); });
+    for (int s = 0; s < NS - 1; ++s) { static_for<0, LPS>([&](auto jc) { issue(jc); }); next_stage(); }
+    static_for<0, LH::value>([&](auto jc) { issue(jc); });
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 2) * LPS + LH::value) : "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     static_for<0, NREAD>([&](auto rc) { read_frag(C0{}, rc, 0); });
-    int slot = 0, pslot = NS - 1;
+    int slot = 0;
     for (int kt = 0; kt < nk; ++kt) {
         const int nslot = slot + 1 < NS ? slot + 1 : 0;
-        multiply_read(C0{}, C1{}, slot, LH{}, LA{}, kt + NS - 1, pslot);
+        multiply_read(C0{}, C1{}, slot, LH{}, LA{});             // the rest of stage kt + NS - 1
+        next_stage();
         sync();
-        multiply_read(C1{}, C0{}, nslot, L0{}, LH{}, kt + NS, slot);
-        pslot = slot;
+        multiply_read(C1{}, C0{}, nslot, L0{}, LH{});            // stage kt + NS
         slot = nslot;
     }
     // The surplus requests must not land in a later workgroup's LDS; the last matrix instructions must have written. Reads of

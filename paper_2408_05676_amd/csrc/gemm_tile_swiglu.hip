@@ -15,7 +15,7 @@ static void go(const GemmTileArgs& t, int ncu, hipStream_t stream) {
 }
 
 void launch_tile_swiglu(const GemmTileArgs& t, bool f16, int ncu, hipStream_t stream) {
-    if (!on_16_byte_grid(t.W)) return launch_off_grid_swiglu(t, stream);
+    if (!on_16_byte_grid(t.W) || (!f16 && (size_t)t.N * t.Kd * 2 >= (3ull << 30))) return launch_off_grid_swiglu(t, stream);
     if (t.Xlo) { if (f16) go<true, true>(t, ncu, stream); else go<true, false>(t, ncu, stream); }
     else { if (f16) go<false, true>(t, ncu, stream); else go<false, false>(t, ncu, stream); }
 }

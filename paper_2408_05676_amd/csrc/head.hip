@@ -25,8 +25,6 @@
 
 namespace laser {
 
-int widen_copies(const uint16_t* const* src, const size_t* elems, int n, uint16_t** dst, hipStream_t stream);
-
 constexpr int kHeadStreamMaxRows = 16;   // up to here lm_head_kernel; beyond, a GEMM with the head epilogue
 constexpr int kHeadMidMaxRows = 80;      // up to here that GEMM streams the head matrix once; beyond, the tiled one
 
@@ -290,9 +288,8 @@ static int run_head_bufs(Model* m, const uint16_t* h, const int32_t* tokens, con
     } else {
         hp.chunks = (V + 127) / 128;
         if (m->f16_copies && !m->wlm16) {          // first many-row head: widen the head matrix to fp16 once
-            const uint16_t* src[1] = {m->d.wlm};
-            const size_t n[1] = {(size_t)V * dm};
-            const int rc = widen_copies(src, n, 1, &m->wlm16, stream);
+            const WidenSource src{m->d.wlm, 1, V, dm};
+            const int rc = widen_copies(&src, 1, &m->wlm16, stream);
             if (rc) return rc;
         }
         if (!on_16_byte_grid(h)) {

@@ -157,7 +157,7 @@ static void launch_rmsnorm(int M, hipStream_t stream, float* x, const float* gai
 
 struct GemmArgs {
     const uint16_t* W;      // [N][Kd]  (EPI_SWIGLU: [2N][Kd], gate rows then up rows)
-    const uint16_t* W16;    // the same matrix widened to fp16 (many-row path only), or NULL
+    const uint16_t* W16;    // the same matrix widened to fp16 and laid out by reduction steps (many-row path only), or NULL
     const uint16_t* X;      // [M][Kd]
     const uint16_t* Xlo;    // [M][Kd] low plane of split activations, or NULL
     int M, N, Kd, S;
@@ -244,30 +244,36 @@ __global__ __launch_bounds__(256) void gemm_skinny_kernel(GemmArgs a) {
 
 constexpr int kSkinnyMaxRows = 80;   // beyond this the weights would be streamed more than once
 
-// bf16 -> fp16 copy of a weight matrix, 8 elements per thread and iteration; counts the values whose magnitude fp16
-// cannot hold (they would become infinities)
-__global__ __launch_bounds__(256) void widen_weights_kernel(const uint16_t* __restrict__ src, uint16_t* __restrict__ dst, size_t n8,
+// bf16 -> fp16 copy of `mats` weight matrices [N][Kd], each laid out by reduction steps of 64: [Kd / 64][N][64]. A thread takes
+// 8 elements per iteration, eight threads a step of a row; the values whose magnitude fp16 cannot hold (they would become
+// infinities) are counted.
+__global__ __launch_bounds__(256) void widen_weights_kernel(const uint16_t* __restrict__ src, uint16_t* __restrict__ dst, int N, int Kd, size_t n8,
                                                             int* __restrict__ overflow) {
     int bad = 0;
+    const uint32_t k8 = (uint32_t)Kd / 8;
     for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n8; i += (size_t)gridDim.x * 256) {
         Frag8 f;
         f.u = reinterpret_cast<const uint4*>(src)[i];
 #pragma unroll
         for (int j = 0; j < 8; ++j) bad += (f.h[j] & 0x7FFFu) > 0x477Fu ? 1 : 0;     // |w| > 65280 (bf16 pattern), inf and NaN included
         bf16x8_to_f16x8(f);
-        reinterpret_cast<uint4*>(dst)[i] = f.u;
+        const size_t row = i / k8;
+        const uint32_t k = (uint32_t)(i - row * k8);
+        const size_t mat = row / (uint32_t)N;
+        const uint32_t n = (uint32_t)(row - mat * (uint32_t)N);
+        reinterpret_cast<uint4*>(dst)[mat * N * k8 + ((size_t)(k / 8) * N + n) * 8 + k % 8] = f.u;
     }
     if (bad) atomicAdd(overflow, bad);
 }
 
-// fp16 copies of `n` bf16 matrices for the tiled many-row kernels (made once, at the first call that needs them; that
+// fp16 copies of `n` groups of bf16 matrices for the tiled many-row kernels (made once, at the first call that needs them; that
 // call synchronises the stream). All or nothing: on failure nothing is kept. LASER_E_LIMIT if a weight does not fit fp16.
-int widen_copies(const uint16_t* const* src, const size_t* elems, int n, uint16_t** dst, hipStream_t stream) {
+int widen_copies(const WidenSource* src, int n, uint16_t** dst, hipStream_t stream) {
     uint16_t* cp[4] = {nullptr, nullptr, nullptr, nullptr};
     int* flag = nullptr;
     auto drop = [&] { for (int i = 0; i < n; ++i) if (cp[i]) (void)hipFree(cp[i]); if (flag) (void)hipFree(flag); };
     hipError_t e = hipMalloc((void**)&flag, sizeof(int));
-    for (int i = 0; i < n && e == hipSuccess; ++i) e = hipMalloc((void**)&cp[i], elems[i] * 2);
+    for (int i = 0; i < n && e == hipSuccess; ++i) e = hipMalloc((void**)&cp[i], (size_t)src[i].mats * src[i].N * src[i].Kd * 2);
     if (e == hipSuccess) e = hipMemsetAsync(flag, 0, sizeof(int), stream);
     if (e != hipSuccess) {
         drop();
@@ -275,7 +281,8 @@ int widen_copies(const uint16_t* const* src, const size_t* elems, int n, uint16_
         return LASER_E_HIP;
     }
     for (int i = 0; i < n; ++i)
-        hipLaunchKernelGGL(widen_weights_kernel, dim3(2048), dim3(256), 0, stream, src[i], cp[i], elems[i] / 8, flag);
+        hipLaunchKernelGGL(widen_weights_kernel, dim3(2048), dim3(256), 0, stream, src[i].w, cp[i], src[i].N, src[i].Kd,
+                           (size_t)src[i].mats * src[i].N * src[i].Kd / 8, flag);
     int bad = 0;
     e = hipMemcpyAsync(&bad, flag, sizeof(int), hipMemcpyDeviceToHost, stream);
     if (e == hipSuccess) e = hipStreamSynchronize(stream);
@@ -294,12 +301,15 @@ template <int EPI>
 static int launch_gemm(GemmArgs& a_in, hipStream_t stream) {
     GemmArgs& a = a_in;
     a.n_part = 0;
-    const bool few = a.M > 16 && a.M <= kSkinnyMaxRows && a.mid_waves == 0 && (EPI != EPI_SWIGLU || a.Xlo) && on_16_byte_grid(a.W);
+    // (32-bit offsets reach the low plane, and the up half of a row-major gate/up matrix)
+    const bool near = (!a.Xlo || (a.Xlo > a.X && (size_t)(a.Xlo - a.X) * 2 < (3ull << 30))) && (EPI != EPI_SWIGLU || (size_t)a.N * a.Kd * 2 < (3ull << 30));
+    const bool few = a.M > 16 && a.M <= kSkinnyMaxRows && a.mid_waves == 0 && (EPI != EPI_SWIGLU || a.Xlo) && on_16_byte_grid(a.W) && near;
     if (a.M > kSkinnyMaxRows || few) {
         int ncu = 0;
         LASER_HIP_CHECK(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, 0));
         GemmTileArgs t{!few && a.W16 ? a.W16 : a.W, a.X, a.Xlo, a.M, a.N, a.Kd, 0, 0, 1, nullptr, a.outh};
         t.want_tile = a.want_tile;
+        t.lo_off = few && a.Xlo ? (uint32_t)(a.Xlo - a.X) * 2 : 0;
         if constexpr (EPI == EPI_SWIGLU) {
             if (few) launch_few_swiglu(t, ncu, stream);
             else launch_tile_swiglu(t, a.W16 != nullptr, ncu, stream);
@@ -713,10 +723,8 @@ static int forward(Model* m, KV* kv, const int32_t* ids_dev, const int32_t* pend
                        R, dm, d.vocab, d.eps, m->x, m->xn, m->xn_lo);
     if (M > kSkinnyMaxRows && m->f16_copies && !m->w16[0]) {
         // first many-row step: widen the four projection matrices to fp16 once (same rounding as the kernels' own)
-        const size_t n[4] = {(size_t)d.n_layers * 3 * dm * dm, (size_t)d.n_layers * dm * dm, (size_t)d.n_layers * 2 * F * dm,
-                             (size_t)d.n_layers * dm * F};
-        const uint16_t* src[4] = {d.wqkv, d.wo, d.wgu, d.wdown};
-        const int rc = widen_copies(src, n, 4, m->w16, stream);
+        const WidenSource src[4] = {{d.wqkv, d.n_layers, 3 * dm, dm}, {d.wo, d.n_layers, dm, dm}, {d.wgu, d.n_layers, 2 * F, dm}, {d.wdown, d.n_layers, dm, F}};
+        const int rc = widen_copies(src, 4, m->w16, stream);
         if (rc) return rc;
     }
     if (M > 16 && !m->kpart) {
@@ -813,7 +821,7 @@ using namespace laser;
 extern "C" int laser_model_destroy(laser_model* h) {
     if (!h) return LASER_OK;
     Model* m = reinterpret_cast<Model*>(h);
-    void* ptrs[] = {m->kpart, m->wlm16, m->w16[0], m->w16[1], m->w16[2], m->w16[3], m->x, m->xn, m->xn_lo, m->q_lo, m->attn_lo, m->qkv, m->q, m->attn, m->act, m->row_pos, m->att_part, m->rope, m->hp_max,
+    void* ptrs[] = {m->kpart, m->wlm16, m->w16[0], m->w16[1], m->w16[2], m->w16[3], m->x, m->xn, m->q_lo, m->qkv, m->q, m->attn, m->act, m->row_pos, m->att_part, m->rope, m->hp_max,
                     m->hp_sum, m->hp_arg, m->hp_topv, m->hp_topi, m->cand_beg, m->cand_cnt, m->cand_x, m->node_cand, m->cand_lx, m->row_slot, m->row_anc,
                     m->row_mx, m->row_sum, m->row_arg, m->cand_rank};
     for (void* p : ptrs) if (p) (void)hipFree(p);
@@ -845,7 +853,7 @@ extern "C" int laser_model_create(const laser_model_desc* desc, void* stream_, l
     auto fail = [&](int rc) { laser_model_destroy(reinterpret_cast<laser_model*>(m)); return rc; };
 #define M_TRY(expr) do { hipError_t e_ = (expr); if (e_ != hipSuccess) { set_error("%s: %s", #expr, hipGetErrorString(e_)); return fail(LASER_E_HIP); } } while (0)
     const size_t R = (size_t)d.max_rows, dm = (size_t)d.d_model;
-    M_TRY(hipMalloc((void**)&m->xn, R * dm * 2));
+    M_TRY(hipMalloc((void**)&m->xn, R * dm * (d.n_layers > 0 ? 4 : 2)));         // both planes
     M_TRY(hipMalloc((void**)&m->cand_beg, R * 4));
     M_TRY(hipMalloc((void**)&m->cand_cnt, R * 4));
     M_TRY(hipMalloc((void**)&m->cand_x, R * 4));
@@ -859,10 +867,10 @@ extern "C" int laser_model_create(const laser_model_desc* desc, void* stream_, l
         M_TRY(hipMalloc((void**)&m->x, R * dm * 4));
         M_TRY(hipMalloc((void**)&m->qkv, R * dm * 3 * 4));
         M_TRY(hipMalloc((void**)&m->q, R * dm * 2));
-        M_TRY(hipMalloc((void**)&m->attn, R * dm * 2));
-        M_TRY(hipMalloc((void**)&m->xn_lo, R * dm * 2));
+        M_TRY(hipMalloc((void**)&m->attn, R * dm * 4));                           // both planes
+        m->xn_lo = m->xn + R * dm;
+        m->attn_lo = m->attn + R * dm;
         M_TRY(hipMalloc((void**)&m->q_lo, R * dm * 2));
-        M_TRY(hipMalloc((void**)&m->attn_lo, R * dm * 2));
         M_TRY(hipMalloc((void**)&m->act, R * (size_t)d.ffn * 2));
         M_TRY(hipMalloc((void**)&m->row_pos, R * 4));
         M_TRY(hipMalloc((void**)&m->row_slot, R * 4));

@@ -48,7 +48,8 @@ struct Model {
     // workspace (device)
     float* x = nullptr;          // [max_rows][d]   residual stream
     uint16_t* xn = nullptr;      // [max_rows][d]   normed activations (fp16, high plane)
-    uint16_t* xn_lo = nullptr;   // [max_rows][d]   their low plane (x = xn + xn_lo / 4096); likewise q_lo, attn_lo
+    uint16_t* xn_lo = nullptr;   // [max_rows][d]   their low plane (x = xn + xn_lo / 4096), behind xn in one allocation; likewise q_lo
+                                 // (an allocation of its own), attn_lo (behind attn)
     uint16_t* q_lo = nullptr;
     uint16_t* attn_lo = nullptr;
     float* qkv = nullptr;        // [max_rows][3d]
@@ -86,9 +87,10 @@ struct Model {
     void* fused_ws = nullptr;          // workspace of the persistent few-row kernel (fused.hip)
     int use_fused = 1;                 // 0 forces the generic multi-kernel path
     int fused_trace = 0;               // 1: thread 0 of every workgroup stamps the wall clock at phase edges
-    uint16_t* w16[4] = {nullptr, nullptr, nullptr, nullptr};   // fp16 copies of wqkv, wo, wgu, wdown for the tiled many-row
-                                                               // kernels, made at the first step with more than 80 rows
-    uint16_t* wlm16 = nullptr;         // fp16 copy of the head matrix, made at the first head call with more than 80 rows
+    uint16_t* w16[4] = {nullptr, nullptr, nullptr, nullptr};   // fp16 copies of wqkv, wo, wgu, wdown for the tiled many-row kernels,
+                                                               // laid out by reduction steps ([Kd / 64][N][64] per layer), made
+                                                               // at the first step with more than 80 rows
+    uint16_t* wlm16 = nullptr;         // fp16 copy of the head matrix, likewise, made at the first head call with more than 80 rows
     int f16_copies = 1;                // 0: the tiled kernels stream the bf16 weights and widen them in the loop (no copies)
     float* kpart = nullptr;            // partial results of reduction-split tiled GEMMs (many-row path), [parts][rows][N]
     size_t kpart_floats = 0;
@@ -99,5 +101,9 @@ struct Model {
     int attn_waves = 0;                // unsplit attention: waves per workgroup that share a context's pages (4 or 8), 0 = chosen per launch shape
     int split_ffn = 0;                 // 1: the many-row (tiled) gate/up product also takes split activations
 };
+
+// `mats` matrices [N][Kd] in a row, and their fp16 copies for the tiled kernels (model.hip)
+struct WidenSource { const uint16_t* w; int mats, N, Kd; };
+int widen_copies(const WidenSource* src, int n, uint16_t** dst, hipStream_t stream);
 
 }  // namespace laser
