@@ -141,3 +141,9 @@ def test_every_tile_of_the_head(tile, topk, copies, B, K):
     assert (acc == K // 2).all()
     assert torch.equal(out[:, :K // 2], drafts[:, :K // 2])
     assert torch.equal(out[:, K // 2], want.view(B, K + 1, V)[:, K // 2].argmax(-1).to(torch.int32))
+
+
+@pytest.mark.parametrize("B,K", [(7, 12), (16, 25)])
+def test_tile_of_128_rows_and_192_columns(B, K):
+    """The entry of the plain table behind those above, as they are tested."""
+    test_every_tile_above_80_rows(14, B, K, 1)
