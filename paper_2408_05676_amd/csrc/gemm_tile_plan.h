@@ -69,9 +69,9 @@ inline void gemm_tile_go(GemmTileArgs t, int S, hipStream_t stream) {
 // t: W, X, Xlo, M, N, Kd and the output; f16: W is fp16. Returns the number of reduction parts stored at t.outf.
 int launch_tile_f32(const GemmTileArgs& t, bool f16, int ncu, int want_split, int max_split, hipStream_t stream);
 void launch_tile_swiglu(const GemmTileArgs& t, bool f16, int ncu, hipStream_t stream);
-// 17..80 rows (gemm_tile_few.hip): t.W is bf16; SwiGLU takes split activations.
-int launch_few_f32(const GemmTileArgs& t, int ncu, int want_split, int max_split, hipStream_t stream);
-void launch_few_swiglu(const GemmTileArgs& t, int ncu, hipStream_t stream);
+// The same for 17..80 rows (gemm_tile_few.hip); SwiGLU takes split activations.
+int launch_few_f32(const GemmTileArgs& t, bool f16, int ncu, int want_split, int max_split, hipStream_t stream);
+void launch_few_swiglu(const GemmTileArgs& t, bool f16, int ncu, hipStream_t stream);
 void launch_tile_head(const GemmTileArgs& t, bool f16, int ncu, hipStream_t stream);
 // The same for t.W bf16 off the 16-byte grid, more than 80 rows (gemm_off_grid.hip).
 int launch_off_grid_f32(const GemmTileArgs& t, int ncu, int want_split, int max_split, hipStream_t stream);

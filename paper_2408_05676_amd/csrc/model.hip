@@ -157,7 +157,7 @@ static void launch_rmsnorm(int M, hipStream_t stream, float* x, const float* gai
 
 struct GemmArgs {
     const uint16_t* W;      // [N][Kd]  (EPI_SWIGLU: [2N][Kd], gate rows then up rows)
-    const uint16_t* W16;    // the same matrix widened to fp16 and laid out by reduction steps (many-row path only), or NULL
+    const uint16_t* W16;    // the same matrix widened to fp16 and laid out by reduction steps (more than 16 rows), or NULL
     const uint16_t* X;      // [M][Kd]
     const uint16_t* Xlo;    // [M][Kd] low plane of split activations, or NULL
     int M, N, Kd, S;
@@ -301,17 +301,17 @@ template <int EPI>
 static int launch_gemm(GemmArgs& a_in, hipStream_t stream) {
     GemmArgs& a = a_in;
     a.n_part = 0;
-    // (32-bit offsets reach the low plane, and the up half of a row-major gate/up matrix)
+    // 32-bit offsets reach the low plane, and the up half of a row-major gate/up matrix
     const bool near = (!a.Xlo || (a.Xlo > a.X && (size_t)(a.Xlo - a.X) * 2 < (3ull << 30))) && (EPI != EPI_SWIGLU || (size_t)a.N * a.Kd * 2 < (3ull << 30));
-    const bool few = a.M > 16 && a.M <= kSkinnyMaxRows && a.mid_waves == 0 && (EPI != EPI_SWIGLU || a.Xlo) && on_16_byte_grid(a.W) && near;
+    const bool few = a.M > 16 && a.M <= kSkinnyMaxRows && a.mid_waves == 0 && (EPI != EPI_SWIGLU || a.Xlo) && (a.W16 || on_16_byte_grid(a.W)) && near;
     if (a.M > kSkinnyMaxRows || few) {
         int ncu = 0;
         LASER_HIP_CHECK(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, 0));
-        GemmTileArgs t{!few && a.W16 ? a.W16 : a.W, a.X, a.Xlo, a.M, a.N, a.Kd, 0, 0, 1, nullptr, a.outh};
+        GemmTileArgs t{a.W16 ? a.W16 : a.W, a.X, a.Xlo, a.M, a.N, a.Kd, 0, 0, 1, nullptr, a.outh};
         t.want_tile = a.want_tile;
         t.lo_off = few && a.Xlo ? (uint32_t)(a.Xlo - a.X) * 2 : 0;
         if constexpr (EPI == EPI_SWIGLU) {
-            if (few) launch_few_swiglu(t, ncu, stream);
+            if (few) launch_few_swiglu(t, a.W16 != nullptr, ncu, stream);
             else launch_tile_swiglu(t, a.W16 != nullptr, ncu, stream);
         } else {
             // The result goes to the workspace, in one or more reduction parts, and the next kernel (rotary + cache write, or
@@ -320,7 +320,7 @@ static int launch_gemm(GemmArgs& a_in, hipStream_t stream) {
             while (max_split > 1 && (size_t)max_split * a.M * a.N > a.part_floats) max_split /= 2;
             LASER_REQUIRE(a.part && (size_t)a.M * a.N <= a.part_floats, LASER_E_LIMIT, "the partial-result workspace is too small");
             t.outf = a.part;
-            a.n_part = few ? launch_few_f32(t, ncu, 0, max_split, stream)
+            a.n_part = few ? launch_few_f32(t, a.W16 != nullptr, ncu, 0, max_split, stream)
                            : launch_tile_f32(t, a.W16 != nullptr, ncu, a.want_split, max_split, stream);
         }
         LASER_HIP_CHECK(hipGetLastError());
@@ -721,11 +721,23 @@ static int forward(Model* m, KV* kv, const int32_t* ids_dev, const int32_t* pend
                        m->row_pos, m->row_slot, m->row_anc);
     hipLaunchKernelGGL(embed_rmsnorm_kernel, dim3(M), dim3(256), 0, stream, d.emb, d.g1, pending, drafts, draft_len,
                        R, dm, d.vocab, d.eps, m->x, m->xn, m->xn_lo);
-    if (M > kSkinnyMaxRows && m->f16_copies && !m->w16[0]) {
-        // first many-row step: widen the four projection matrices to fp16 once (same rounding as the kernels' own)
+    if (M > 16 && m->f16_copies && !m->w16[0] && (M > kSkinnyMaxRows || !m->no_few_copies)) {
+        // first step with more than 16 rows: widen the four projection matrices to fp16 once (same rounding as the kernels' own)
         const WidenSource src[4] = {{d.wqkv, d.n_layers, 3 * dm, dm}, {d.wo, d.n_layers, dm, dm}, {d.wgu, d.n_layers, 2 * F, dm}, {d.wdown, d.n_layers, dm, F}};
-        const int rc = widen_copies(src, 4, m->w16, stream);
-        if (rc) return rc;
+        if (M > kSkinnyMaxRows) {
+            const int rc = widen_copies(src, 4, m->w16, stream);
+            if (rc) return rc;
+        } else {
+            // up to 80 rows the kernels take the caller's weights as well (10 % slower): copies only out of memory that is plainly
+            // spare, and none where they cannot be made (a weight beyond fp16, a stream being captured)
+            hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+            size_t free_b = 0, total_b = 0, need = 0;
+            for (const WidenSource& w : src) need += (size_t)w.mats * w.N * w.Kd * 2;
+            if (hipStreamIsCapturing(stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone) {
+                m->no_few_copies = hipMemGetInfo(&free_b, &total_b) != hipSuccess || need > free_b / 4 || widen_copies(src, 4, m->w16, stream) != LASER_OK;
+                if (m->no_few_copies) (void)hipGetLastError();
+            }
+        }
     }
     if (M > 16 && !m->kpart) {
         // workspace for reduction-split partial results: up to 8 parts of [max_rows][d] or 2 of [max_rows][3 d], 4 up to 80 rows
@@ -757,7 +769,7 @@ static int forward(Model* m, KV* kv, const int32_t* ids_dev, const int32_t* pend
         if (l > 0)
             launch_rmsnorm(M, stream, m->x, d.g1 + (size_t)l * dm, dm, d.eps, m->xn, m->xn_lo, (const float*)m->kpart, pend, (size_t)M * dm);
         pend = 0;
-        const bool many = M > kSkinnyMaxRows && m->w16[0];      // tiled path: weights from the fp16 copy (if kept)
+        const bool many = M > 16 && m->w16[0];      // tiled path: weights from the fp16 copy (if kept)
         GemmArgs g{d.wqkv + (size_t)l * 3 * dm * dm, many ? m->w16[0] + (size_t)l * 3 * dm * dm : nullptr, m->xn, m->xn_lo, M, 3 * dm, dm, 1, m->qkv, nullptr};
         g.part = m->kpart; g.part_floats = m->kpart_floats; g.want_split = m->ksplit_opt[0]; g.mid_waves = m->mid_waves; g.want_tile = m->tile;
         if ((rc = launch_gemm<EPI_F32>(g, stream))) return rc;

@@ -147,3 +147,34 @@ def test_every_tile_of_the_head(tile, topk, copies, B, K):
 def test_tile_of_128_rows_and_192_columns(B, K):
     """The entry of the plain table behind those above, as they are tested."""
     test_every_tile_above_80_rows(14, B, K, 1)
+
+
+@pytest.mark.parametrize("d,heads,ffn", [(128, 2, 128), (640, 5, 1920)])
+@pytest.mark.parametrize("B,K", [(1, 16), (4, 7), (6, 7), (10, 7)])
+def test_copies_of_17_to_80_rows(d, heads, ffn, B, K):
+    """The fp16 copies hold the values that the kernels make of the bf16 weights: the same products, bit for bit."""
+    sh = synth.SHAPES["tiny"].with_(d=d, n_heads=heads, ffn=ffn, vocab=512)
+    out = []
+    for copies in (1, 0):
+        model = gu.make_model(sh, max_rows=80, max_batch=16, max_pos=256)
+        model.set_option("f16_copies", copies)
+        out.append(_step(model, sh, B, K))
+    assert torch.equal(out[0], out[1])
+
+
+def test_a_weight_beyond_fp16_takes_no_copies():
+    """Up to 80 rows the step does without copies; with more it is refused, as it says."""
+    import paper_2408_05676_amd as laser
+    sh = _tile_shape()
+    w = dict(gu.gpu_weights(sh))
+    w["wdown"] = w["wdown"].clone()
+    w["wdown"][1, 3, 5] = 1e5
+    out = []
+    for copies in (1, 0):
+        model = laser.Model(sh.n_layers, sh.d, sh.n_heads, sh.ffn, sh.vocab, w, 96, 16, 256, eps=sh.eps, rope_base=sh.rope_base)
+        model.set_option("f16_copies", copies)
+        out.append(_step(model, sh, 4, 7))
+    assert torch.equal(out[0], out[1])
+    model.set_option("f16_copies", 1)
+    with pytest.raises(laser.LaserError, match="fp16 range"):
+        _step(model, sh, 12, 7)
