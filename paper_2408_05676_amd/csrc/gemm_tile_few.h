@@ -29,9 +29,10 @@ constexpr int few_stages(int wm, FewShape s, bool split) {
     return ns;
 }
 
-// Of three tiles the best or within 7 % of it at 72 and 80 rows of both widths; with 24 rows the narrowest is up to 22 % better
-// than the one taken (O 8.8 against 10.7 us, down 18.8 against 21.3). Microseconds of a launch: 0.02 per kilobyte a workgroup stages and 4 for its start and end, one workgroup
-// per compute unit at a time, never less than the weights take from memory; a reduction part is written and read again.
+// Microseconds of a launch: per kilobyte a workgroup stages 0.0095 for rows and for weights 0.032, or more from 195 workgroups on,
+// where memory is what they wait for; 4 for its start and end, one workgroup per compute unit at a time; a reduction part is
+// written and read again. (One rate for both sent 24 rows to too few workgroups: at the 7B width QKV 22.5 us, now 18.8, O
+// 10.2 -> 8.7, down 18.3 -> 16.7; down of 48 rows 22.3 -> 18.6.)
 template <int N>
 GemmTilePlan few_plan(const FewShape (&shapes)[N], const GemmTileArgs& t, bool swiglu, int ncu, int want_split, int max_split) {
     GemmTilePlan best{0, 1};
@@ -42,12 +43,12 @@ GemmTilePlan few_plan(const FewShape (&shapes)[N], const GemmTileArgs& t, bool s
         if (t.want_tile > 0 && t.want_tile <= N && v != t.want_tile - 1) continue;
         const int bn = shapes[v].wn * 16 * shapes[v].nwn, bf = swiglu ? bn / 2 : bn;
         const long tiles = (t.N + bf - 1) / bf;
-        const double stage = 0.02 * (gemm_tile_lds(bm, bn, 1, t.Xlo != nullptr) / 1024);
         for (int S = 1; S <= max_split; S *= 2) {
             if (want_split > 0 ? S != want_split : (nk % S || (S > 1 && nk / S < 4))) continue;
             const long rounds = (tiles * S + ncu - 1) / ncu;
-            const double stream = (double)t.N * t.Kd * (swiglu ? 4 : 2) / 5.0e6 + 4.0;
-            const double cost = std::max((double)rounds * (nk / S * stage + 4.0), stream) + (S - 1) * (8.0 * t.M * t.N / 4.0e6);
+            const double w_kb = std::max(0.032, 0.164e-3 * (double)std::min((long)ncu, tiles * S));
+            const double stage = 0.0095 * (bm * (t.Xlo ? 2 : 1) / 8) + w_kb * (bn / 8);
+            const double cost = (double)rounds * (nk / S * stage + 4.0) + (S - 1) * (8.0 * t.M * t.N / 4.0e6);
             if (cost < best_cost) { best_cost = cost; best = GemmTilePlan{v, S}; }
         }
     }
