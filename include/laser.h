@@ -189,11 +189,11 @@ typedef struct laser_model_desc {
  * (head-only use). Further allocations happen lazily, inside the first call that needs them:
  * with more than 16 rows a workspace for reduction-split partial results (d_model * 32 bytes per row of max_rows, 48 for
  * the first 80 if that is more);
- * with more than 16 rows fp16 copies of the four projection matrices, with more than 80 rows of the head matrix too (2
- * bytes per parameter: the weight memory doubles), for the tiled kernels. That call synchronises the stream. With more than
- * 80 rows it fails with LASER_E_HIP if the memory is not there and with LASER_E_LIMIT if a weight exceeds the fp16 range
- * (|w| > 65280); up to 80 rows it then does without, as it does while the stream is being captured and where the copies
- * would take more than a quarter of the free memory.
+ * fp16 copies of the four projection matrices and of the head matrix (2 bytes per parameter: the weight memory doubles),
+ * inside the first step that takes them; that call synchronises the stream. With more than 80 rows it fails with
+ * LASER_E_HIP if the memory is not there and with LASER_E_LIMIT if a weight exceeds the fp16 range (|w| > 65280); up to 80
+ * rows it then does without, as it does while the stream is being captured and where the copies would take more than a
+ * quarter of the free memory. laser_verify_head makes its copy with more than 80 rows, laser_verify_head_static none.
  * Without copies (option "f16_copies" = 0 makes none) the tiled kernels widen the bf16 weights on the fly (slower).
  * Weights need the alignment of their elements only; off the 16-byte grid and without copies they take kernels that stage
  * them through registers (slower). */

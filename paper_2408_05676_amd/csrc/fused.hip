@@ -197,6 +197,7 @@ enum { PH_QKV = 0, PH_O = 1, PH_GU = 2, PH_DOWN = 3, PH_HEAD = 4 };
 struct Phase {
     const uint16_t* W;    // matrix of this layer
     int kind, Kd;
+    int N;                // its rows
     int planes;           // planes of its activations: 2 = split (fp16 high + 8-bit low), 1 = single fp16
 };
 
@@ -242,9 +243,17 @@ __device__ inline int unit_row(const FusedArgs& a, int kind, int u, int st) {
 // holds elements 32 c + 8 g .. + 7 of row r, so the four lanes of a row read 64 contiguous bytes per instruction
 // and an instruction touches 16 half lines (a lane reading its own 64 contiguous bytes would spread every
 // instruction over 32 lines, each requested four times per step).
-__device__ inline void load_w(Frag8 (&f)[4], const uint16_t* p) {
+// `next`: elements from one fragment to the next: 32 in a row-major matrix, where an instruction touches 16 half lines and the
+// next one their other halves; in the fp16 copies ([Kd / 32][N][32]) an instruction reads one kilobyte in a row, and the loads
+// say that nobody reads it again (which costs 6 % where two instructions share a line). 7B, nine rows: 3.95 ms row-major,
+// 3.85 with the copies, 3.71 with both; 1B, four rows 1.11, 1.06, 1.05.
+template <bool W16>
+__device__ inline void load_w(Frag8 (&f)[4], const uint16_t* p, size_t next) {
 #pragma unroll
-    for (int c = 0; c < 4; ++c) f[c].u = *reinterpret_cast<const uint4*>(p + c * 32);
+    for (int c = 0; c < 4; ++c) {
+        if constexpr (W16) f[c].v4 = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p + c * next));
+        else f[c].u = *reinterpret_cast<const uint4*>(p + c * 32);
+    }
 }
 
 // The reduction dimension is processed in chunks whose activations fit the LDS staging area
@@ -280,9 +289,15 @@ __device__ inline WaveWork wave_work(const FusedArgs& a, const Phase& ph, int ch
     return w;
 }
 
+// W16: the weights are the fp16 copies, laid out by fragments of the reduction ([Kd / 32][N][32])
+template <bool W16>
 __device__ inline const uint16_t* w_ptr(const FusedArgs& a, const Phase& ph, int u, int st, int ks, int lane) {
+    if constexpr (W16) return ph.W + ((size_t)4 * ks * ph.N + unit_row(a, ph.kind, u, st) + (lane & 15)) * 32 + (lane >> 4) * 8;
     return ph.W + (size_t)(unit_row(a, ph.kind, u, st) + (lane & 15)) * ph.Kd + ks * 128 + (lane >> 4) * 8;
 }
+// elements from one step (of 128) of a weight row to the next, and what load_w wants
+template <bool W16> __device__ inline size_t w_step(const Phase& ph) { return W16 ? (size_t)128 * ph.N : 128; }
+template <bool W16> __device__ inline size_t w_next(const Phase& ph) { return W16 ? (size_t)32 * ph.N : 32; }
 
 // Weight streaming through a register ring. A step (128 reduction elements) of a phase with NA
 // streams occupies NA weight fragments (4 x 16 B per lane each); the ring holds DS steps, so DS-1
@@ -319,7 +334,7 @@ static_assert(DS_QKV <= RING_SLOTS && DS_O <= RING_SLOTS && DS_DOWN <= RING_SLOT
 // phase's activations. The loads are unconditional (steps past the wave's last one re-request one cached line),
 // so that the number of vector-memory instructions issued here is a compile-time constant: stage_wait counts
 // on it.
-template <int NA, int T0, int T1>
+template <bool W16, int NA, int T0, int T1>
 __device__ inline void prime_steps(const FusedArgs& a, const Phase& ph, int chunk, Ring& R) {
     const int lane = threadIdx.x & 63;
     const WaveWork w = wave_work(a, ph, chunk);
@@ -331,7 +346,7 @@ __device__ inline void prime_steps(const FusedArgs& a, const Phase& ph, int chun
         const int tc = on ? t : 0;
 #pragma unroll
         for (int s = 0; s < NA; ++s)
-            load_w(R.f[t * NA + s], on ? w_ptr(a, ph, tc / nks, s, w.ks0 + tc % nks, lane) : park);
+            load_w<W16>(R.f[t * NA + s], on ? w_ptr<W16>(a, ph, tc / nks, s, w.ks0 + tc % nks, lane) : park, on ? w_next<W16>(ph) : 32);
     }
 }
 // vector-memory instructions prime_steps<NA, T0, T1> issues
@@ -414,7 +429,7 @@ __device__ inline void stage_wait() {
 
 // Streams one chunk: this wave's units x steps, partial sums of finished units to sh.red
 // (stored on the first chunk, accumulated on later ones; slot = unit * NA + stream).
-template <int NA, int DS, bool SPLIT>
+template <bool W16, int NA, int DS, bool SPLIT>
 __device__ inline void stream_chunk(const FusedArgs& a, Shared& sh, const uint4* xs, const Phase& ph,
                                     const WaveWork& w, bool first, Ring& R) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -426,25 +441,28 @@ __device__ inline void stream_chunk(const FusedArgs& a, Shared& sh, const uint4*
         // Past the last step the pointers park on one lane-uniform, always-valid address, so the
         // surplus requests of the padded loop cost a single cached line each.
         const uint16_t* park = reinterpret_cast<const uint16_t*>(a.gf);
+        const size_t wstep = w_step<W16>(ph);
+        size_t next = w_next<W16>(ph);
         auto set_unit = [&](int j) {
 #pragma unroll
-            for (int s = 0; s < NA; ++s) wp[s] = w_ptr(a, ph, j, s, w.ks0, lane);
+            for (int s = 0; s < NA; ++s) wp[s] = w_ptr<W16>(a, ph, j, s, w.ks0, lane);
         };
         auto advance = [&]() {              // scalar control only
             if (kn + 1 < w.nks) {
                 ++kn;
 #pragma unroll
-                for (int s = 0; s < NA; ++s) wp[s] += 128;
+                for (int s = 0; s < NA; ++s) wp[s] += wstep;
             } else if (jn + 1 < w.n_my) {
                 kn = 0; ++jn; set_unit(jn);
             } else {
 #pragma unroll
                 for (int s = 0; s < NA; ++s) wp[s] = park;
+                next = 32;
             }
         };
         auto request = [&](int slot) {      // weights of the next step, then advance
 #pragma unroll
-            for (int s = 0; s < NA; ++s) load_w(A[slot * NA + s], wp[s]);
+            for (int s = 0; s < NA; ++s) load_w<W16>(A[slot * NA + s], wp[s], next);
             advance();
         };
         set_unit(0);
@@ -477,7 +495,8 @@ __device__ inline void stream_chunk(const FusedArgs& a, Shared& sh, const uint4*
 #pragma unroll
                     for (int s = 0; s < NA; ++s) {
 #pragma unroll
-                        for (int c = 0; c < 4; ++c) bf16x8_to_f16x8(A[j * NA + s][c]);
+                        for (int c = 0; c < 4; ++c)
+                            if constexpr (!W16) bf16x8_to_f16x8(A[j * NA + s][c]);
 #pragma unroll
                         for (int c = 0; c < 4; ++c) acc[s] = mfma_16x16x32(A[j * NA + s][c], Bf[c], acc[s]);
                         if constexpr (SPLIT) {
@@ -512,7 +531,7 @@ __device__ inline void stream_chunk(const FusedArgs& a, Shared& sh, const uint4*
 // Streams a whole phase: for every chunk stage its activations, stream, and issue the next chunk's
 // first weights before the staging barrier. On return sh.red holds every unit's partial sums and
 // all waves have passed a workgroup barrier.
-template <int NA, bool SPLIT, bool TR, int DS, int PF1, bool OWN = true>
+template <bool W16, int NA, bool SPLIT, bool TR, int DS, int PF1, bool OWN = true>
 __device__ inline void stream_phase(const FusedArgs& a, Shared& sh, uint4* xs, const Phase& ph,
                                     const uint16_t* __restrict__ X, const uint8_t* __restrict__ Xlo, Ring& R,
                                     int trace_layer = -1, int trace_slot = 0) {
@@ -529,17 +548,17 @@ __device__ inline void stream_phase(const FusedArgs& a, Shared& sh, uint4* xs, c
         // relies on the issue order)
         __builtin_amdgcn_sched_barrier(0);
         if (c == 0) {
-            prime_steps<NA, PF1, DS - 1>(a, ph, c, R);
+            prime_steps<W16, NA, PF1, DS - 1>(a, ph, c, R);
             __builtin_amdgcn_sched_barrier(0);
             stage_wait<PrimeCount<NA, PF1, DS - 1>::value>();
         } else {
-            prime_steps<NA, 0, DS - 1>(a, ph, c, R);
+            prime_steps<W16, NA, 0, DS - 1>(a, ph, c, R);
             __builtin_amdgcn_sched_barrier(0);
             stage_wait<PrimeCount<NA, 0, DS - 1>::value>();
         }
         if constexpr (!OWN) __syncthreads();     // shared staging: every wave's pieces have landed
         if (c == 0) stamp_fine<TR>(a, trace_layer, trace_slot);
-        stream_chunk<NA, DS, SPLIT>(a, sh, xs, ph, w, c == 0, R);
+        stream_chunk<W16, NA, DS, SPLIT>(a, sh, xs, ph, w, c == 0, R);
     }
     __syncthreads();
     stamp_fine<TR>(a, trace_layer, trace_slot + 1);
@@ -1167,7 +1186,7 @@ __device__ inline void accept_phase_tree(const FusedArgs& a, Shared& sh, int chu
 }
 
 // ---- the kernel --------------------------------------------------------------------------------------
-template <int DH, bool TR, bool TREE>
+template <int DH, bool TR, bool TREE, bool W16>
 __global__ __launch_bounds__(FT) void verify_fused_kernel(FusedArgs a) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     Shared& sh = *reinterpret_cast<Shared*>(smem_raw);
@@ -1189,7 +1208,7 @@ __global__ __launch_bounds__(FT) void verify_fused_kernel(FusedArgs a) {
 
     Ring ring;
     uint4* xs = reinterpret_cast<uint4*>(smem_raw + XS_OFFSET);
-    const Phase p_head{a.wlm, PH_HEAD, a.d, 1};
+    const Phase p_head{a.wlm, PH_HEAD, a.d, a.V, 1};
 
     // ---- phase 0: embedding, x0, x0*g1[0], sum of squares ----
     {
@@ -1226,9 +1245,9 @@ __global__ __launch_bounds__(FT) void verify_fused_kernel(FusedArgs a) {
         // The barrier that ends the previous layer (or the embedding) opens the loop body, so that the
         // weights issued ahead during it are never carried around the loop's back edge.
         {
-            const Phase p_q{a.wqkv + (size_t)l * 3 * a.d * a.d, PH_QKV, a.d, 2};
+            const Phase p_q{a.wqkv + (size_t)l * 3 * a.d * a.d, PH_QKV, a.d, 3 * a.d, 2};
             stamp<TR>(a, ns);
-            if (!grid_sync(a, sh, epoch, [&] { prime_steps<1, 0, PF_QKV>(a, p_q, 0, ring); })) return;
+            if (!grid_sync(a, sh, epoch, [&] { prime_steps<W16, 1, 0, PF_QKV>(a, p_q, 0, ring); })) return;
             stamp<TR>(a, ns);
         }
         const float* x_in = a.xbuf + (size_t)(2 * l) * XS;           // after the previous layer
@@ -1245,17 +1264,17 @@ __global__ __launch_bounds__(FT) void verify_fused_kernel(FusedArgs a) {
         float* ss_out = a.ssbuf + (size_t)(2 * l + 2) * nwg * 16;
         const size_t lo = (size_t)l * XS;
 
-        const Phase p_qkv{a.wqkv + (size_t)l * 3 * a.d * a.d, PH_QKV, a.d, 2};
-        const Phase p_o{a.wo + (size_t)l * a.d * a.d, PH_O, a.d, 2};
-        const Phase p_gu{a.wgu + (size_t)l * 2 * a.F * a.d, PH_GU, a.d, 2};
-        const Phase p_dn{a.wdown + (size_t)l * a.d * a.F, PH_DOWN, a.F, 1};
+        const Phase p_qkv{a.wqkv + (size_t)l * 3 * a.d * a.d, PH_QKV, a.d, 3 * a.d, 2};
+        const Phase p_o{a.wo + (size_t)l * a.d * a.d, PH_O, a.d, a.d, 2};
+        const Phase p_gu{a.wgu + (size_t)l * 2 * a.F * a.d, PH_GU, a.d, 2 * a.F, 2};
+        const Phase p_dn{a.wdown + (size_t)l * a.d * a.F, PH_DOWN, a.F, a.d, 1};
         const int w = blockIdx.x;
 
         // ---- QKV + RoPE ----
         {
             float ssv[8];
             ss_issue(ss_in, ssv);
-            stream_phase<1, true, TR, DS_QKV, PF_QKV>(a, sh, xs, p_qkv, xg_in, xgl_in, ring, l, 0);
+            stream_phase<W16, 1, true, TR, DS_QKV, PF_QKV>(a, sh, xs, p_qkv, xg_in, xgl_in, ring, l, 0);
             ss_finish(a, sh, ssv);
             const int per = a.d / 32, pph = DH / 32, half = DH / 2;
             const int cnt = count_mine(a.d / 16, w, nwg);
@@ -1318,14 +1337,14 @@ __global__ __launch_bounds__(FT) void verify_fused_kernel(FusedArgs a) {
         // ---- attention ----
         attention_phase<DH, TR, TREE>(a, sh, l, pg_first);
         stamp<TR>(a, ns);
-        if (!grid_sync(a, sh, epoch, [&] { prime_steps<1, 0, PF_O>(a, p_o, 0, ring); })) return;
+        if (!grid_sync(a, sh, epoch, [&] { prime_steps<W16, 1, 0, PF_O>(a, p_o, 0, ring); })) return;
         stamp<TR>(a, ns);
 
         // ---- O projection + residual; publish x, x*g2, sum of squares ----
         {
             float ss = 0.f;
             const float* g2 = a.g2 + (size_t)l * a.d;
-            stream_phase<1, true, TR, DS_O, PF_O>(a, sh, xs, p_o, a.attn + lo, a.attnl + lo, ring, l, 3);
+            stream_phase<W16, 1, true, TR, DS_O, PF_O>(a, sh, xs, p_o, a.attn + lo, a.attnl + lo, ring, l, 3);
             reduce_epilogue<1>(a, sh, n_units(a, PH_O), [&](int u, int row, int f0, float (&v)[1][2]) {
                 const int item = w + u * nwg;
                 const size_t o = (size_t)row * a.d + item * 16 + f0;
@@ -1341,14 +1360,14 @@ __global__ __launch_bounds__(FT) void verify_fused_kernel(FusedArgs a) {
             publish_ss(sh, ss_mid + (size_t)blockIdx.x * 16, ss);
         }
         stamp<TR>(a, ns);
-        if (!grid_sync(a, sh, epoch, [&] { prime_steps<2, 0, PF_GU>(a, p_gu, 0, ring); })) return;
+        if (!grid_sync(a, sh, epoch, [&] { prime_steps<W16, 2, 0, PF_GU>(a, p_gu, 0, ring); })) return;
         stamp<TR>(a, ns);
 
         // ---- gate/up + SwiGLU ----
         {
             float ssv[8];
             ss_issue(ss_mid, ssv);
-            stream_phase<2, true, TR, DS_GU, PF_GU>(a, sh, xs, p_gu, xg_mid, xgl_mid, ring, l, 6);
+            stream_phase<W16, 2, true, TR, DS_GU, PF_GU>(a, sh, xs, p_gu, xg_mid, xgl_mid, ring, l, 6);
             ss_finish(a, sh, ssv);
             uint16_t* act = a.act + (size_t)l * 16 * a.F;
             reduce_epilogue<2>(a, sh, n_units(a, PH_GU), [&](int u, int row, int f0, float (&v)[2][2]) {
@@ -1364,7 +1383,7 @@ __global__ __launch_bounds__(FT) void verify_fused_kernel(FusedArgs a) {
             });
         }
         stamp<TR>(a, ns);
-        if (!grid_sync(a, sh, epoch, [&] { prime_steps<1, 0, PF_DOWN>(a, p_dn, 0, ring); })) return;
+        if (!grid_sync(a, sh, epoch, [&] { prime_steps<W16, 1, 0, PF_DOWN>(a, p_dn, 0, ring); })) return;
         stamp<TR>(a, ns);
 
         // ---- down projection + residual; publish x, x*gain(next norm), sum of squares ----
@@ -1372,7 +1391,7 @@ __global__ __launch_bounds__(FT) void verify_fused_kernel(FusedArgs a) {
             float ss = 0.f;
             const bool last = l + 1 == a.L;
             const float* gn = last ? a.gf : a.g1 + (size_t)(l + 1) * a.d;
-            stream_phase<1, false, TR, DS_DOWN, PF_DOWN>(a, sh, xs, p_dn, a.act + (size_t)l * 16 * a.F, nullptr, ring, l, 9);
+            stream_phase<W16, 1, false, TR, DS_DOWN, PF_DOWN>(a, sh, xs, p_dn, a.act + (size_t)l * 16 * a.F, nullptr, ring, l, 9);
             reduce_epilogue<1>(a, sh, n_units(a, PH_DOWN), [&](int u, int row, int f0, float (&v)[1][2]) {
                 const int item = w + u * nwg;
                 const size_t o = (size_t)row * a.d + item * 16 + f0;
@@ -1389,7 +1408,7 @@ __global__ __launch_bounds__(FT) void verify_fused_kernel(FusedArgs a) {
         }
     }
     stamp<TR>(a, ns);
-    if (!grid_sync(a, sh, epoch, [&] { prime_steps<1, 0, PF_HEAD>(a, p_head, 0, ring); })) return;
+    if (!grid_sync(a, sh, epoch, [&] { prime_steps<W16, 1, 0, PF_HEAD>(a, p_head, 0, ring); })) return;
     stamp<TR>(a, ns);
 
     // ---- output head + acceptance ----
@@ -1397,7 +1416,7 @@ __global__ __launch_bounds__(FT) void verify_fused_kernel(FusedArgs a) {
     {
         float ssv[8];
         ss_issue(a.ssbuf + (size_t)(2 * a.L) * nwg * 16, ssv);
-        stream_phase<1, false, TR, DS_HEAD, PF_HEAD, false>(a, sh, xs, p_head, a.xgbuf + (size_t)(2 * a.L) * XS, nullptr, ring);
+        stream_phase<W16, 1, false, TR, DS_HEAD, PF_HEAD, false>(a, sh, xs, p_head, a.xgbuf + (size_t)(2 * a.L) * XS, nullptr, ring);
         ss_finish(a, sh, ssv);
         if (a.topk <= 2) head_epilogue<2, TREE>(a, sh, xs, chunks);
         else head_epilogue<KTOP, TREE>(a, sh, xs, chunks);
@@ -1436,6 +1455,20 @@ struct FusedWS {
     long long* trace = nullptr;
     int trace_cap = 0;
 };
+
+// The instantiation for a head size; a token tree is never traced: its launches take the untraced one.
+static const void* fused_kernel(int dh, bool tr, bool tree, bool w16) {
+    auto pick = [&](auto dhc, auto wc) {
+        constexpr int DH = decltype(dhc)::value;
+        constexpr bool W = decltype(wc)::value;
+        return tree ? (const void*)verify_fused_kernel<DH, false, true, W>
+             : tr ? (const void*)verify_fused_kernel<DH, true, false, W> : (const void*)verify_fused_kernel<DH, false, false, W>;
+    };
+    using D64 = std::integral_constant<int, 64>;
+    using D128 = std::integral_constant<int, 128>;
+    return w16 ? (dh == 128 ? pick(D128{}, std::true_type{}) : pick(D64{}, std::true_type{}))
+               : (dh == 128 ? pick(D128{}, std::false_type{}) : pick(D64{}, std::false_type{}));
+}
 
 // context splits of a launch: a fixed AW * PPW pages (256 tokens) each, enough to cover the longest sequence
 static int fused_splits(int max_len_ub, int R) {
@@ -1503,9 +1536,8 @@ static int fused_prepare(Model* m, int B, hipStream_t stream, FusedWS** out) {
         ws->hp_topv = (float*)(b + o_tv); ws->hp_topi = (int32_t*)(b + o_ti); ws->hp_lx = (float*)(b + o_lx);
         ws->nwg = nwg; ws->bh_cap = bh_cap;
         const size_t lds = (size_t)g_lds_max;
-        const void* fns[6] = {(const void*)verify_fused_kernel<128, false, false>, (const void*)verify_fused_kernel<128, true, false>,
-                              (const void*)verify_fused_kernel<64, false, false>, (const void*)verify_fused_kernel<64, true, false>,
-                              (const void*)verify_fused_kernel<128, false, true>, (const void*)verify_fused_kernel<64, false, true>};
+        const void* fns[12];
+        for (int i = 0; i < 12; ++i) fns[i] = fused_kernel(i & 1 ? 128 : 64, i / 2 % 3 == 1, i / 2 % 3 == 2, i >= 6);
         for (const void* f : fns) LASER_HIP_CHECK(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     }
     if (m->fused_trace && !ws->trace) {
@@ -1533,7 +1565,9 @@ int run_fused(Model* m, KV* kv, const int32_t* ids_dev, const int32_t* pending, 
                   "context of %d tokens needs %d attention splits; the persistent kernel holds %d",
                   max_len_ub + R, B * d.n_heads * S, ws->bh_cap);      // fused_supported() has already ruled this out
     FusedArgs a{};
-    a.wqkv = d.wqkv; a.wo = d.wo; a.wgu = d.wgu; a.wdown = d.wdown; a.emb = d.emb; a.wlm = d.wlm;
+    const bool w16 = m->w16[0] && m->wlm16;
+    a.wqkv = w16 ? m->w16[0] : d.wqkv; a.wo = w16 ? m->w16[1] : d.wo; a.wgu = w16 ? m->w16[2] : d.wgu; a.wdown = w16 ? m->w16[3] : d.wdown;
+    a.emb = d.emb; a.wlm = w16 ? m->wlm16 : d.wlm;
     a.g1 = d.g1; a.g2 = d.g2; a.gf = d.gf;
     a.L = d.n_layers; a.d = d.d_model; a.H = d.n_heads; a.dh = m->dh; a.F = d.ffn; a.V = d.vocab; a.eps = d.eps;
     a.rope = m->rope;
@@ -1556,10 +1590,7 @@ int run_fused(Model* m, KV* kv, const int32_t* ids_dev, const int32_t* pending, 
     a.trace_cap = ws->trace_cap;
     void* args[] = {&a};
     const bool tr = a.trace != nullptr;
-    // (a token tree is never traced: its launches take the untraced instantiation)
-    const void* fn = parent ? (m->dh == 128 ? (const void*)verify_fused_kernel<128, false, true> : (const void*)verify_fused_kernel<64, false, true>)
-                   : m->dh == 128 ? (tr ? (const void*)verify_fused_kernel<128, true, false> : (const void*)verify_fused_kernel<128, false, false>)
-                                  : (tr ? (const void*)verify_fused_kernel<64, true, false> : (const void*)verify_fused_kernel<64, false, false>);
+    const void* fn = fused_kernel(m->dh, tr, parent != nullptr, w16);
     const bool prof = m->prof_on && m->prof_n < m->prof_cap;
     if (prof) LASER_HIP_CHECK(hipEventRecord(m->prof_ev[2 * m->prof_n], stream));
     LASER_HIP_CHECK(hipLaunchCooperativeKernel(fn, dim3(ws->nwg), dim3(FT), args, (size_t)g_lds_max, stream));

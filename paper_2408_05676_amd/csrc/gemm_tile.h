@@ -11,8 +11,8 @@ typedef unsigned u32x4a2 __attribute__((ext_vector_type(4), aligned(2)));
 typedef float float4a4_t __attribute__((ext_vector_type(4), aligned(4)));   // a caller's buffer may be aligned to its elements only
 
 struct GemmTileArgs {
-    const uint16_t* W;      // [N][Kd] bf16, or (WF16 kernels) the same values widened to fp16, one reduction step after the
-                            // other: [Kd / 64][N][64] (SwiGLU: 2F rows, gate rows then up rows; N = F)
+    const uint16_t* W;      // [N][Kd] bf16, or (WF16 kernels) the same values widened to fp16 and laid out by the 32 reduction
+                            // elements of a fragment: [Kd / 32][N][32] (SwiGLU: 2F rows, gate rows then up rows; N = F)
     const uint16_t* X;      // [M][Kd] fp16
     const uint16_t* Xlo;    // [M][Kd] low plane of split activations (x = X + Xlo / 4096), SPLIT kernels only
     int M, N, Kd;
@@ -76,10 +76,13 @@ void gemm_tile_kernel(GemmTileArgs a) {
     // Rows are unpadded; chunk c of row r sits at c ^ swz(r), so that the 16 rows a fragment read touches at one logical
     // chunk lie in 16 distinct 16-byte bank groups.
     auto swz = [](int row) { return (row / (16 / CH)) & (CH - 1); };
-    // Steps of a weight row are next to each other in a row-major matrix; in the widened copy a step's rows are, so that the
-    // workgroups, which walk the steps together, read one stretch of memory at a time: alone, 256 workgroups with 96 rows
-    // each read 5.0 TB/s of a row-major matrix in pieces of 128 bytes and 6.2 TB/s of the copy.
-    const uint32_t ldw = WF16 ? BK * 2 : ldb;
+    // Steps of a weight row are next to each other in a row-major matrix; in the widened copy the rows of half a step are, so
+    // that the workgroups, which walk the steps together, read one stretch of memory at a time: alone, 256 workgroups with 96
+    // rows each read 5.0 TB/s of a row-major matrix in pieces of 128 bytes and 6.2 TB/s of the copy. A piece of the copy is
+    // half a step of 16 rows, and a stage holds the halves one after the other, rows of 64 bytes.
+    constexpr int CW = WF16 ? BK / 16 : CH, RPW = 64 / CW;   // chunks per staged weight row, rows per weight piece
+    auto swzw = [](int row) { return (row / (16 / CW)) & (CW - 1); };
+    const uint32_t ldw = WF16 ? BK : ldb;
     const uint32_t wstep = WF16 ? (uint32_t)a.N * (EPI == GEPI_SWIGLU ? 2 : 1) * (BK * 2) : BK * 2;
     constexpr int WPW = BN / RPP / NW;                       // weight pieces per wave: load j of a wave is a weight piece iff j < WPW
     static_assert(WPW * RPP * NW == BN, "every wave's loads change from weights to rows at the same j");
@@ -91,17 +94,19 @@ void gemm_tile_kernel(GemmTileArgs a) {
     for (int j = 0; j < LPS; ++j) {
         int p = wave + j * NW;
         p = p < PIECES ? p : PIECES - 1;                     // surplus requests repeat the last piece (same bytes, same place)
-        const int row = p * RPP + lane / CH;
-        const int c = (lane % CH) ^ swz(row);                // the chunk that lives in this slot of the swizzled row
         if (j < WPW) {
+            const int half = WF16 ? p / (BN / 16) : 0, row = (WF16 ? p % (BN / 16) : p) * RPW + lane / CW;
+            const int c = (lane % CW) ^ swzw(row);            // the chunk that lives in this slot of the swizzled row
             // SwiGLU: the 16-row fragments alternate gate, up of the same 16 features
             int r0 = 0, r = row;
             if (EPI == GEPI_SWIGLU) { r0 = (row >> 5) * 16; r = row & 15; }
             const int left = a.N - 1 - tn * (EPI == GEPI_SWIGLU ? BN / 2 : BN);
             r = r0 + r < left ? r0 + r : left;               // (rows past the last repeat it)
             const uint32_t up = EPI == GEPI_SWIGLU && (row & 16) ? (uint32_t)a.N * ldw : 0;
-            voff[j] = up + (uint32_t)r * ldw + c * 16;
+            voff[j] = up + (uint32_t)r * ldw + c * 16 + half * (wstep / 2);
         } else {
+            const int row = p * RPP + lane / CH;
+            const int c = (lane % CH) ^ swz(row);
             const bool low = SPLIT && p * RPP >= BN + BM;
             int xr = row - BN - (low ? BM : 0);
             xr = tm * BM + xr < a.M ? xr : a.M - 1 - tm * BM;
@@ -152,7 +157,7 @@ void gemm_tile_kernel(GemmTileArgs a) {
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
         const uint32_t ch = (uint32_t)(((s * 4 + lg) ^ swz(lr)) * 16);
-        ow[s] = (uint32_t)(wn * WN * 16 + lr) * (BK * 2) + ch;
+        ow[s] = (uint32_t)(wn * WN * 16 + lr) * (CW * 16) + (WF16 ? s * BN * CW * 16 + ((lg ^ swzw(lr)) * 16) : ch);
         ox[s] = (uint32_t)(BN + wm * WM * 16 + lr) * (BK * 2) + ch;
     }
     // fragment r of substep s: the wave's weight fragments, then its activation fragments (high plane, low plane)
@@ -160,7 +165,7 @@ void gemm_tile_kernel(GemmTileArgs a) {
     auto read_frag = [&](auto sc, auto rc, int slot) {
         constexpr int s = decltype(sc)::value, r = decltype(rc)::value;
         if constexpr (r < WN) {
-            fw[s][r].v4 = *reinterpret_cast<const u32x4*>(lds + slot * SBYTES + ow[s] + r * 16 * BK * 2);
+            fw[s][r].v4 = *reinterpret_cast<const u32x4*>(lds + slot * SBYTES + ow[s] + r * 16 * CW * 16);
         } else {
             constexpr int i = SPLIT ? (r - WN) / 2 : r - WN;
             constexpr bool low = SPLIT && ((r - WN) & 1);

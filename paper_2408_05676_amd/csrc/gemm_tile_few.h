@@ -3,7 +3,7 @@
 //
 // What bounds it: the lines a compute unit has in flight. Alone, a compute unit loads 115 bytes per ns of rows that its L2
 // holds and 45 of weights from memory, and a mixture takes the sum of both times, however many loads are in flight and
-// whichever waves make them; beyond 170 compute units the weights' part is memory's 6.2 TB/s. A stage of 72 rows in two planes
+// whichever waves make them; beyond 195 compute units the weights' part is memory's 6.2 TB/s. A stage of 72 rows in two planes
 // is 20 KB beside 8, 12 or 16 KB of weights. Row-major weights stream 20 % slower (gemm_tile.h): with the copy, us inside a step
 // at 72 rows, 7B: gate/up 49.5 -> 45.1, QKV 30.5 -> 27.1, down 23.2 -> 20.3, O 12.9 -> 13.0; 24 rows: gate/up 42 -> 31.8;
 // 1B at 72 rows: gate/up 23.8 -> 21.9. Tried: weights touched ahead by scalar loads (2.7 bytes per ns), waves that load only

@@ -157,7 +157,7 @@ static void launch_rmsnorm(int M, hipStream_t stream, float* x, const float* gai
 
 struct GemmArgs {
     const uint16_t* W;      // [N][Kd]  (EPI_SWIGLU: [2N][Kd], gate rows then up rows)
-    const uint16_t* W16;    // the same matrix widened to fp16 and laid out by reduction steps (more than 16 rows), or NULL
+    const uint16_t* W16;    // the same matrix widened to fp16 and laid out by fragments (see widen_weights_kernel), or NULL
     const uint16_t* X;      // [M][Kd]
     const uint16_t* Xlo;    // [M][Kd] low plane of split activations, or NULL
     int M, N, Kd, S;
@@ -244,8 +244,8 @@ __global__ __launch_bounds__(256) void gemm_skinny_kernel(GemmArgs a) {
 
 constexpr int kSkinnyMaxRows = 80;   // beyond this the weights would be streamed more than once
 
-// bf16 -> fp16 copy of `mats` weight matrices [N][Kd], each laid out by reduction steps of 64: [Kd / 64][N][64]. A thread takes
-// 8 elements per iteration, eight threads a step of a row; the values whose magnitude fp16 cannot hold (they would become
+// bf16 -> fp16 copy of `mats` weight matrices [N][Kd], each laid out by the 32 reduction elements of a matrix instruction:
+// [Kd / 32][N][32], so that the 16 rows of a fragment are one kilobyte. A thread takes 8 elements per iteration; the values whose magnitude fp16 cannot hold (they would become
 // infinities) are counted.
 __global__ __launch_bounds__(256) void widen_weights_kernel(const uint16_t* __restrict__ src, uint16_t* __restrict__ dst, int N, int Kd, size_t n8,
                                                             int* __restrict__ overflow) {
@@ -261,7 +261,7 @@ __global__ __launch_bounds__(256) void widen_weights_kernel(const uint16_t* __re
         const uint32_t k = (uint32_t)(i - row * k8);
         const size_t mat = row / (uint32_t)N;
         const uint32_t n = (uint32_t)(row - mat * (uint32_t)N);
-        reinterpret_cast<uint4*>(dst)[mat * N * k8 + ((size_t)(k / 8) * N + n) * 8 + k % 8] = f.u;
+        reinterpret_cast<uint4*>(dst)[mat * N * k8 + ((size_t)(k / 4) * N + n) * 4 + k % 4] = f.u;
     }
     if (bad) atomicAdd(overflow, bad);
 }
@@ -712,6 +712,31 @@ __global__ void rope_table_kernel(float2* tab, int max_pos, int half, int dh, do
 }
 
 // ------------------------------------------------------------------------------------------------
+// fp16 copies of the four projection matrices, made once (same rounding as the kernels' own)
+static int widen_projections(Model* m, hipStream_t stream) {
+    const laser_model_desc& d = m->d;
+    const WidenSource src[4] = {{d.wqkv, d.n_layers, 3 * d.d_model, d.d_model}, {d.wo, d.n_layers, d.d_model, d.d_model},
+                                {d.wgu, d.n_layers, 2 * d.ffn, d.d_model}, {d.wdown, d.n_layers, d.d_model, d.ffn}};
+    return widen_copies(src, 4, m->w16, stream);
+}
+
+// The copies for steps of up to 80 rows, whose kernels take the caller's weights as well (10 % slower): made at the first one,
+// out of memory that is plainly spare; where they cannot be made (a weight beyond fp16) the steps do without. Nothing is
+// made while the stream is being captured.
+static void copies_for_few_rows(Model* m, hipStream_t stream) {
+    const laser_model_desc& d = m->d;
+    if (!m->f16_copies || m->no_few_copies || (m->w16[0] && m->wlm16)) return;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return;
+    const size_t dm = d.d_model, head = (size_t)d.vocab * dm * 2;
+    const size_t need = head + (m->w16[0] ? 0 : (size_t)d.n_layers * (4 * dm * dm + 3 * dm * d.ffn) * 2);
+    size_t free_b = 0, total_b = 0;
+    const WidenSource lm{d.wlm, 1, d.vocab, d.d_model};
+    m->no_few_copies = hipMemGetInfo(&free_b, &total_b) != hipSuccess || need > free_b / 4 ||
+                       (!m->w16[0] && widen_projections(m, stream) != LASER_OK) || (!m->wlm16 && widen_copies(&lm, 1, &m->wlm16, stream) != LASER_OK);
+    if (m->no_few_copies) (void)hipGetLastError();
+}
+
 // parent: NULL for a chain of drafts, else the token tree's parent array (see tree_parent_of)
 static int forward(Model* m, KV* kv, const int32_t* ids_dev, const int32_t* pending, const int32_t* drafts,
                    const int32_t* parent, const int32_t* draft_len, int B, int K, int max_len_ub, hipStream_t stream) {
@@ -721,23 +746,8 @@ static int forward(Model* m, KV* kv, const int32_t* ids_dev, const int32_t* pend
                        m->row_pos, m->row_slot, m->row_anc);
     hipLaunchKernelGGL(embed_rmsnorm_kernel, dim3(M), dim3(256), 0, stream, d.emb, d.g1, pending, drafts, draft_len,
                        R, dm, d.vocab, d.eps, m->x, m->xn, m->xn_lo);
-    if (M > 16 && m->f16_copies && !m->w16[0] && (M > kSkinnyMaxRows || !m->no_few_copies)) {
-        // first step with more than 16 rows: widen the four projection matrices to fp16 once (same rounding as the kernels' own)
-        const WidenSource src[4] = {{d.wqkv, d.n_layers, 3 * dm, dm}, {d.wo, d.n_layers, dm, dm}, {d.wgu, d.n_layers, 2 * F, dm}, {d.wdown, d.n_layers, dm, F}};
-        if (M > kSkinnyMaxRows) {
-            const int rc = widen_copies(src, 4, m->w16, stream);
-            if (rc) return rc;
-        } else {
-            // up to 80 rows the kernels take the caller's weights as well (10 % slower): copies only out of memory that is plainly
-            // spare, and none where they cannot be made (a weight beyond fp16, a stream being captured)
-            hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-            size_t free_b = 0, total_b = 0, need = 0;
-            for (const WidenSource& w : src) need += (size_t)w.mats * w.N * w.Kd * 2;
-            if (hipStreamIsCapturing(stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone) {
-                m->no_few_copies = hipMemGetInfo(&free_b, &total_b) != hipSuccess || need > free_b / 4 || widen_copies(src, 4, m->w16, stream) != LASER_OK;
-                if (m->no_few_copies) (void)hipGetLastError();
-            }
-        }
+    if (M > kSkinnyMaxRows && m->f16_copies && !m->w16[0]) {
+        if (const int rc = widen_projections(m, stream)) return rc;
     }
     if (M > 16 && !m->kpart) {
         // workspace for reduction-split partial results: up to 8 parts of [max_rows][d] or 2 of [max_rows][3 d], 4 up to 80 rows
@@ -956,7 +966,9 @@ static int verify_impl(laser_model* mh, laser_kv* kh, const int32_t* seq_ids, co
     }
     const int32_t* ids_dev = nullptr;
     if ((rc = kv->stage_ids(seq_ids, B, stream, &ids_dev))) return rc;
-    if (m->use_fused && fused_supported(m, B, K, max_ub)) {
+    const bool fused = m->use_fused && fused_supported(m, B, K, max_ub);
+    if (fused || (B * R > 16 && B * R <= kSkinnyMaxRows)) copies_for_few_rows(m, stream);
+    if (fused) {
         if (parent)          // token tree: positions (depth) and ancestor masks of the rows
             hipLaunchKernelGGL(rows_kernel, dim3((B * R + 255) / 256), dim3(256), 0, stream, parent, draft_len, ids_dev, kv->len, B, R,
                                m->row_pos, m->row_slot, m->row_anc);

@@ -87,11 +87,11 @@ struct Model {
     void* fused_ws = nullptr;          // workspace of the persistent few-row kernel (fused.hip)
     int use_fused = 1;                 // 0 forces the generic multi-kernel path
     int fused_trace = 0;               // 1: thread 0 of every workgroup stamps the wall clock at phase edges
-    uint16_t* w16[4] = {nullptr, nullptr, nullptr, nullptr};   // fp16 copies of wqkv, wo, wgu, wdown for the tiled many-row kernels,
-                                                               // laid out by reduction steps ([Kd / 64][N][64] per layer), made
-                                                               // at the first step with more than 16 rows
-    bool no_few_copies = false;        // they could not be made for a step of 17..80 rows, which do without
-    uint16_t* wlm16 = nullptr;         // fp16 copy of the head matrix, likewise, made at the first head call with more than 80 rows
+    uint16_t* w16[4] = {nullptr, nullptr, nullptr, nullptr};   // fp16 copies of wqkv, wo, wgu, wdown for the tiled and the persistent kernels,
+                                                               // laid out by fragments ([Kd / 32][N][32] per layer), made
+                                                               // at the first step that takes them
+    bool no_few_copies = false;        // they could not be made for a step of up to 80 rows, which does without
+    uint16_t* wlm16 = nullptr;         // fp16 copy of the head matrix, likewise
     int f16_copies = 1;                // 0: the tiled kernels stream the bf16 weights and widen them in the loop (no copies)
     float* kpart = nullptr;            // partial results of reduction-split tiled GEMMs (many-row path), [parts][rows][N]
     size_t kpart_floats = 0;

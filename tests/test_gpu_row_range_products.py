@@ -150,9 +150,10 @@ def test_tile_of_128_rows_and_192_columns(B, K):
 
 
 @pytest.mark.parametrize("d,heads,ffn", [(128, 2, 128), (640, 5, 1920)])
-@pytest.mark.parametrize("B,K", [(1, 16), (4, 7), (6, 7), (10, 7)])
-def test_copies_of_17_to_80_rows(d, heads, ffn, B, K):
-    """The fp16 copies hold the values that the kernels make of the bf16 weights: the same products, bit for bit."""
+@pytest.mark.parametrize("B,K", [(1, 0), (1, 8), (3, 4), (2, 7), (1, 16), (4, 7), (6, 7), (10, 7)])
+def test_copies_up_to_80_rows(d, heads, ffn, B, K):
+    """The fp16 copies hold the values that the kernels make of the bf16 weights: the same products, bit for bit (up to 16 rows
+    on the persistent kernel)."""
     sh = synth.SHAPES["tiny"].with_(d=d, n_heads=heads, ffn=ffn, vocab=512)
     out = []
     for copies in (1, 0):
