@@ -259,63 +259,95 @@ void gemm_tile_kernel(GemmTileArgs a) {
         if (chunk >= a.hp.chunks) return;
         const int n0 = tn * BN + wn * WN * 16 + 4 * lg;
         const int kt = a.hp.topk < KD ? a.hp.topk : KD;
+        const bool whole = tn * BN + (wn + 1) * WN * 16 <= a.N;
+        // The rows' first candidates, two round trips for all of them: fetched row by row they also waited for the stores of the
+        // row before. The rest is read by the few lanes that hold one of the tokens, or rows with several.
+        int x0[WM], several = 0;
+        {
+            int cb[WM], cn[WM];
+#pragma unroll
+            for (int i = 0; i < WM; ++i) {
+                const int row = tm * BM + (wm * WM + i) * 16 + lr, rowc = row < a.M ? row : a.M - 1;
+                cb[i] = a.hp.cand_beg[rowc];
+                cn[i] = row < a.M ? a.hp.cand_cnt[rowc] : 0;
+            }
+#pragma unroll
+            for (int i = 0; i < WM; ++i) {
+                const int x = a.hp.cand_x[cb[i]];                // (a row without candidates names a place that exists)
+                x0[i] = cn[i] > 0 ? x : -1;
+                several |= (cn[i] > 1 ? 1 : 0) << i;
+            }
+        }
         static_for<0, WM>([&](auto ic) {                     // (a loop this long is not unrolled by itself, and acc must not be indexed at run time)
             constexpr int i = decltype(ic)::value;
             const int row = tm * BM + (wm * WM + i) * 16 + lr;
             RowStatT<KD> st;
             st.init();
-            if (row < a.M) {
-                float v[WN * 4];
-                float mx = -INFINITY;
-                int arg = 0x7FFFFFFF;
+            float v[WN * 4];
+#pragma unroll
+            for (int j = 0; j < WN; ++j)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[j * 4 + e] = acc[i][j][e];
+            if (!whole) {
 #pragma unroll
                 for (int j = 0; j < WN; ++j)
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const int n = n0 + j * 16 + e;
-                        const float x = n < a.N ? acc[i][j][e] : -INFINITY;
-                        v[j * 4 + e] = x;
-                        arg = x > mx ? n : arg;                                  // ids ascend: earlier ties stay
-                        mx = fmaxf(mx, x);
-                    }
-                float sum = 0.f;
-                if (mx != -INFINITY) {
+                    for (int e = 0; e < 4; ++e) v[j * 4 + e] = n0 + j * 16 + e < a.N ? v[j * 4 + e] : -INFINITY;
+            }
+            // maximum, its id and the second largest value in one pass, four instructions an element
+            float mx = -INFINITY, second = -INFINITY;
+            int at = 0x7FFFFFFF - n0;                        // ids relative to n0
 #pragma unroll
-                    for (int j = 0; j < WN; ++j)
+            for (int q = 0; q < WN * 4; ++q) {
+                if constexpr (KD == 2) second = __builtin_amdgcn_fmed3f(v[q], mx, second);
+                at = v[q] > mx ? q / 4 * 16 + q % 4 : at;    // ids ascend: earlier ties stay
+                mx = fmaxf(mx, v[q]);
+            }
+            float sum = 0.f;
+            if (mx != -INFINITY) {
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) sum += __expf(v[j * 4 + e] - mx);
-                }
-                st.mx = mx; st.sum = sum; st.arg = arg;
+                for (int q = 0; q < WN * 4; ++q) sum += __expf(v[q] - mx);
+            }
+            st.mx = mx; st.sum = sum; st.arg = n0 + at;
+            bool plain = false;
+            if constexpr (KD == 2) plain = __ballot(!(second < mx && second > -INFINITY)) == 0;
+            if (plain) {
+                // two different finite values head the list of every lane: the second one's id is where it first stands
+                int at2 = 0;
+#pragma unroll
+                for (int q = WN * 4 - 1; q >= 0; --q) at2 = v[q] == second ? q / 4 * 16 + q % 4 : at2;
+                st.tv[0] = mx; st.ti[0] = n0 + at;
+                st.tv[KD - 1] = second; st.ti[KD - 1] = n0 + at2;
+            } else {
                 float thr_v = -INFINITY;
                 int thr_i = 0x7FFFFFFF;
 #pragma unroll
-                for (int j = 0; j < WN; ++j)
+                for (int q = 0; q < WN * 4; ++q) {
+                    const int n = n0 + q / 4 * 16 + q % 4;
+                    if (n < a.N && before(v[q], n, thr_v, thr_i)) {
+                        st.push_top(v[q], n);
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const int n = n0 + j * 16 + e;
-                        if (n < a.N && before(v[j * 4 + e], n, thr_v, thr_i)) {
-                            st.push_top(v[j * 4 + e], n);
-#pragma unroll
-                            for (int t = 0; t < KD; ++t) if (t == kt - 1) { thr_v = st.tv[t]; thr_i = st.ti[t]; }
-                        }
+                        for (int t = 0; t < KD; ++t) if (t == kt - 1) { thr_v = st.tv[t]; thr_i = st.ti[t]; }
                     }
+                }
+            }
+            auto mine = [&](int x) { const int o = x - n0; return o >= 0 && o < WN * 16 && (o & 15) < 4; };
+            if (x0[i] >= 0 && (mine(x0[i]) || ((several >> i) & 1))) {
                 const int cb = a.hp.cand_beg[row], cn = a.hp.cand_cnt[row];
                 for (int c = 0; c < cn; ++c) {
-                    const int x = a.hp.cand_x[cb + c], o = x - n0;
-                    if (o >= 0 && o < WN * 16 && (o & 15) < 4) {
+                    const int x = a.hp.cand_x[cb + c];
+                    if (mine(x)) {
 #pragma unroll
-                        for (int j = 0; j < WN; ++j)
-#pragma unroll
-                            for (int e = 0; e < 4; ++e)
-                                if (o == j * 16 + e) a.hp.cand_lx[cb + c] = v[j * 4 + e];
+                        for (int q = 0; q < WN * 4; ++q)
+                            if (x - n0 == q / 4 * 16 + q % 4) a.hp.cand_lx[cb + c] = v[q];
                     }
                 }
-                if (a.hp.logits_dbg) {
+            }
+            if (a.hp.logits_dbg && row < a.M) {
 #pragma unroll
-                    for (int j = 0; j < WN; ++j)
-                        if (n0 + j * 16 < a.N)                                   // N is a multiple of 16
-                            *reinterpret_cast<float4a4_t*>(a.hp.logits_dbg + (size_t)row * a.N + n0 + j * 16) = float4a4_t{v[j * 4], v[j * 4 + 1], v[j * 4 + 2], v[j * 4 + 3]};
-                }
+                for (int j = 0; j < WN; ++j)
+                    if (n0 + j * 16 < a.N)                                   // N is a multiple of 16
+                        *reinterpret_cast<float4a4_t*>(a.hp.logits_dbg + (size_t)row * a.N + n0 + j * 16) = float4a4_t{v[j * 4], v[j * 4 + 1], v[j * 4 + 2], v[j * 4 + 3]};
             }
             st.merge_from_lane(16);
             st.merge_from_lane(32);

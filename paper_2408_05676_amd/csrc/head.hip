@@ -7,8 +7,8 @@
 //   M <= 16   lm_head_kernel: every wavefront owns a contiguous chunk of the vocabulary, streams those rows of the
 //             head matrix once through the matrix cores against all verified rows and keeps the running statistics
 //             in registers (chunk = wavefront).
-//   M <= 80   the weight-streaming kernel of gemm_mid.h with its head epilogue (chunk = workgroup, 64 or 128
-//             vocabulary entries): the head matrix is read once.
+//   M <= 80   the tiled GEMM with one row tile (chunk = a wave's 32 columns), which reads the head matrix once; with operands off
+//             the 16-byte grid the kernel of gemm_mid.h with its head epilogue (chunk = workgroup, 64 or 128 vocabulary entries).
 //   more      the LDS-tiled matrix-core GEMM of gemm_tile.h with its head epilogue (chunk = a wave's 128 columns); rows off
 //             the 16-byte grid are copied onto it first (1024 rows at a 128 k vocabulary: 1205 us, on the grid 1198).
 // Pass 2: a wavefront per row merges the per-chunk partials. The draft's rank is the number of partial-list entries
@@ -165,12 +165,13 @@ __global__ __launch_bounds__(256) void accept_rows_kernel(AcceptArgs a) {
             for (int j = 0; j < kCandPass; ++j) any |= x[j] >= 0 && ca != x[j] && before(cm, ca, lx[j], x[j]);
             if (any)
 #pragma unroll
-                for (int t = 0; t < KT; ++t) {
-                    const float v = a.hp_topv[o * KT + t];
-                    const int i = a.hp_topi[o * KT + t];
+                for (int t = 0; t < KT; ++t)
+                    if (t < a.topk) {                            // (a record holds that many, possibly no more)
+                        const float v = a.hp_topv[o * KT + t];
+                        const int i = a.hp_topi[o * KT + t];
 #pragma unroll
-                    for (int j = 0; j < kCandPass; ++j) ahead[j] += (x[j] >= 0 && i != x[j] && before(v, i, lx[j], x[j])) ? 1 : 0;
-                }
+                        for (int j = 0; j < kCandPass; ++j) ahead[j] += (x[j] >= 0 && i != x[j] && before(v, i, lx[j], x[j])) ? 1 : 0;
+                    }
         }
         for (int off = 32; off > 0; off >>= 1) {
             const float omx = __shfl_xor(mx, off), osum = __shfl_xor(sum, off);
@@ -251,11 +252,15 @@ struct HeadBufs {
 static int head_chunks_for(const Model* m, int M) {
     if (M <= kHeadStreamMaxRows) return m->head_chunks;
     if (M <= kHeadMidMaxRows && m->d.d_model % kGemmKStep == 0)
-        return (m->d.vocab / 16 + 3) / 4;                          // at most: the 4-wave form has the most workgroups
+        return (m->d.vocab + 31) / 32;                             // at most: the tiled form's waves of 32 columns
     return (m->d.vocab + 127) / 128;
 }
-int head_chunks_cap(const Model* m) {
-    return std::max(m->head_chunks, std::max(head_chunks_for(m, kHeadMidMaxRows), head_chunks_for(m, kHeadMidMaxRows + 1)));
+// The records a call may need: the most over all row counts.
+size_t head_records(const Model* m) {
+    const size_t R = m->d.max_rows;
+    size_t n = R * (size_t)head_chunks_for(m, kHeadMidMaxRows + 1);
+    for (int M : {kHeadStreamMaxRows, kHeadMidMaxRows}) n = std::max(n, std::min<size_t>(R, M) * head_chunks_for(m, M));
+    return n;
 }
 
 // Rows off the 16-byte grid onto it, for loads into LDS; n8: groups of eight values.
@@ -280,6 +285,10 @@ static int run_head_bufs(Model* m, const uint16_t* h, const int32_t* tokens, con
         HeadArgs a{m->d.wlm, h, M, V, dm, tpw, hp};
         dim3 grid((unsigned)((m->head_chunks + 3) / 4), 1u);         // at most 16 rows: one row tile
         hipLaunchKernelGGL(lm_head_kernel<1>, grid, dim3(256), 0, stream, a);
+    } else if (M <= kHeadMidMaxRows && m->mid_waves == 0 && (m->wlm16 || on_16_byte_grid(m->d.wlm)) && on_16_byte_grid(h)) {
+        hp.chunks = (V + 31) / 32;
+        GemmTileArgs t{m->wlm16 ? m->wlm16 : m->d.wlm, h, nullptr, M, V, dm, 0, 0, 1, nullptr, nullptr, hp};
+        launch_few_head(t, m->wlm16 != nullptr, stream);
     } else if (M <= kHeadMidMaxRows && dm % kGemmKStep == 0) {
         const GemmMidPlan pl = gemm_mid_plan(M, V, dm, 1, false, 0);
         hp.chunks = (V / 16 + pl.NW - 1) / pl.NW;                     // = workgroups of the launch
@@ -315,6 +324,8 @@ static int run_head_bufs(Model* m, const uint16_t* h, const int32_t* tokens, con
 int run_head(Model* m, const uint16_t* h, const int32_t* tokens, const int32_t* parent, const int32_t* n_nodes, int B, int K,
              int topk, float p, int mode, int32_t* accept_len, int32_t* out_tokens, int32_t* accept_path, float* logits_dbg,
              hipStream_t stream) {
+    const int M = B * (K + 1);
+    if (M > kHeadStreamMaxRows && M <= kHeadMidMaxRows) copies_for_few_rows(m, false, stream);
     HeadBufs hb{m->cand_beg, m->cand_cnt, m->cand_x, m->node_cand, m->cand_lx, m->hp_max, m->hp_sum, m->hp_arg, m->hp_topv, m->hp_topi,
                 m->row_mx, m->row_sum, m->row_arg, m->cand_rank};
     return run_head_bufs(m, h, tokens, parent, n_nodes, B, K, topk, p, mode, accept_len, out_tokens, accept_path, logits_dbg, hb, stream);

@@ -54,7 +54,7 @@ __device__ inline void store_candidates(const HeadPart& hp, int row, int n0, int
 __device__ inline bool before(float v, int i, float w, int j) { return v > w || (v == w && i < j); }
 
 // KD: entries of the list the statistics keep, topk <= KD <= KT (a shorter list is all a call with a small k needs,
-// and costs a fraction of the full one to maintain); the stored record is padded to KT entries.
+// and costs a fraction of the full one to maintain and to store); the first topk entries of a stored record are read.
 template <int KD>
 struct RowStatT {
     static_assert(KD >= 1 && KD <= KT, "list depth");
@@ -104,10 +104,7 @@ struct RowStatT {
         const size_t o = (size_t)row * hp.chunks + chunk;
         hp.hp_max[o] = mx; hp.hp_sum[o] = sum; hp.hp_arg[o] = arg;
 #pragma unroll
-        for (int j = 0; j < KT; ++j) {
-            hp.hp_topv[o * KT + j] = j < KD ? tv[j < KD ? j : 0] : -INFINITY;
-            hp.hp_topi[o * KT + j] = j < KD ? ti[j < KD ? j : 0] : 0x7FFFFFFF;
-        }
+        for (int j = 0; j < KD; ++j) { hp.hp_topv[o * KT + j] = tv[j]; hp.hp_topi[o * KT + j] = ti[j]; }
     }
     // the same record in LDS for a merge across the waves of a workgroup
     static constexpr int kWords = 3 + 2 * KD;

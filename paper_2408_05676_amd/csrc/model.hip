@@ -23,7 +23,7 @@ int fused_read_trace(Model* m, hipStream_t stream, long long* out, int max_elems
 int run_head(Model* m, const uint16_t* h, const int32_t* tokens, const int32_t* parent, const int32_t* n_nodes, int B, int K,
              int topk, float p, int mode, int32_t* accept_len, int32_t* out_tokens, int32_t* accept_path, float* logits_dbg,
              hipStream_t stream);
-int head_chunks_cap(const Model* m);
+size_t head_records(const Model* m);
 int run_head_static(Model* m, const uint16_t* h, const int32_t* drafts, const int32_t* draft_len, int B, int K,
                     int topk, float p, int mode, int32_t* accept_len, int32_t* out_tokens, hipStream_t stream);
 
@@ -245,23 +245,24 @@ __global__ __launch_bounds__(256) void gemm_skinny_kernel(GemmArgs a) {
 constexpr int kSkinnyMaxRows = 80;   // beyond this the weights would be streamed more than once
 
 // bf16 -> fp16 copy of `mats` weight matrices [N][Kd], each laid out by the 32 reduction elements of a matrix instruction:
-// [Kd / 32][N][32], so that the 16 rows of a fragment are one kilobyte. A thread takes 8 elements per iteration; the values whose magnitude fp16 cannot hold (they would become
+// [Kd / 32][N][32], so that the 16 rows of a fragment are one kilobyte. A wave takes 128 elements of 4
+// rows per iteration, whole lines on both sides; the values whose magnitude fp16 cannot hold (they would become
 // infinities) are counted.
 __global__ __launch_bounds__(256) void widen_weights_kernel(const uint16_t* __restrict__ src, uint16_t* __restrict__ dst, int N, int Kd, size_t n8,
                                                             int* __restrict__ overflow) {
     int bad = 0;
-    const uint32_t k8 = (uint32_t)Kd / 8;
+    const uint32_t k128 = (uint32_t)Kd / 128;                // (Kd is a multiple of 128, N of 16)
     for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n8; i += (size_t)gridDim.x * 256) {
+        const size_t quad = (i >> 6) / k128, row = quad * 4 + ((i >> 4) & 3);
+        const uint32_t kb = (uint32_t)((i >> 6) - quad * k128), c = (uint32_t)i & 15;
         Frag8 f;
-        f.u = reinterpret_cast<const uint4*>(src)[i];
+        f.u = reinterpret_cast<const uint4*>(src)[(row * k128 + kb) * 16 + c];
 #pragma unroll
         for (int j = 0; j < 8; ++j) bad += (f.h[j] & 0x7FFFu) > 0x477Fu ? 1 : 0;     // |w| > 65280 (bf16 pattern), inf and NaN included
         bf16x8_to_f16x8(f);
-        const size_t row = i / k8;
-        const uint32_t k = (uint32_t)(i - row * k8);
         const size_t mat = row / (uint32_t)N;
         const uint32_t n = (uint32_t)(row - mat * (uint32_t)N);
-        reinterpret_cast<uint4*>(dst)[mat * N * k8 + ((size_t)(k / 4) * N + n) * 4 + k % 4] = f.u;
+        reinterpret_cast<uint4*>(dst)[(mat * k128 * 4 * N + (size_t)(kb * 4 + c / 4) * N + n) * 4 + c % 4] = f.u;
     }
     if (bad) atomicAdd(overflow, bad);
 }
@@ -723,17 +724,17 @@ static int widen_projections(Model* m, hipStream_t stream) {
 // The copies for steps of up to 80 rows, whose kernels take the caller's weights as well (10 % slower): made at the first one,
 // out of memory that is plainly spare; where they cannot be made (a weight beyond fp16) the steps do without. Nothing is
 // made while the stream is being captured.
-static void copies_for_few_rows(Model* m, hipStream_t stream) {
+void copies_for_few_rows(Model* m, bool projections, hipStream_t stream) {
     const laser_model_desc& d = m->d;
-    if (!m->f16_copies || m->no_few_copies || (m->w16[0] && m->wlm16)) return;
+    projections = projections && !m->w16[0];
+    if (!m->f16_copies || m->no_few_copies || (!projections && m->wlm16)) return;
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return;
-    const size_t dm = d.d_model, head = (size_t)d.vocab * dm * 2;
-    const size_t need = head + (m->w16[0] ? 0 : (size_t)d.n_layers * (4 * dm * dm + 3 * dm * d.ffn) * 2);
+    const size_t dm = d.d_model, need = (m->wlm16 ? 0 : (size_t)d.vocab * dm * 2) + (projections ? (size_t)d.n_layers * (4 * dm * dm + 3 * dm * d.ffn) * 2 : 0);
     size_t free_b = 0, total_b = 0;
     const WidenSource lm{d.wlm, 1, d.vocab, d.d_model};
     m->no_few_copies = hipMemGetInfo(&free_b, &total_b) != hipSuccess || need > free_b / 4 ||
-                       (!m->w16[0] && widen_projections(m, stream) != LASER_OK) || (!m->wlm16 && widen_copies(&lm, 1, &m->wlm16, stream) != LASER_OK);
+                       (projections && widen_projections(m, stream) != LASER_OK) || (!m->wlm16 && widen_copies(&lm, 1, &m->wlm16, stream) != LASER_OK);
     if (m->no_few_copies) (void)hipGetLastError();
 }
 
@@ -907,7 +908,7 @@ extern "C" int laser_model_create(const laser_model_desc* desc, void* stream_, l
         const int ntiles = d.vocab / 16;
         const int tpw = (ntiles + 1023) / 1024;
         m->head_chunks = (ntiles + tpw - 1) / tpw;
-        const size_t n = R * (size_t)head_chunks_cap(m);      // the most records per row any row count produces
+        const size_t n = head_records(m);
         M_TRY(hipMalloc((void**)&m->hp_max, n * 4));
         M_TRY(hipMalloc((void**)&m->hp_sum, n * 4));
         M_TRY(hipMalloc((void**)&m->hp_arg, n * 4));
@@ -967,7 +968,7 @@ static int verify_impl(laser_model* mh, laser_kv* kh, const int32_t* seq_ids, co
     const int32_t* ids_dev = nullptr;
     if ((rc = kv->stage_ids(seq_ids, B, stream, &ids_dev))) return rc;
     const bool fused = m->use_fused && fused_supported(m, B, K, max_ub);
-    if (fused || (B * R > 16 && B * R <= kSkinnyMaxRows)) copies_for_few_rows(m, stream);
+    if (fused || (B * R > 16 && B * R <= kSkinnyMaxRows)) copies_for_few_rows(m, true, stream);
     if (fused) {
         if (parent)          // token tree: positions (depth) and ancestor masks of the rows
             hipLaunchKernelGGL(rows_kernel, dim3((B * R + 255) / 256), dim3(256), 0, stream, parent, draft_len, ids_dev, kv->len, B, R,

@@ -179,3 +179,77 @@ def test_a_weight_beyond_fp16_takes_no_copies():
     model.set_option("f16_copies", 1)
     with pytest.raises(laser.LaserError, match="fp16 range"):
         _step(model, sh, 12, 7)
+
+
+def _head_case(d, V, B, K, topk, seed):
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    w = torch.empty((V, d), dtype=torch.bfloat16, device="cuda").normal_(0.0, 0.1, generator=gen)
+    h = torch.empty((B, K + 1, d), dtype=torch.float16, device="cuda").normal_(generator=gen)
+    return w, h
+
+
+@pytest.mark.parametrize("topk", [1, 2, 5])
+@pytest.mark.parametrize("copies", [1, 0])
+@pytest.mark.parametrize("B,K", [(1, 16), (4, 7), (3, 10), (6, 7), (9, 7), (8, 9)])
+def test_head_of_17_to_80_rows(B, K, topk, copies):
+    """Logits against a float64 product; drafts of rank topk - 1 pass, the one of rank topk does not."""
+    import paper_2408_05676_amd as laser
+    d, V = 256, 1040
+    w, h = _head_case(d, V, B, K, topk, B)
+    want = h.double().flatten(0, 1) @ w.double().t()
+    by_rank = want.view(B, K + 1, V)[:, :K].topk(topk + 1, dim=-1).indices.to(torch.int32)
+    drafts = by_rank[..., topk - 1].contiguous()
+    drafts[:, K // 2] = by_rank[:, K // 2, topk]
+    n = torch.full((B,), K, dtype=torch.int32, device="cuda")
+    model = laser.Model(0, d, 2, 128, V, {"wlm": w}, B * (K + 1), B, 0)
+    model.set_option("f16_copies", copies)
+    acc, out, logits = laser.verify_head(model, h, drafts, n, topk, -1.0, 2, want_logits=True)
+    # products of fp16 and bf16 are exact in float32, 256 of them are added in float32
+    assert float((logits.double().flatten(0, 1) - want).norm() / want.norm()) <= 1e-5
+    assert (acc == K // 2).all()
+    assert torch.equal(out[:, K // 2], want.view(B, K + 1, V)[:, K // 2].argmax(-1).to(torch.int32))
+
+
+@pytest.mark.parametrize("B,K", [(8, 8), (9, 10), (30, 12)])
+@pytest.mark.parametrize("topk", [1, 2, 3])
+def test_head_ties(B, K, topk):
+    """Every logit stands twice in a lane, twice in a chunk and in another chunk: the smaller id is ahead. A row of zeros ties all."""
+    import paper_2408_05676_amd as laser
+    d, V = 256, 1024
+    w, h = _head_case(d, V, B, K, topk, 3)
+    w = w[:128].repeat_interleave(2, 0).repeat(4, 1).contiguous()                # ids 2 i, 2 i + 1, and the same 256 further on
+    h[:, K] = 0                                                                  # (the last row is only read for its arg-max)
+    top = (h[:, :K].double() @ w[:256:2].double().t()).argmax(-1) * 2
+    order = torch.stack([top, top + 1, top + 256, top + 257], -1).to(torch.int32)
+    n = torch.full((B,), K, dtype=torch.int32, device="cuda")
+    model = laser.Model(0, d, 2, 128, V, {"wlm": w}, B * (K + 1), B, 0)
+    acc, out = laser.verify_head(model, h, order[..., topk - 1].contiguous(), n, topk, -1.0, 2)[:2]
+    assert (acc == K).all() and (out[:, K] == 0).all()
+    acc, out = laser.verify_head(model, h, order[..., topk].contiguous(), n, topk, -1.0, 2)[:2]
+    assert (acc == 0).all() and torch.equal(out[:, 0], order[:, 0, 0])
+
+
+@pytest.mark.parametrize("topk", [1, 2, 5])
+def test_head_infinities(topk):
+    """Infinite and undefined logits: as the kernel for operands off the grid, whose epilogue is another one, takes them."""
+    import paper_2408_05676_amd as laser
+    d, V, B, K = 256, 1040, 9, 10
+    w, h = _head_case(d, V, B, K, topk, 5)
+    h[1, 0, 3] = float("inf")
+    h[2, 0] = float("nan")
+    h[3, 0, 5], h[3, 0, 6] = float("inf"), float("-inf")
+    w[:, 7] = -0.25
+    h[4, 0, 7] = float("inf")                                                   # every logit is -inf
+    h[5, 1] = 0
+    flat = torch.empty(w.numel() + 8, dtype=w.dtype, device="cuda")
+    flat[1:1 + w.numel()] = w.flatten()
+    drafts = torch.randint(0, V, (B, K), device="cuda", dtype=torch.int32)
+    drafts[:, 0] = torch.arange(B, device="cuda", dtype=torch.int32)
+    n = torch.full((B,), K, dtype=torch.int32, device="cuda")
+    got = []
+    for wlm, copies in ((w, 1), (flat[1:1 + w.numel()].view(w.shape), 0)):
+        model = laser.Model(0, d, 2, 128, V, {"wlm": wlm}, B * (K + 1), B, 0)
+        model.set_option("f16_copies", copies)
+        got.append(laser.verify_head(model, h, drafts, n, topk, 0.01, 2, want_logits=True))
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+    assert torch.allclose(got[0][2], got[1][2], rtol=1e-4, atol=1e-4, equal_nan=True)
