@@ -21,7 +21,7 @@ namespace {
 
 struct FewShape { int wn, nwn; };                       // 16-column fragments per wave, waves
 constexpr FewShape kFewF32[] = {{2, 3}, {2, 4}, {1, 4}};
-constexpr FewShape kFewSwiglu[] = {{2, 3}, {2, 4}};     // gate and up fragments come in pairs
+constexpr FewShape kFewSwiglu[] = {{2, 3}, {2, 4}, {2, 2}};     // gate and up fragments come in pairs
 
 constexpr int few_stages(int wm, FewShape s, bool split) {
     int ns = s.wn == 1 ? 5 : split && s.nwn == 4 ? 3 : 4;
