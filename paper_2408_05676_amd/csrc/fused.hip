@@ -66,11 +66,12 @@ struct FusedArgs {
     uint8_t* xglbuf;    // [2L+1][16][d]   8-bit low plane: x * gain = xgbuf + xglbuf / 4096 (split operands, see mfma.h)
     float* ssbuf;       // [2L+1][nwg][16]
     uint16_t *qbuf, *knew, *attn;          // [L][16][d]
-    uint16_t* vnew;     // [L][16][H][dh][16]  new values in the cache's page layout (channel-major): entry
+    uint16_t* vnew;     // [L][16][H][dh * 16] new values in the cache's page layout (page_v): entry
                         // (b * npp + i) holds the new rows of sequence b that fall into its i-th page from len / 16
                         // on (npp = 1 if R == 1, else 2; B * npp <= 16 because B * R <= 16)
     uint16_t* qlbuf;                       // [L][16][d]      fp16 low plane of the queries
-    uint8_t *knewl, *attnl;                // [L][16][d]      8-bit low planes of the new keys and of the attention output
+    uint8_t *knewl, *attnl;                // [L][16][d]      8-bit low planes of the new keys (a row's channels in the order
+                                           // of a token in a page, page_kl) and of the attention output
     uint16_t* act;      // [L][16][F]
     float* apart;       // [L][B*H][nsplit][32 + 16*dh]
     int* acount;        // [L][B*H]   (self-resetting)
@@ -103,6 +104,8 @@ __device__ inline void st_i32(int* p, int v) { st_u32(p, (uint32_t)v); }
 __device__ inline void st_u16(void* p, uint16_t v) {
     __hip_atomic_store(reinterpret_cast<uint16_t*>(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+// place of channel c of a row in knewl
+__device__ inline int kl_off(int c) { return (c & ~63) + page_kl(0, c & 63); }
 __device__ inline uint32_t pack_h2(float a, float b) { return (uint32_t)f32_to_f16(a) | ((uint32_t)f32_to_f16(b) << 16); }
 
 constexpr int MAX_UNITS = 6;         // 16-row weight tiles one wave slot can accumulate per phase
@@ -693,8 +696,8 @@ __device__ inline void attention_phase(const FusedArgs& a, Shared& sh, int layer
                 const size_t qo = (size_t)(b * a.R + min(r, a.R - 1)) * a.d + (size_t)h * DH + g * 8;
                 const uint16_t *qp = qb + qo, *qlp = qlb + qo;
                 Frag8 ak[PPW][NC32];
-                uint2 akl[PPW][NC32];               // 8-bit low plane of the keys, widened right before use
-                Frag4 bv[PPW][NC16], nv[PPW][NC16];
+                u32x4 akl[PPW][NC32 / 2];           // 8-bit low plane of the keys, widened right before use
+                Frag8 bv[PPW][NC32], nv[PPW][NC32]; // values of two 16-channel fragments each
                 const int npp = a.R == 1 ? 1 : 2, pg0 = len / kPageSize;
                 // A key slot at or past len is a NEW row: its lane reads the exchange buffer instead of the cache
                 // page (pointer select, same registers). New values come from the page-shaped exchange buffer
@@ -702,6 +705,7 @@ __device__ inline void attention_phase(const FusedArgs& a, Shared& sh, int layer
                 const uint16_t *kp[PPW], *vp[PPW], *nvp[PPW];
                 const uint8_t* klp[PPW];
                 size_t pbase_off[PPW];
+                int kst[PPW], klst[PPW];            // from one load to the next: the exchange buffer holds a row's channels in a row
                 bool p_new[PPW];
 #pragma unroll
                 for (int pp = 0; pp < PPW; ++pp) {
@@ -711,12 +715,14 @@ __device__ inline void attention_phase(const FusedArgs& a, Shared& sh, int layer
                     pbase_off[pp] = base;
                     const int ks = p * kPageSize + r;                   // this lane's key slot
                     const size_t ko = (size_t)(b * a.R + min(max(ks - len, 0), a.R - 1)) * a.d + (size_t)h * DH + g * 8;
-                    kp[pp] = ks >= len ? kn + ko : a.kpages + base + (size_t)r * DH + g * 8;
-                    klp[pp] = ks >= len ? knl + ko : a.klpages + base + (size_t)r * DH + g * 8;
-                    vp[pp] = a.vpages + base + (size_t)r * kPageSize + 4 * g;
+                    kp[pp] = ks >= len ? kn + ko : a.kpages + base + page_k(r, 8 * g);
+                    klp[pp] = ks >= len ? knl + ko + g * 8 : a.klpages + base + page_kl(r, 8 * g);
+                    kst[pp] = ks >= len ? 32 : 512;
+                    klst[pp] = ks >= len ? 64 : 1024;
+                    vp[pp] = a.vpages + base + page_v(4 * g, r);
                     // pages without new rows read one shared line instead (the loads stay unconditional)
                     const int pi = min(max(p - pg0, 0), npp - 1);
-                    nvp[pp] = p >= pg0 ? vn + ((size_t)(b * npp + pi) * a.H + h) * kPageSize * DH + (size_t)r * kPageSize + 4 * g : vn;
+                    nvp[pp] = p >= pg0 ? vn + ((size_t)(b * npp + pi) * a.H + h) * kPageSize * DH + page_v(4 * g, r) : vn;
                 }
                 __builtin_amdgcn_sched_barrier(0);
                 unsigned anc = 0;
@@ -728,13 +734,13 @@ __device__ inline void attention_phase(const FusedArgs& a, Shared& sh, int layer
 #pragma unroll
                 for (int pp = 0; pp < PPW; ++pp) {
 #pragma unroll
-                    for (int c = 0; c < NC32; ++c) ak[pp][c].u = *reinterpret_cast<const uint4*>(kp[pp] + c * 32);
+                    for (int c = 0; c < NC32; ++c) ak[pp][c].v4 = *reinterpret_cast<const u32x4*>(kp[pp] + c * kst[pp]);
 #pragma unroll
-                    for (int c = 0; c < NC32; ++c) akl[pp][c] = *reinterpret_cast<const uint2*>(klp[pp] + c * 32);
+                    for (int c = 0; c < NC32 / 2; ++c) akl[pp][c] = *reinterpret_cast<const u32x4*>(klp[pp] + c * klst[pp]);
 #pragma unroll
-                    for (int c = 0; c < NC16; ++c) bv[pp][c].u = *reinterpret_cast<const uint2*>(vp[pp] + (size_t)c * 16 * kPageSize);
+                    for (int c = 0; c < NC32; ++c) bv[pp][c].v4 = *reinterpret_cast<const u32x4*>(vp[pp] + c * 512);
 #pragma unroll
-                    for (int c = 0; c < NC16; ++c) nv[pp][c].u = *reinterpret_cast<const uint2*>(nvp[pp] + (p_new[pp] ? (size_t)c * 16 * kPageSize : 0));
+                    for (int c = 0; c < NC32; ++c) nv[pp][c].v4 = *reinterpret_cast<const u32x4*>(nvp[pp] + (p_new[pp] ? c * 512 : 0));
                 }
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -743,20 +749,20 @@ __device__ inline void attention_phase(const FusedArgs& a, Shared& sh, int layer
                     if (p >= n_pages) continue;
                     // new rows' values replace the cache's (unconditional selects: nothing here may be sunk into a branch)
 #pragma unroll
-                    for (int j = 0; j < 4; ++j)
+                    for (int j = 0; j < 8; ++j)
 #pragma unroll
-                        for (int c = 0; c < NC16; ++c) bv[pp][c].h[j] = (s0 + 4 * g + j >= len) ? nv[pp][c].h[j] : bv[pp][c].h[j];
+                        for (int c = 0; c < NC32; ++c) bv[pp][c].h[j] = (s0 + 4 * g + j % 4 >= len) ? nv[pp][c].h[j] : bv[pp][c].h[j];
                     if (s0 + kPageSize > len) {                         // the page holds new rows
                         const size_t base = pbase_off[pp];
                         const int ks = s0 + r;
                         // this wave owns the page: store its new rows into the cache for later steps
                         if (ks >= len && ks < len + a.R) {
-                            uint16_t* kd = a.kpages + base + (size_t)r * DH + g * 8;
-                            uint8_t* kld = a.klpages + base + (size_t)r * DH + g * 8;
+                            uint16_t* kd = a.kpages + base + page_k(r, 8 * g);
+                            uint8_t* kld = a.klpages + base + page_kl(r, 8 * g);
 #pragma unroll
-                            for (int c = 0; c < NC32; ++c) *reinterpret_cast<uint4*>(kd + c * 32) = ak[pp][c].u;
+                            for (int c = 0; c < NC32; ++c) *reinterpret_cast<u32x4*>(kd + c * 512) = ak[pp][c].v4;
 #pragma unroll
-                            for (int c = 0; c < NC32; ++c) *reinterpret_cast<uint2*>(kld + c * 32) = akl[pp][c];
+                            for (int c = 0; c < NC32 / 2; ++c) *reinterpret_cast<u32x4*>(kld + c * 1024) = akl[pp][c];
                         }
 #pragma unroll
                         for (int j = 0; j < 4; ++j) {
@@ -764,7 +770,7 @@ __device__ inline void attention_phase(const FusedArgs& a, Shared& sh, int layer
                             if (vs >= len && vs < len + a.R) {
 #pragma unroll
                                 for (int c = 0; c < NC16; ++c)
-                                    a.vpages[base + (size_t)(c * 16 + r) * kPageSize + 4 * g + j] = bv[pp][c].h[j];
+                                    a.vpages[base + page_v(4 * g + j, c * 16 + r)] = bv[pp][c / 2].h[c % 2 * 4 + j];
                             }
                         }
                     }
@@ -777,7 +783,7 @@ __device__ inline void attention_phase(const FusedArgs& a, Shared& sh, int layer
 #pragma unroll
                     for (int c = 0; c < NC32; ++c) {
                         Frag8 kl;
-                        b8x8_to_f16x8(akl[pp][c].x, akl[pp][c].y, kl);
+                        b8x8_to_f16x8(akl[pp][c / 2][c % 2 * 2], akl[pp][c / 2][c % 2 * 2 + 1], kl);
                         sl = mfma_16x16x32(kl, bq[c], sl);
                     }
 #pragma unroll
@@ -816,7 +822,9 @@ __device__ inline void attention_phase(const FusedArgs& a, Shared& sh, int layer
                     for (int c = 0; c < NC16; ++c) {
 #pragma unroll
                         for (int i = 0; i < 4; ++i) acc[c][i] *= al[i];
-                        acc[c] = mfma_16x16x16(pa, bv[pp][c], acc[c]);
+                        Frag4 v;
+                        v.v2 = u32x2{bv[pp][c / 2].w[c % 2 * 2], bv[pp][c / 2].w[c % 2 * 2 + 1]};
+                        acc[c] = mfma_16x16x16(pa, v, acc[c]);
                     }
                 }
             }
@@ -1308,9 +1316,9 @@ __global__ __launch_bounds__(FT) void verify_fused_kernel(FusedArgs a) {
                         st_u32(a.qbuf + ro + c0 + half, hi); st_u32(a.qlbuf + ro + c0 + half, lw);
                     } else {
                         split_pack_h2_b8(o0[0], o0[1], hi, l8);
-                        st_u32(a.knew + ro + c0, hi); st_u16(a.knewl + ro + c0, l8);
+                        st_u32(a.knew + ro + c0, hi); st_u16(a.knewl + ro + kl_off(c0), l8);
                         split_pack_h2_b8(o1[0], o1[1], hi, l8);
-                        st_u32(a.knew + ro + c0 + half, hi); st_u16(a.knewl + ro + c0 + half, l8);
+                        st_u32(a.knew + ro + c0 + half, hi); st_u16(a.knewl + ro + kl_off(c0 + half), l8);
                     }
                 } else {
                     const int idx = w + (u - 2 * cnt) * nwg;
@@ -1319,10 +1327,10 @@ __global__ __launch_bounds__(FT) void verify_fused_kernel(FusedArgs a) {
                     const int pos = TREE ? sh.seq_len[bb] + row - bb * a.R : sh.row_pos[row];        // cache slot (row order), not the rotary position
                     const int pi = row < a.M ? pos / kPageSize - sh.seq_len[bb] / kPageSize : 0;
                     const int ch = idx * 16 + f0;                          // channel (head * dh + c) of v[0][0]
-                    uint16_t* dst = a.vnew + lo * kPageSize + ((size_t)(bb * npp + pi) * a.d + ch) * kPageSize + pos % kPageSize;
+                    uint16_t* dst = a.vnew + lo * kPageSize + ((size_t)(bb * npp + pi) * a.d + ch / DH * DH) * kPageSize + page_v(pos % kPageSize, ch % DH);
                     if (row < a.M) {                                       // padding rows have no slot
                         st_u16(dst, f32_to_f16(v[0][0] * rs));
-                        st_u16(dst + kPageSize, f32_to_f16(v[0][1] * rs));
+                        st_u16(dst + 32, f32_to_f16(v[0][1] * rs));        // channel ch + 1 (f0 is even)
                     }
                 }
             });

@@ -63,9 +63,9 @@ __global__ void kv_compact_kernel(uint16_t* kpages, uint8_t* klpages, uint16_t* 
         const size_t sb = (((size_t)l * n_pages + bt[src / kPageSize]) * H + h) * kPageSize * dh;
         const size_t db = (((size_t)l * n_pages + bt[dst / kPageSize]) * H + h) * kPageSize * dh;
         const int st = src % kPageSize, dt = dst % kPageSize;
-        kpages[db + (size_t)dt * dh + c] = kpages[sb + (size_t)st * dh + c];
-        klpages[db + (size_t)dt * dh + c] = klpages[sb + (size_t)st * dh + c];
-        vpages[db + (size_t)c * kPageSize + dt] = vpages[sb + (size_t)c * kPageSize + st];
+        kpages[db + page_k(dt, c)] = kpages[sb + page_k(st, c)];
+        klpages[db + page_kl(dt, c)] = klpages[sb + page_kl(st, c)];
+        vpages[db + page_v(dt, c)] = vpages[sb + page_v(st, c)];
     }
 }
 
@@ -99,9 +99,9 @@ __global__ void kv_import_kernel(uint16_t* kpages, uint8_t* klpages, uint16_t* v
     const int t = (int)(i / ((size_t)dh * H));
     const int pg = block_row[t / kPageSize], tp = t % kPageSize;
     const size_t base = (((size_t)layer * n_pages + pg) * H + h) * kPageSize * dh;
-    kpages[base + (size_t)tp * dh + c] = k[i];
-    klpages[base + (size_t)tp * dh + c] = 0;          // imported keys are plain fp16
-    vpages[base + (size_t)c * kPageSize + tp] = v[i];
+    kpages[base + page_k(tp, c)] = k[i];
+    klpages[base + page_kl(tp, c)] = 0;               // imported keys are plain fp16
+    vpages[base + page_v(tp, c)] = v[i];
 }
 
 }  // namespace laser

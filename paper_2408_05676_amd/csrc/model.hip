@@ -390,11 +390,11 @@ __device__ inline float4 ld4_sum(const float* p, size_t stride) {
     return t;
 }
 
-// Values. The cache keeps them channel-major ([dh][16 tokens] per page and head), so one row's values are 2-byte
-// pieces 32 bytes apart: written row by row they cost a partial-sector write each (2.9 M of them at 704 rows).
-// Instead a thread owns one (sequence, head, channel): it reads that channel's 32-byte page row, replaces the
-// slots of the sequence's R new tokens and writes the row back, so all loads and stores are whole 16-byte pieces
-// and a wave covers 2 KiB of contiguous page memory.
+// Values. One row's values are 2-byte pieces 16 or more bytes apart in a page (state.h): written row by row they cost a
+// partial-sector write each (2.9 M of them at 704 rows). Instead a thread collects the sixteen tokens of one channel c,
+// exchanges eight of them with the thread of channel c ^ 16 and then owns 32 bytes of the page, eight tokens of both channels: it
+// reads them, replaces the slots of the sequence's R new tokens and writes them back, so that all page loads and stores
+// are whole 16-byte pieces and a wave covers 2 KiB of contiguous page memory.
 // Each page of a sequence's new tokens is a block's own work and its sixteen values are requested together: walked page by
 // page and row by row, 64 rows were 64 memory round trips in a row (27.7 us at 4 x 64 rows of the 7B width).
 template <int NPART>
@@ -406,13 +406,14 @@ __device__ inline void write_values(const RopeArgs& a, int blk) {
     const int b = item / a.H, h = item % a.H;
     const int pos0 = a.row_slot[b * a.R];                   // slot of the sequence's first row
     const int pg = pos0 / kPageSize + blk % pages;
-    if (pg > (pos0 + a.R - 1) / kPageSize) return;
+    if (pg > (pos0 + a.R - 1) / kPageSize) return;          // (the same for all lanes of a wave, as the check above: a head is 64 or 128 channels)
     const int32_t* bt = a.block_table + (size_t)a.seq_ids[b] * a.mpps;
     const float* v = a.qkv + (size_t)b * a.R * 3 * a.d + 2 * a.d + (size_t)h * a.dh + c;
-    uint16_t* rowp = a.vpages + ((((size_t)a.layer * a.n_pages + bt[pg]) * a.H + h) * a.dh + c) * kPageSize;
-    Frag8 lo, hi;                                           // tokens 0..7 and 8..15 of the page
-    lo.u = reinterpret_cast<const uint4*>(rowp)[0];
-    hi.u = reinterpret_cast<const uint4*>(rowp)[1];
+    const bool upper = c & 16;                              // which eight tokens are this thread's
+    uint16_t* rowp = a.vpages + (((size_t)a.layer * a.n_pages + bt[pg]) * a.H + h) * a.dh * kPageSize + page_v(upper ? 8 : 0, c & ~16);
+    Frag8 old[2];                                           // its tokens 0 .. 3 and 4 .. 7, each of channels c & ~16 and c | 16
+    old[0].u = reinterpret_cast<const uint4*>(rowp)[0];
+    old[1].u = reinterpret_cast<const uint4*>(rowp)[1];
     const int r0 = pg * kPageSize - pos0;                   // row of the page's first token
     float vs[kPageSize];
 #pragma unroll
@@ -428,15 +429,25 @@ __device__ inline void write_values(const RopeArgs& a, int blk) {
 #pragma unroll
         for (int tp = 0; tp < kPageSize; ++tp) vs[tp] += q[tp];
     }
+    Frag8 lo, hi;                                           // tokens 0..7 and 8..15 of channel c
 #pragma unroll
-    for (int tp = 0; tp < kPageSize; ++tp) {
-        const uint16_t val = f32_to_f16(vs[tp]);
-        const bool mine = r0 + tp >= 0 && r0 + tp < a.R;
-        if (tp < 8) lo.h[tp & 7] = mine ? val : lo.h[tp & 7];
-        else hi.h[tp & 7] = mine ? val : hi.h[tp & 7];
+    for (int tp = 0; tp < 8; ++tp) { lo.h[tp] = f32_to_f16(vs[tp]); hi.h[tp] = f32_to_f16(vs[tp + 8]); }
+    Frag8 keep, got;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        keep.w[i] = upper ? hi.w[i] : lo.w[i];
+        got.w[i] = __shfl_xor(upper ? lo.w[i] : hi.w[i], 16);
     }
-    reinterpret_cast<uint4*>(rowp)[0] = lo.u;
-    reinterpret_cast<uint4*>(rowp)[1] = hi.u;
+#pragma unroll
+    for (int tp = 0; tp < 8; ++tp) {
+        const int r = r0 + tp + (upper ? 8 : 0);
+        const bool mine = r >= 0 && r < a.R;
+        uint16_t &o0 = old[tp / 4].h[tp % 4], &o1 = old[tp / 4].h[tp % 4 + 4];
+        o0 = mine ? (upper ? got.h[tp] : keep.h[tp]) : o0;
+        o1 = mine ? (upper ? keep.h[tp] : got.h[tp]) : o1;
+    }
+    reinterpret_cast<uint4*>(rowp)[0] = old[0].u;
+    reinterpret_cast<uint4*>(rowp)[1] = old[1].u;
 }
 
 template <int NPART>
@@ -472,12 +483,12 @@ __global__ __launch_bounds__(256) void rope_kv_kernel(RopeArgs a) {
         *reinterpret_cast<uint2*>(a.q_lo + (size_t)m * a.d + c0) = lq0.u;
         *reinterpret_cast<uint2*>(a.q_lo + (size_t)m * a.d + c1) = lq1.u;
         const size_t base = (((size_t)a.layer * a.n_pages + pg) * a.H + h) * kPageSize * a.dh;
-        *reinterpret_cast<uint2*>(a.kpages + base + (size_t)tp * a.dh + i) = ok0.u;
-        *reinterpret_cast<uint2*>(a.kpages + base + (size_t)tp * a.dh + i + half) = ok1.u;
+        *reinterpret_cast<uint2*>(a.kpages + base + page_k(tp, i)) = ok0.u;
+        *reinterpret_cast<uint2*>(a.kpages + base + page_k(tp, i + half)) = ok1.u;
         // the keys' low plane is kept in 8 bits
-        *reinterpret_cast<uint32_t*>(a.klpages + base + (size_t)tp * a.dh + i) =
+        *reinterpret_cast<uint32_t*>(a.klpages + base + page_kl(tp, i)) =
             f16_to_b8(lk0.h[0]) | (f16_to_b8(lk0.h[1]) << 8) | (f16_to_b8(lk0.h[2]) << 16) | (f16_to_b8(lk0.h[3]) << 24);
-        *reinterpret_cast<uint32_t*>(a.klpages + base + (size_t)tp * a.dh + i + half) =
+        *reinterpret_cast<uint32_t*>(a.klpages + base + page_kl(tp, i + half)) =
             f16_to_b8(lk1.h[0]) | (f16_to_b8(lk1.h[1]) << 8) | (f16_to_b8(lk1.h[2]) << 16) | (f16_to_b8(lk1.h[3]) << 24);
     }
 }
@@ -500,7 +511,7 @@ constexpr int kSplitPages = 16;   // pages (of 16 tokens) per context split
 // NWV = waves per workgroup that share a context's pages (4, or 8 for unsplit launches of few workgroups: half
 // the pages per wave; waves 4..7 hand their partial results to waves 0..3 before the four-way merge).
 template <int DH, int NWV>
-__global__ __launch_bounds__(NWV * 64, NWV == 4 ? 4 : 2) void attn_kernel(AttnArgs a) {
+__global__ __launch_bounds__(NWV * 64, 4) void attn_kernel(AttnArgs a) {
     constexpr int NC32 = DH / 32, NC16 = DH / 16;
     __shared__ float sm_m[4][16], sm_l[4][16];
     __shared__ float sm_o[4][16][DH];
@@ -540,22 +551,22 @@ __global__ __launch_bounds__(NWV * 64, NWV == 4 ? 4 : 2) void attn_kernel(AttnAr
     // Pages p0 + wave, + NWV, ..: the K and V fragments of the next page are requested before the current
     // one is multiplied (unconditionally: past the wave's last page the current page is requested again,
     // a cache hit), so a wave always has one page in flight.
-    auto load_page = [&](int p, Frag8 (&ak)[NC32], u32x2 (&akl)[NC32], Frag4 (&bv)[NC16]) {
+    auto load_page = [&](int p, Frag8 (&ak)[NC32], u32x4 (&akl)[NC32 / 2], u32x4 (&bv)[NC32]) {
         const int pg = bt[p];
         const size_t base = (((size_t)a.layer * a.n_pages + pg) * a.H + h) * kPageSize * DH;
-        const uint16_t* kp = a.kpages + base + (size_t)r * DH + g * 8;
-        const uint8_t* klp = a.klpages + base + (size_t)r * DH + g * 8;
+        const uint16_t* kp = a.kpages + base + page_k(r, 8 * g);
+        const uint8_t* klp = a.klpages + base + page_kl(r, 8 * g);
 #pragma unroll
-        for (int c = 0; c < NC32; ++c) ak[c].v4 = *reinterpret_cast<const u32x4*>(kp + c * 32);
+        for (int c = 0; c < NC32; ++c) ak[c].v4 = *reinterpret_cast<const u32x4*>(kp + c * 512);
 #pragma unroll
-        for (int c = 0; c < NC32; ++c) akl[c] = *reinterpret_cast<const u32x2*>(klp + c * 32);
-        const uint16_t* vp = a.vpages + base + (size_t)r * kPageSize + 4 * g;
+        for (int c = 0; c < NC32 / 2; ++c) akl[c] = *reinterpret_cast<const u32x4*>(klp + c * 1024);
+        const uint16_t* vp = a.vpages + base + page_v(4 * g, r);
 #pragma unroll
-        for (int c = 0; c < NC16; ++c) bv[c].v2 = *reinterpret_cast<const u32x2*>(vp + (size_t)c * 16 * kPageSize);
+        for (int c = 0; c < NC32; ++c) bv[c] = *reinterpret_cast<const u32x4*>(vp + c * 512);
     };
     Frag8 ak[NC32], akn[NC32];
-    u32x2 akl[NC32], akln[NC32];        // 8-bit low plane of the keys, widened right before use
-    Frag4 bv[NC16], bvn[NC16];
+    u32x4 akl[NC32 / 2], akln[NC32 / 2];    // 8-bit low plane of the keys, widened right before use
+    u32x4 bv[NC32], bvn[NC32];              // values of two 16-channel fragments each
     int p = p0 + wave;
     if (p < p1) load_page(p, ak, akl, bv);
     for (; p < p1; p += NWV) {
@@ -569,7 +580,7 @@ __global__ __launch_bounds__(NWV * 64, NWV == 4 ? 4 : 2) void attn_kernel(AttnAr
 #pragma unroll
         for (int c = 0; c < NC32; ++c) {
             Frag8 kl;
-            b8x8_to_f16x8(akl[c][0], akl[c][1], kl);
+            b8x8_to_f16x8(akl[c / 2][c % 2 * 2], akl[c / 2][c % 2 * 2 + 1], kl);
             sl = mfma_16x16x32(kl, bq[c], sl);
         }
 #pragma unroll
@@ -613,12 +624,14 @@ __global__ __launch_bounds__(NWV * 64, NWV == 4 ? 4 : 2) void attn_kernel(AttnAr
         for (int c = 0; c < NC16; ++c) {
 #pragma unroll
             for (int i = 0; i < 4; ++i) acc[c][i] *= al[i];
-            acc[c] = mfma_16x16x16(pa, bv[c], acc[c]);  // acc[c][i] = O[q 4g+i][channel 16c + r]
+            Frag4 v;
+            v.v2 = u32x2{bv[c / 2][c % 2 * 2], bv[c / 2][c % 2 * 2 + 1]};
+            acc[c] = mfma_16x16x16(pa, v, acc[c]);      // acc[c][i] = O[q 4g+i][channel 16c + r]
         }
 #pragma unroll
-        for (int c = 0; c < NC32; ++c) { ak[c] = akn[c]; akl[c] = akln[c]; }
+        for (int c = 0; c < NC32; ++c) { ak[c] = akn[c]; bv[c] = bvn[c]; }
 #pragma unroll
-        for (int c = 0; c < NC16; ++c) bv[c] = bvn[c];
+        for (int c = 0; c < NC32 / 2; ++c) akl[c] = akln[c];
     }
     if constexpr (NWV == 8) {
         // ---- waves 4..7 hand over to waves 0..3 (same lane layout on both sides) ----

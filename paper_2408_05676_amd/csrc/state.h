@@ -10,16 +10,23 @@ namespace laser {
 constexpr int kPageSize = 16;     // tokens per KV page (fixed: one MFMA token tile)
 constexpr int kIdSlots = 64;      // ring of staged seq-id vectors
 
-// KV page layouts (fp16), per layer l, page g, head h:
-//   kpages[((l * n_pages + g) * H + h) * 16 * dh + t * dh + c]     token-major  (t = slot in page)
-//   vpages[((l * n_pages + g) * H + h) * dh * 16 + c * 16 + t]     channel-major (transposed)
-// so that a 16-token page of one head is one contiguous 4 KiB block (dh = 128) in either pool and
-// both feed the matrix cores without an in-kernel transpose. Keys are stored split (see mfma.h):
-// klpages holds their 8-bit low plane, one byte per element, indexed like kpages.
+// KV pages: a 16-token page of one head is one contiguous block of 16 * dh elements in each pool, at
+// ((l * n_pages + g) * H + h) * 16 * dh for layer l, page g, head h. Keys are stored split (see mfma.h): klpages holds their
+// 8-bit low plane, one byte per element. Inside a page (t = slot in the page, c = channel) the elements lie in the order in
+// which the 64 lanes of a wave hold a matrix operand, so that every load of the attention kernels is one kilobyte in a row,
+// 16 bytes a lane: lane (r = lane % 16, g = lane / 16) takes
+//   keys       token r, channels 32 i + 8 g .. + 7                                           (load i)
+//   low plane  token r, channels 64 i + 8 g .. + 7 and 64 i + 32 + 8 g .. + 7                (load i)
+//   values     tokens 4 g .. + 3 of channel 32 i + r, then of channel 32 i + 16 + r          (load i)
+// With tokens (values: channels) one after the other a load touched 16 pieces of 64, 32 and 32 bytes; ATTN_FIG
+__host__ __device__ inline int page_k(int t, int c) { return (c >> 5) * 512 + t * 32 + (c & 31); }
+__host__ __device__ inline int page_kl(int t, int c) { return (c >> 6) * 1024 + t * 64 + ((c >> 3) & 3) * 16 + ((c >> 5) & 1) * 8 + (c & 7); }
+__host__ __device__ inline int page_v(int t, int c) { return (c >> 5) * 512 + (c & 15) * 32 + (t >> 2) * 8 + ((c >> 4) & 1) * 4 + (t & 3); }
+
 struct KV {
     laser_kv_desc d{};
     uint16_t* kpages = nullptr;
-    uint8_t* klpages = nullptr;       // 8-bit low plane of the split keys, indexed like kpages: k = kpages + klpages / 4096
+    uint8_t* klpages = nullptr;       // 8-bit low plane of the split keys: k = kpages + klpages / 4096
     uint16_t* vpages = nullptr;
     int32_t* block_table = nullptr;   // [dev] [max_seqs][max_pages_per_seq]
     int32_t* len = nullptr;           // [dev] [max_seqs] committed tokens

@@ -1,0 +1,43 @@
+"""Cache pages as every writer and reader of them sees them: keys and values brought in by laser_kv_import, rows written by the
+step itself (persistent and general kernels, 16 rows and fewer, and more), read back by the next step; against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import synth
+from oracle.decoder import Decoder
+from tests import gpu_util as gu
+
+pytestmark = pytest.mark.gpu
+
+
+# both head sizes; committed lengths at the edges of pages and of a wave's pair of pages; new rows inside one page, over two and over three
+@pytest.mark.parametrize("heads", [4, 2])
+@pytest.mark.parametrize("fused", [1, 0])
+@pytest.mark.parametrize("ctx,K", [(1, 3), (15, 1), (16, 15), (31, 7), (45, 19), (270, 4)])
+def test_imported_and_written_pages(heads, fused, ctx, K):
+    import paper_2408_05676_amd as laser
+    sh = synth.SHAPES["tiny"].with_(d=256, n_heads=heads, ffn=640, vocab=512)
+    model = gu.make_model(sh, max_rows=32, max_batch=1, max_pos=512)
+    model.set_option("fused", fused)
+    kv = gu.make_kv(sh, n_pages=24, max_seqs=1, max_pages_per_seq=24)
+    kv.reserve(0, ctx + 2 * (K + 1))
+    dec = Decoder(sh.n_layers, sh.d, sh.n_heads, sh.ffn, sh.vocab, synth.gen_all_weights(sh), sh.eps, sh.rope_base)
+    cache = dec.new_cache(ctx + 2 * (K + 1))
+    gen = torch.Generator().manual_seed(ctx)
+    for layer in range(sh.n_layers):
+        t = torch.randn((2, ctx, sh.n_heads, sh.head_dim), generator=gen).to(torch.float16)
+        cache.k[layer, :ctx], cache.v[layer, :ctx] = t[0].double().numpy(), t[1].double().numpy()
+        t = t.cuda()
+        kv.import_layer(0, layer, t[0], t[1])
+    cache.commit(ctx)
+    kv.set_len(0, ctx)
+    n = torch.full((1,), K, dtype=torch.int32, device="cuda")
+    for step in range(2):                            # the second step reads the pages the first one wrote
+        tok = torch.randint(0, sh.vocab, (1, K + 1), generator=gen, dtype=torch.int32)
+        _, _, logits = laser.verify_step(model, kv, [0], tok[:, 0].cuda(), tok[:, 1:].contiguous().cuda(), n, 1, -1.0, 0, want_logits=True)
+        laser.kv_commit(kv, [0], n)
+        want = dec.verify_forward(cache, tok[0].numpy())
+        cache.commit(K + 1)
+        ok, err, ratio = gu.logits_close(logits.cpu().numpy().reshape(want.shape).astype(np.float64), want)
+        assert ok, (step, err, ratio)
