@@ -27,7 +27,7 @@
 namespace laser {
 
 // ------------------------------------------------------------------------------------ kernel
-constexpr int kCand = 512;         // occurrences a wave keeps in LDS (more: streamed from the index, re-checked against the chain)
+constexpr int kCand = 512;         // occurrences a wave keeps in LDS (more: streamed from the index, re-checked against the chain); see retrieve_kernel
 constexpr int kVote = 512;         // vote-table slots (power of two; wider votes are partitioned)
 // Groups of 64 occurrences whose loads a vote over a streamed run has in flight together. A wave alone waits for memory: four.
 // Beyond 1024 contexts the waves of a compute unit cover each other's waits and four groups each outgrow its cache: one. A run
@@ -64,24 +64,25 @@ struct RetrieveArgs {
 // their own, K = 1 / 4 / 16: ballots alone 47.8 / 48.8 / 56.4 us, now 14.6 / 14.3 / 27.4; votes by the table alone 14.1 /
 // 20.1 / 45.0. Occurrences that agree but for a tenth per step: ballots alone 10.1 / 11.1 / 20.0, now 12.5 / 9.6 / 20.3,
 // the table alone 12.0 / 29.4 / 75.2.
+constexpr int follow_table(int q) { return q > 4 ? 64 * q : kVote; }       // slots: as many as the 64 q voters or more (each may bring a token of its own)
 template <int Q, int kAhead, bool OWN>
 __device__ __forceinline__ int follow_lanes(const RetrieveArgs& a, const uint32_t* cand, const uint32_t* cand_end, uint32_t m, const uint32_t* own_cand,
                                    const int32_t* own, uint32_t own_len, uint32_t mo, int j0, int* chain, int* vote_tok, int* vote_cnt,
                                    uint32_t& lane_min, uint32_t& lane_own) {
-    constexpr int kBallots = 8;
-    static_assert(64 * Q < kVote, "every voter may bring a token of its own");
+    constexpr int kBallots = 8, kTable = follow_table(Q);
     const int lane = threadIdx.x;
     uint32_t e[Q], end[Q];
     const int32_t* text[Q];
-    bool live[Q], mine_own[Q];
+    uint32_t live = 0, mine_own = 0;               // bit s: occurrence s of this lane (in lane masks, sixteen occurrences ran out of scalar registers)
 #pragma unroll
     for (int s = 0; s < Q; ++s) {
         const uint32_t i = (uint32_t)(s * 64 + lane);
-        live[s] = i < m + mo;
-        mine_own[s] = OWN && live[s] && i >= m;
-        e[s] = mine_own[s] ? own_cand[OWN ? i - m : 0] : live[s] ? cand[i] : 0u;
-        end[s] = mine_own[s] ? own_len : live[s] ? cand_end[i] : 0u;
-        text[s] = mine_own[s] ? own : a.P;
+        const bool have = i < m + mo, is_own = OWN && have && i >= m;
+        live |= (have ? 1u : 0u) << s;
+        mine_own |= (is_own ? 1u : 0u) << s;
+        e[s] = is_own ? own_cand[OWN ? i - m : 0] : have ? cand[i] : 0u;
+        end[s] = is_own ? own_len : have ? cand_end[i] : 0u;
+        text[s] = is_own ? own : a.P;
     }
     int len = j0 - 1;
     bool more = true;
@@ -93,67 +94,64 @@ __device__ __forceinline__ int follow_lanes(const RetrieveArgs& a, const uint32_
         for (int s = 0; s < Q; ++s)
 #pragma unroll
             for (int q = 0; q < kAhead; ++q)
-                tok[s][q] = live[s] && j + q <= a.K && e[s] + (uint32_t)(j + q) < end[s] ? text[s][e[s] + (uint32_t)(j + q)] : 0;
+                tok[s][q] = ((live >> s) & 1u) && j + q <= a.K && e[s] + (uint32_t)(j + q) < end[s] ? text[s][e[s] + (uint32_t)(j + q)] : 0;
 #pragma unroll
         for (int q = 0; q < kAhead; ++q) {
-            bool ok[Q];
-            uint64_t rest[Q], win[Q];
-            int left = 0;                              // voters not counted yet
+            uint32_t rest = 0, win = 0;                // voters not counted yet, the winner's
+            int left = 0;
 #pragma unroll
             for (int s = 0; s < Q; ++s) {
-                ok[s] = more && live[s] && j + q <= a.K && e[s] + (uint32_t)(j + q) < end[s];
-                rest[s] = __ballot(ok[s]);
-                win[s] = 0;
-                left += __popcll(rest[s]);
+                const bool ok = more && ((live >> s) & 1u) && j + q <= a.K && e[s] + (uint32_t)(j + q) < end[s];
+                rest |= (ok ? 1u : 0u) << s;
+                left += __popcll(__ballot(ok));
             }
             int win_tok = 0, win_cnt = 0, ballots = 0;
+            while (left >= win_cnt) {                  // larger count, then smaller token id: an equal count can still win
+                const uint64_t voters = __ballot(rest != 0);
+                if (!voters) break;
+                if (Q > 1 && ballots++ == kBallots) { left = -1; break; }
+                int mine = 0;                          // a token of this lane that is not counted yet
 #pragma unroll
-            for (int s = 0; s < Q; ++s)
-                while (rest[s] && left >= win_cnt) {   // larger count, then smaller token id: an equal count can still win
-                    if (Q > 1 && ballots++ == kBallots) { left = -1; break; }
-                    const int t = __builtin_amdgcn_readlane(tok[s][q], __ffsll((unsigned long long)rest[s]) - 1);
-                    uint64_t same[Q];
-                    int c = 0;
+                for (int u = Q - 1; u >= 0; --u) mine = ((rest >> u) & 1u) ? tok[u][q] : mine;
+                const int t = __builtin_amdgcn_readlane(mine, __ffsll((unsigned long long)voters) - 1);
+                uint32_t same = 0;
+                int c = 0;
 #pragma unroll
-                    for (int u = 0; u < Q; ++u) {
-                        same[u] = u < s ? 0ull : __ballot(ok[u] && tok[u][q] == t);
-                        c += __popcll(same[u]);
-                        rest[u] &= ~same[u];
-                    }
-                    left -= c;
-                    if (c > win_cnt || (c == win_cnt && t < win_tok)) {
-                        win_cnt = c; win_tok = t;
-#pragma unroll
-                        for (int u = 0; u < Q; ++u) win[u] = same[u];
-                    }
+                for (int u = 0; u < Q; ++u) {
+                    const bool is = ((rest >> u) & 1u) && tok[u][q] == t;
+                    same |= (is ? 1u : 0u) << u;
+                    c += __popcll(__ballot(is));
                 }
+                rest &= ~same;
+                left -= c;
+                if (c > win_cnt || (c == win_cnt && t < win_tok)) { win_cnt = c; win_tok = t; win = same; }
+            }
             if (Q > 1 && left < 0) { open = j + q; win_cnt = 0; }
             if (win_cnt == 0) { more = false; continue; }          // no survivor has a successor left, or K steps are done
             if (lane == 0) chain[j + q - 1] = win_tok;
             len = j + q;
-#pragma unroll
-            for (int s = 0; s < Q; ++s) live[s] = (win[s] >> lane) & 1ull;
+            live = win;
         }
         if (Q > 1 && open) {
             int t[Q];
 #pragma unroll
-            for (int s = 0; s < Q; ++s) t[s] = live[s] && e[s] + (uint32_t)open < end[s] ? text[s][e[s] + (uint32_t)open] : -1;
-            for (int i = lane; i < kVote; i += 64) { vote_tok[i] = kEmptyTok; vote_cnt[i] = 0; }
+            for (int s = 0; s < Q; ++s) t[s] = ((live >> s) & 1u) && e[s] + (uint32_t)open < end[s] ? text[s][e[s] + (uint32_t)open] : -1;
+            for (int i = lane; i < kTable; i += 64) { vote_tok[i] = kEmptyTok; vote_cnt[i] = 0; }
             __syncthreads();
 #pragma unroll
             for (int s = 0; s < Q; ++s)
                 if (t[s] >= 0) {
-                    uint32_t at = fmix32((uint32_t)t[s]) & (kVote - 1);
+                    uint32_t at = fmix32((uint32_t)t[s]) & (kTable - 1);
                     for (;;) {
                         const int was = atomicCAS(&vote_tok[at], kEmptyTok, t[s]);
                         if (was == kEmptyTok || was == t[s]) break;
-                        at = (at + 1) & (kVote - 1);
+                        at = (at + 1) & (kTable - 1);
                     }
                     atomicAdd(&vote_cnt[at], 1);
                 }
             __syncthreads();
             int bt = 0, bc = 0;
-            for (int i = lane; i < kVote; i += 64) {
+            for (int i = lane; i < kTable; i += 64) {
                 const int c = vote_cnt[i], tk = vote_tok[i];
                 if (c > bc || (c == bc && c > 0 && tk < bt)) { bc = c; bt = tk; }
             }
@@ -164,8 +162,9 @@ __device__ __forceinline__ int follow_lanes(const RetrieveArgs& a, const uint32_
             __syncthreads();
             if (lane == 0) chain[open - 1] = bt;
             len = open;
+            live = 0;
 #pragma unroll
-            for (int s = 0; s < Q; ++s) live[s] = t[s] == bt;
+            for (int s = 0; s < Q; ++s) live |= (t[s] == bt ? 1u : 0u) << s;
             next = open + 1;
             more = true;
         }
@@ -173,8 +172,8 @@ __device__ __forceinline__ int follow_lanes(const RetrieveArgs& a, const uint32_
     lane_min = lane_own = 0xFFFFFFFFu;
 #pragma unroll
     for (int s = 0; s < Q; ++s) {
-        if (live[s] && !mine_own[s]) lane_min = min(lane_min, e[s]);
-        if (live[s] && mine_own[s]) lane_own = min(lane_own, e[s]);
+        if (((live & ~mine_own) >> s) & 1u) lane_min = min(lane_min, e[s]);
+        if (((live & mine_own) >> s) & 1u) lane_own = min(lane_own, e[s]);
     }
     return len;
 }
@@ -184,6 +183,10 @@ __device__ __forceinline__ int follow_lanes(const RetrieveArgs& a, const uint32_
 // in LDS (own_cand, position-ascending) and take part in every vote and filter next to the pool's.
 template <bool OWN, int kGroups>
 __global__ __launch_bounds__(64) void retrieve_kernel(RetrieveArgs a) {
+    // Up to kFourGroupsMax contexts a compute unit has few waves and LDS to spare: twice the occurrences are kept, and a lane follows up
+    // to sixteen of them. Eight contexts over runs of some 900 occurrences, chains of 8, thinned by a tenth per step: 139 us streamed, 39 so.
+    constexpr int kCand = kGroups == 4 ? 1024 : laser::kCand, kLanesMax = kGroups == 4 ? 1024 : 256;
+    constexpr int kTable = follow_table(kLanesMax / 64);
     __shared__ uint32_t cand[kCand];
     // Beside each occurrence kept in LDS: the end of its sequence, and the successor token the current vote read for
     // it (-1: none). The filter that follows a vote then needs no memory round trip at all, the vote one instead of
@@ -191,8 +194,8 @@ __global__ __launch_bounds__(64) void retrieve_kernel(RetrieveArgs a) {
     __shared__ uint32_t cand_end[kCand];
     __shared__ int cand_tok[kCand];
     __shared__ uint32_t own_cand[OWN ? kOwnMax : 1];
-    __shared__ int vote_tok[kVote];
-    __shared__ int vote_cnt[kVote];
+    __shared__ int vote_tok[kTable];
+    __shared__ int vote_cnt[kTable];
     __shared__ int chain[LASER_MAX_DRAFT + 1];
     __shared__ int best_chain[LASER_MAX_DRAFT + 1];
     __shared__ int sh_distinct;
@@ -251,10 +254,15 @@ __global__ __launch_bounds__(64) void retrieve_kernel(RetrieveArgs a) {
         bool in_lds = count <= (uint32_t)kCand;
         uint32_t m = count;
         if (in_lds)
-            for (uint32_t i = lane; i < count; i += 64) {
-                const uint32_t e = a.sa[start + i];
-                cand[i] = e;
-                cand_end[i] = a.seq_end[e];
+            for (uint32_t i0 = lane; i0 < count; i0 += 64 * kGroups) {
+                uint32_t e[kGroups], end[kGroups];
+#pragma unroll
+                for (int u = 0; u < kGroups; ++u) e[u] = i0 + u * 64 < count ? a.sa[start + i0 + u * 64] : 0u;
+#pragma unroll
+                for (int u = 0; u < kGroups; ++u) end[u] = i0 + u * 64 < count ? a.seq_end[e[u]] : 0u;
+#pragma unroll
+                for (int u = 0; u < kGroups; ++u)
+                    if (i0 + u * 64 < count) { cand[i0 + u * 64] = e[u]; cand_end[i0 + u * 64] = end[u]; }
             }
         __syncthreads();
 
@@ -269,15 +277,20 @@ __global__ __launch_bounds__(64) void retrieve_kernel(RetrieveArgs a) {
             // ballots pay off for fewer: 64 occurrences that all differ, 2048 lookups, K = 1 / 2: 12.7 / 12.8 us, by the
             // vote table 9.5 / 10.4.
             const int steps = a.K - j + 1;
-            if (in_lds && m + mo <= (steps > 1 ? 256u : 32u)) {
+            if (in_lds && m + mo <= (steps > 1 ? (uint32_t)kLanesMax : 32u)) {
                 in_lanes = true;
                 auto follow = [&](auto q, auto ahead) {
                     len = follow_lanes<decltype(q)::value, decltype(ahead)::value, OWN>(a, cand, cand_end, m, own_cand, own, own_len, mo, j, chain, vote_tok, vote_cnt, lane_min, lane_own);
                 };
                 using std::integral_constant;
                 if (m + mo <= (steps > 2 ? 64u : 32u)) follow(integral_constant<int, 1>{}, integral_constant<int, 8>{});
-                else if (steps <= 4) follow(integral_constant<int, 4>{}, integral_constant<int, 1>{});
-                else follow(integral_constant<int, 4>{}, integral_constant<int, 8>{});
+                else if (m + mo <= 256u) {
+                    if (steps <= 4) follow(integral_constant<int, 4>{}, integral_constant<int, 1>{});
+                    else follow(integral_constant<int, 4>{}, integral_constant<int, 8>{});
+                } else if constexpr (kLanesMax > 256) {
+                    if (steps <= 4) follow(integral_constant<int, 16>{}, integral_constant<int, 1>{});
+                    else follow(integral_constant<int, 16>{}, integral_constant<int, 8>{});
+                }
                 break;
             }
             int win_tok = -1, win_cnt = 0;

@@ -1,0 +1,41 @@
+"""Lookups of few contexts whose 257 .. 1024 survivors are followed up to sixteen to a lane, and the counts beyond, which are streamed, against
+the oracle, exactly: texts that agree for a while, that all differ, pool and own text mixed."""
+import numpy as np
+import pytest
+
+from tests.test_gpu_lane_votes import _flat_pool, _pool
+from tests.test_gpu_retrieval import _compare as compare_pool
+from tests.test_gpu_temp_branch import _compare as compare_own
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("count", [257, 700, 1023, 1024, 1025, 1500])
+@pytest.mark.parametrize("vocab", [2, 1000])
+@pytest.mark.parametrize("K", [1, 2, 4, 9, 33])
+def test_counts_up_to_sixteen_waves(count, vocab, K):
+    rng = np.random.default_rng(count * 100 + K + vocab)
+    toks, off, keys, _ = _pool(rng, count, vocab)
+    compare_pool(toks, off, keys, [3, 3, 4], [[1, 7], [toks[0], toks[1]], [1, 7]], 1, 2, K)
+
+
+@pytest.mark.parametrize("count", [900, 1024])
+@pytest.mark.parametrize("agree", [0, 3, 9])
+@pytest.mark.parametrize("spread", [5, 100, 5000])
+def test_votes_over_many_tokens(count, agree, spread):
+    rng = np.random.default_rng(count + 10 * agree + spread)
+    pool = _flat_pool(rng, count, agree, spread)
+    compare_pool(pool[0], pool[1], pool[2], [3, 3], [[1, 7], [1, 7]], 1, 2, 16)
+
+
+@pytest.mark.parametrize("count", [400, 1000, 1020, 1024])
+def test_pool_and_own_text_beyond_four_waves(count):
+    rng = np.random.default_rng(count)
+    toks, off, keys, trunk = _pool(rng, count, 2)
+    owns = []
+    for reps in (0, 3, 5, 24, 70):
+        own = []
+        for _ in range(reps):
+            own += [7] + trunk[:int(rng.integers(1, 12))].tolist()
+        owns.append(own + [5, 7])
+    compare_own(toks, off, keys, [3, 3, 3, 3, 9], owns, 1, 2, 12)
