@@ -152,26 +152,58 @@ __global__ __launch_bounds__(256) void accept_rows_kernel(AcceptArgs a) {
         }
         float mx = -INFINITY, sum = 0.f;
         int arg = 0x7FFFFFFF, ahead[kCandPass] = {0, 0, 0, 0};
-        for (int c = lane; c < a.chunks; c += 64) {
-            const size_t o = (size_t)row * a.chunks + c;
-            const float cm = a.hp_max[o], cs = a.hp_sum[o];
-            const int ca = a.hp_arg[o];
-            const float M = fmaxf(mx, cm);
-            sum = sum * __expf(mx - M) + cs * __expf(cm - M);
-            if (before(cm, ca, mx, arg)) arg = ca;
-            mx = M;
-            bool any = false;
+        // A lane's records, eight requested at a time: one by one, the 1000 chunks of 72 rows at a vocabulary of 32000 were
+        // sixteen round trips in a row (22.4 us; 18.8 with the lists still read one by one, 16.86 so).
+        constexpr int kRec = 8;
+        for (int c1 = lane; c1 < a.chunks; c1 += 64 * kRec) {
+            float vm[kRec], vs[kRec];
+            int va[kRec];
 #pragma unroll
-            for (int j = 0; j < kCandPass; ++j) any |= x[j] >= 0 && ca != x[j] && before(cm, ca, lx[j], x[j]);
-            if (any)
+            for (int u = 0; u < kRec; ++u) {
+                const int c = c1 + 64 * u < a.chunks ? c1 + 64 * u : c1;
+                const size_t o = (size_t)row * a.chunks + c;
+                vm[u] = a.hp_max[o]; vs[u] = a.hp_sum[o]; va[u] = a.hp_arg[o];
+            }
 #pragma unroll
-                for (int t = 0; t < KT; ++t)
-                    if (t < a.topk) {                            // (a record holds that many, possibly no more)
-                        const float v = a.hp_topv[o * KT + t];
-                        const int i = a.hp_topi[o * KT + t];
+            for (int u = 0; u < kRec; ++u) {
+                if (c1 + 64 * u >= a.chunks) break;
+                const float cm = vm[u], cs = vs[u];
+                const int ca = va[u];
+                const float M = fmaxf(mx, cm);
+                sum = sum * __expf(mx - M) + cs * __expf(cm - M);
+                if (before(cm, ca, mx, arg)) arg = ca;
+                mx = M;
+            }
+            // records whose list may hold entries ahead of a candidate; the first two entries of all of them together as well
+            uint32_t open = 0;
 #pragma unroll
-                        for (int j = 0; j < kCandPass; ++j) ahead[j] += (x[j] >= 0 && i != x[j] && before(v, i, lx[j], x[j])) ? 1 : 0;
+            for (int u = 0; u < kRec; ++u)
+#pragma unroll
+                for (int j = 0; j < kCandPass; ++j)
+                    open |= (c1 + 64 * u < a.chunks && x[j] >= 0 && va[u] != x[j] && before(vm[u], va[u], lx[j], x[j]) ? 1u : 0u) << u;
+            if (!open) continue;
+            float2 tv[kRec];
+            int2 ti[kRec];
+#pragma unroll
+            for (int u = 0; u < kRec; ++u) {
+                const size_t o = ((size_t)row * a.chunks + (((open >> u) & 1u) ? c1 + 64 * u : c1)) * KT;
+                tv[u] = *reinterpret_cast<const float2*>(a.hp_topv + o);
+                ti[u] = *reinterpret_cast<const int2*>(a.hp_topi + o);
+            }
+            auto count = [&](float v, int i) {
+#pragma unroll
+                for (int j = 0; j < kCandPass; ++j) ahead[j] += (x[j] >= 0 && i != x[j] && before(v, i, lx[j], x[j])) ? 1 : 0;
+            };
+#pragma unroll
+            for (int u = 0; u < kRec; ++u)
+                if ((open >> u) & 1u) {
+                    count(tv[u].x, ti[u].x);
+                    if (a.topk > 1) count(tv[u].y, ti[u].y);                // (a record holds topk entries, possibly no more)
+                    for (int t = 2; t < a.topk && t < KT; ++t) {
+                        const size_t o = ((size_t)row * a.chunks + c1 + 64 * u) * KT + t;
+                        count(a.hp_topv[o], a.hp_topi[o]);
                     }
+                }
         }
         for (int off = 32; off > 0; off >>= 1) {
             const float omx = __shfl_xor(mx, off), osum = __shfl_xor(sum, off);
