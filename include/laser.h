@@ -194,6 +194,7 @@ typedef struct laser_model_desc {
  * LASER_E_HIP if the memory is not there and with LASER_E_LIMIT if a weight exceeds the fp16 range (|w| > 65280); up to 80
  * rows it then does without, as it does while the stream is being captured and where the copies would take more than a
  * quarter of the free memory. laser_verify_head makes its copy with more than 80 rows, laser_verify_head_static none.
+ * Copies are made once: weights changed in place afterwards are seen only after the option below has been set again.
  * Without copies (option "f16_copies" = 0 makes none) the tiled kernels widen the bf16 weights on the fly (slower).
  * Weights need the alignment of their elements only; off the 16-byte grid and without copies they take kernels that stage
  * them through registers (slower). */
@@ -356,7 +357,8 @@ int laser_generate(laser_model* model, laser_kv* kv, const laser_pool* pool, con
  * shape or the workspace cannot take falls back to 1). The parts are added in a fixed order by the
  * kernel that follows, so a given setting is deterministic; different settings may differ in the
  * last bits. Tuning and test knobs: the default is what the benchmark measures.
- * "f16_copies" = 1 (default) or 0: see laser_model_create.
+ * "f16_copies" = 1 (default) or 0: see laser_model_create. Either value drops the copies made so far (the call waits for
+ * the device); with 1 the next step that takes them makes them anew.
  * "mid_waves" = 0 (default): 17..80 rows take the tiled GEMM; 4 or 8: the one that stages rows through
  * registers, with that many waves per workgroup.
  * "tile" = 0 (default: chosen from the launch shape) or i: with more than 16 rows every tiled product takes the i-th entry

@@ -1095,6 +1095,11 @@ extern "C" int laser_model_set_option(laser_model* mh, const char* name, int val
     if (std::string(name) == "f16_copies") {
         LASER_REQUIRE(value == 0 || value == 1, LASER_E_INVALID_ARG, "f16_copies must be 0 or 1");
         m->f16_copies = value;
+        for (uint16_t** p : {&m->w16[0], &m->w16[1], &m->w16[2], &m->w16[3], &m->wlm16}) {     // (hipFree waits for the steps that read them)
+            if (*p) LASER_HIP_CHECK(hipFree(*p));
+            *p = nullptr;
+        }
+        m->no_few_copies = false;
         return LASER_OK;
     }
     if (std::string(name) == "mid_waves") {

@@ -41,3 +41,31 @@ def test_imported_and_written_pages(heads, fused, ctx, K):
         cache.commit(K + 1)
         ok, err, ratio = gu.logits_close(logits.cpu().numpy().reshape(want.shape).astype(np.float64), want)
         assert ok, (step, err, ratio)
+
+
+@pytest.mark.parametrize("rows", [4, 24, 96])
+def test_weights_changed_in_place_are_seen_after_the_option_is_set(rows):
+    """A step before and after: the fp16 copies are made anew, and without copies the weights are the caller's own."""
+    import paper_2408_05676_amd as laser
+    sh = synth.SHAPES["tiny"].with_(d=256, n_heads=4, ffn=640, vocab=512)
+    w, other = gu.gpu_weights(sh), gu.gpu_weights(sh.with_(vocab=512))
+    other["wqkv"], other["wlm"] = other["wqkv"].flip(1).contiguous(), other["wlm"].flip(0).contiguous()
+    tok = torch.arange(rows, device="cuda", dtype=torch.int32)[:, None]
+
+    def logits(model):
+        kv = gu.make_kv(sh, n_pages=rows, max_seqs=rows, max_pages_per_seq=1)
+        for s in range(rows):
+            kv.reserve(s, 16)
+        none = torch.empty((rows, 0), dtype=torch.int32, device="cuda")
+        return laser.verify_step(model, kv, list(range(rows)), tok[:, 0].contiguous(), none, torch.zeros(rows, dtype=torch.int32, device="cuda"),
+                                 1, -1.0, 0, want_logits=True)[2].clone()
+
+    def make(weights):
+        return laser.Model(sh.n_layers, sh.d, sh.n_heads, sh.ffn, sh.vocab, weights, rows, rows, 64, eps=sh.eps, rope_base=sh.rope_base)
+
+    model, want = make(w), logits(make(other))
+    logits(model)
+    w["wqkv"].copy_(other["wqkv"])
+    w["wlm"].copy_(other["wlm"])
+    model.set_option("f16_copies", 1)
+    assert torch.equal(logits(model), want)
