@@ -193,7 +193,8 @@ typedef struct laser_model_desc {
  * inside the first step that takes them; that call synchronises the stream. With more than 80 rows it fails with
  * LASER_E_HIP if the memory is not there and with LASER_E_LIMIT if a weight exceeds the fp16 range (|w| > 65280); up to 80
  * rows it then does without, as it does while the stream is being captured and where the copies would take more than a
- * quarter of the free memory. laser_verify_head makes its copy with more than 80 rows, laser_verify_head_static none.
+ * quarter of the free memory. laser_verify_head makes its copy with more than 80 rows, and up to there reads the caller's
+ * matrix at every call; laser_verify_head_static makes none.
  * Copies are made once: weights changed in place afterwards are seen only after the option below has been set again.
  * Without copies (option "f16_copies" = 0 makes none) the tiled kernels widen the bf16 weights on the fly (slower).
  * Weights need the alignment of their elements only; off the 16-byte grid and without copies they take kernels that stage

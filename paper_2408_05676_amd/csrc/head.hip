@@ -301,9 +301,10 @@ __global__ __launch_bounds__(256) void copy_rows_kernel(const uint16_t* __restri
     if (i < n8) *reinterpret_cast<u32x4*>(dst + i * 8) = *reinterpret_cast<const u32x4a2*>(src + i * 8);
 }
 
-// candidates -> pass 1 -> acceptance. Allocates nothing. tokens / parent / n_nodes: the drafts as a pseudo-sequence
-// (parent == NULL: a chain, n_nodes = draft_len).
-static int run_head_bufs(Model* m, const uint16_t* h, const int32_t* tokens, const int32_t* parent, const int32_t* n_nodes, int B, int K,
+// candidates -> pass 1 -> acceptance. Allocates nothing up to 80 rows. tokens / parent / n_nodes: the drafts as a pseudo-sequence
+// (parent == NULL: a chain, n_nodes = draft_len). few16: the fp16 copy of the head matrix for 17..80 rows, or NULL for the
+// caller's own matrix.
+static int run_head_bufs(Model* m, const uint16_t* few16, const uint16_t* h, const int32_t* tokens, const int32_t* parent, const int32_t* n_nodes, int B, int K,
                          int topk, float p, int mode, int32_t* accept_len, int32_t* out_tokens, int32_t* accept_path, float* logits_dbg,
                          const HeadBufs& hb, hipStream_t stream) {
     const int M = B * (K + 1), V = m->d.vocab, dm = m->d.d_model;
@@ -317,10 +318,10 @@ static int run_head_bufs(Model* m, const uint16_t* h, const int32_t* tokens, con
         HeadArgs a{m->d.wlm, h, M, V, dm, tpw, hp};
         dim3 grid((unsigned)((m->head_chunks + 3) / 4), 1u);         // at most 16 rows: one row tile
         hipLaunchKernelGGL(lm_head_kernel<1>, grid, dim3(256), 0, stream, a);
-    } else if (M <= kHeadMidMaxRows && m->mid_waves == 0 && (m->wlm16 || on_16_byte_grid(m->d.wlm)) && on_16_byte_grid(h)) {
+    } else if (M <= kHeadMidMaxRows && m->mid_waves == 0 && (few16 || on_16_byte_grid(m->d.wlm)) && on_16_byte_grid(h)) {
         hp.chunks = (V + 31) / 32;
-        GemmTileArgs t{m->wlm16 ? m->wlm16 : m->d.wlm, h, nullptr, M, V, dm, 0, 0, 1, nullptr, nullptr, hp};
-        launch_few_head(t, m->wlm16 != nullptr, stream);
+        GemmTileArgs t{few16 ? few16 : m->d.wlm, h, nullptr, M, V, dm, 0, 0, 1, nullptr, nullptr, hp};
+        launch_few_head(t, few16 != nullptr, stream);
     } else if (M <= kHeadMidMaxRows && dm % kGemmKStep == 0) {
         const GemmMidPlan pl = gemm_mid_plan(M, V, dm, 1, false, 0);
         hp.chunks = (V / 16 + pl.NW - 1) / pl.NW;                     // = workgroups of the launch
@@ -353,14 +354,14 @@ static int run_head_bufs(Model* m, const uint16_t* h, const int32_t* tokens, con
     return LASER_OK;
 }
 
-int run_head(Model* m, const uint16_t* h, const int32_t* tokens, const int32_t* parent, const int32_t* n_nodes, int B, int K,
+// few_copy: a step's own head, which up to 80 rows takes the copy that the step has made. The head alone (laser_verify_head)
+// reads the caller's matrix at every call there, allocates nothing and waits for nothing.
+int run_head(Model* m, bool few_copy, const uint16_t* h, const int32_t* tokens, const int32_t* parent, const int32_t* n_nodes, int B, int K,
              int topk, float p, int mode, int32_t* accept_len, int32_t* out_tokens, int32_t* accept_path, float* logits_dbg,
              hipStream_t stream) {
-    const int M = B * (K + 1);
-    if (M > kHeadStreamMaxRows && M <= kHeadMidMaxRows) copies_for_few_rows(m, false, stream);
     HeadBufs hb{m->cand_beg, m->cand_cnt, m->cand_x, m->node_cand, m->cand_lx, m->hp_max, m->hp_sum, m->hp_arg, m->hp_topv, m->hp_topi,
                 m->row_mx, m->row_sum, m->row_arg, m->cand_rank};
-    return run_head_bufs(m, h, tokens, parent, n_nodes, B, K, topk, p, mode, accept_len, out_tokens, accept_path, logits_dbg, hb, stream);
+    return run_head_bufs(m, few_copy ? m->wlm16 : nullptr, h, tokens, parent, n_nodes, B, K, topk, p, mode, accept_len, out_tokens, accept_path, logits_dbg, hb, stream);
 }
 
 // ---- the head without any allocation ------------------------------------------------------------------------
@@ -413,7 +414,7 @@ int run_head_static(Model* m, const uint16_t* h, const int32_t* drafts, const in
     // lm_head_kernel overwrites every (row, chunk) record that the acceptance kernels read.
     HeadBufs hb{sc->cand_beg, sc->cand_cnt, sc->cand_x, sc->node_cand, sc->cand_lx, sc->hp_max, sc->hp_sum, sc->hp_arg, sc->hp_topv, sc->hp_topi,
                 sc->row_mx, sc->row_sum, sc->row_arg, sc->cand_rank};
-    return run_head_bufs(m, h, drafts, nullptr, draft_len, B, K, topk, p, mode, accept_len, out_tokens, nullptr, nullptr, hb, stream);
+    return run_head_bufs(m, nullptr, h, drafts, nullptr, draft_len, B, K, topk, p, mode, accept_len, out_tokens, nullptr, nullptr, hb, stream);
 }
 
 }  // namespace laser

@@ -20,7 +20,7 @@ int run_fused(Model* m, KV* kv, const int32_t* ids_dev, const int32_t* pending, 
 int fused_status(Model* m, hipStream_t stream, int* aborted);
 int fused_read_trace(Model* m, hipStream_t stream, long long* out, int max_elems, int* nwg, int* cap);
 
-int run_head(Model* m, const uint16_t* h, const int32_t* tokens, const int32_t* parent, const int32_t* n_nodes, int B, int K,
+int run_head(Model* m, bool few_copy, const uint16_t* h, const int32_t* tokens, const int32_t* parent, const int32_t* n_nodes, int B, int K,
              int topk, float p, int mode, int32_t* accept_len, int32_t* out_tokens, int32_t* accept_path, float* logits_dbg,
              hipStream_t stream);
 size_t head_records(const Model* m);
@@ -757,9 +757,9 @@ static int widen_projections(Model* m, hipStream_t stream) {
 // The copies for steps of up to 80 rows, whose kernels take the caller's weights as well (10 % slower): made at the first one,
 // out of memory that is plainly spare; where they cannot be made (a weight beyond fp16) the steps do without. Nothing is
 // made while the stream is being captured.
-void copies_for_few_rows(Model* m, bool projections, hipStream_t stream) {
+static void copies_for_few_rows(Model* m, hipStream_t stream) {
     const laser_model_desc& d = m->d;
-    projections = projections && !m->w16[0];
+    const bool projections = !m->w16[0];
     if (!m->f16_copies || m->no_few_copies || (!projections && m->wlm16)) return;
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return;
@@ -1001,7 +1001,7 @@ static int verify_impl(laser_model* mh, laser_kv* kh, const int32_t* seq_ids, co
     const int32_t* ids_dev = nullptr;
     if ((rc = kv->stage_ids(seq_ids, B, stream, &ids_dev))) return rc;
     const bool fused = m->use_fused && fused_supported(m, B, K, max_ub);
-    if (fused || (B * R > 16 && B * R <= kSkinnyMaxRows)) copies_for_few_rows(m, true, stream);
+    if (fused || (B * R > 16 && B * R <= kSkinnyMaxRows)) copies_for_few_rows(m, stream);
     if (fused) {
         if (parent)          // token tree: positions (depth) and ancestor masks of the rows
             hipLaunchKernelGGL(rows_kernel, dim3((B * R + 255) / 256), dim3(256), 0, stream, parent, draft_len, ids_dev, kv->len, B, R,
@@ -1010,7 +1010,7 @@ static int verify_impl(laser_model* mh, laser_kv* kh, const int32_t* seq_ids, co
                        accept_path, logits_dbg, max_ub, stream);
     } else {
         if ((rc = forward(m, kv, ids_dev, pending, drafts, parent, draft_len, B, K, max_ub, stream))) return rc;
-        rc = run_head(m, m->xn, drafts, parent, draft_len, B, K, topk, p, mode, accept_len, out_tokens, accept_path, logits_dbg, stream);
+        rc = run_head(m, true, m->xn, drafts, parent, draft_len, B, K, topk, p, mode, accept_len, out_tokens, accept_path, logits_dbg, stream);
     }
     // only a step that has been enqueued may be committed
     if (rc == LASER_OK)
@@ -1042,7 +1042,7 @@ extern "C" int laser_verify_head(laser_model* mh, const uint16_t* h, const int32
     if (rc) return rc;
     if (B == 0) return LASER_OK;
     LASER_REQUIRE(h != nullptr, LASER_E_INVALID_ARG, "h is NULL");
-    return run_head(m, h, drafts, nullptr, draft_len, B, K, topk, p, mode, accept_len, out_tokens, nullptr, logits_dbg, (hipStream_t)stream);
+    return run_head(m, false, h, drafts, nullptr, draft_len, B, K, topk, p, mode, accept_len, out_tokens, nullptr, logits_dbg, (hipStream_t)stream);
 }
 
 extern "C" int laser_verify_head_static(laser_model* mh, const uint16_t* h, const int32_t* drafts, const int32_t* draft_len,

@@ -115,7 +115,5 @@ struct Model {
 // `mats` matrices [N][Kd] in a row, and their fp16 copies for the tiled kernels (model.hip)
 struct WidenSource { const uint16_t* w; int mats, N, Kd; };
 int widen_copies(const WidenSource* src, int n, uint16_t** dst, hipStream_t stream);
-// Up to 80 rows: the head's copy and, if asked for, the projections', where they can be made (model.hip)
-void copies_for_few_rows(Model* m, bool projections, hipStream_t stream);
 
 }  // namespace laser

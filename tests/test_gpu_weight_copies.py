@@ -1,0 +1,70 @@
+"""Which weights a call reads -- the caller's matrices or the fp16 copies the handle makes of them -- and how long the copies' memory lives."""
+import pytest
+import torch
+
+import synth
+from tests import gpu_util as gu
+
+
+pytestmark = pytest.mark.gpu
+
+
+def _head(d, V, rows, seed=1):
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    w = torch.empty((V, d), dtype=torch.bfloat16, device="cuda").normal_(0.0, 0.1, generator=gen)
+    h = torch.empty((1, rows, d), dtype=torch.float16, device="cuda").normal_(generator=gen)
+    return w, h, torch.zeros((1, rows - 1), dtype=torch.int32, device="cuda"), torch.full((1,), rows - 1, dtype=torch.int32, device="cuda")
+
+
+@pytest.mark.parametrize("topk", [2, 5])
+@pytest.mark.parametrize("rows", [16, 17, 24, 64])
+def test_the_head_alone_reads_the_callers_matrix(rows, topk):
+    """Up to 80 rows at every call: a matrix changed in place between two calls is seen by the second, which makes no copy."""
+    import paper_2408_05676_amd as laser
+    d, V = 1024, 32768                                                    # a copy would take 64 MB
+    w, h, drafts, n = _head(d, V, rows)
+    model = laser.Model(0, d, 8, 128, V, {"wlm": w}, rows, 1, 0)
+    for turn in range(2):
+        free = torch.cuda.mem_get_info()[0]
+        logits = laser.verify_head(model, h, drafts, n, topk, -1.0, 2, want_logits=True)[2]
+        torch.cuda.synchronize()
+        # (torch itself takes blocks of at most 20 MB for the results)
+        assert free - torch.cuda.mem_get_info()[0] < 48 << 20
+        want = h[0].double() @ w.double().t()
+        # products of fp16 and bf16 are exact in float32, 1024 of them are added in float32
+        assert float((logits[0].double() - want).norm() / want.norm()) <= 1e-5, turn
+        w.copy_(w.flip(0))
+
+
+def _shape():
+    return synth.SHAPES["tiny"].with_(d=256, n_heads=4, ffn=640, vocab=1040)
+
+
+def _model(sh, w, rows):
+    import paper_2408_05676_amd as laser
+    return laser.Model(sh.n_layers, sh.d, sh.n_heads, sh.ffn, sh.vocab, w, rows, rows, 64, eps=sh.eps, rope_base=sh.rope_base)
+
+
+def _step(model, sh, rows, K=0, topk=1):
+    """(accept_len, out_tokens, logits) of a step of that many rows into empty caches."""
+    import paper_2408_05676_amd as laser
+    B = rows // (K + 1)
+    kv = gu.make_kv(sh, n_pages=4 * B, max_seqs=B, max_pages_per_seq=4)
+    for s in range(B):
+        kv.reserve(s, 64)
+    tok = (torch.arange(B * (K + 1), device="cuda", dtype=torch.int32) * 37 % sh.vocab).view(B, K + 1)
+    n = torch.full((B,), K, dtype=torch.int32, device="cuda")
+    return laser.verify_step(model, kv, list(range(B)), tok[:, 0].contiguous(), tok[:, 1:].contiguous(), n, topk, -1.0, 2, want_logits=True)
+
+
+@pytest.mark.parametrize("topk", [1, 2, 5])
+@pytest.mark.parametrize("rows", [24, 72, 80])
+def test_a_steps_head_on_the_copies(rows, topk):
+    """The copies hold the values the kernels make of the caller's weights: both give the same, bit for bit."""
+    sh = _shape()
+    w, got = gu.gpu_weights(sh), []
+    for copies in (1, 0):
+        model = _model(sh, w, rows)
+        model.set_option("f16_copies", copies)
+        got.append(_step(model, sh, rows, 7, topk))
+    assert all(torch.equal(a, b) for a, b in zip(*got))
