@@ -192,9 +192,10 @@ typedef struct laser_model_desc {
  * fp16 copies of the four projection matrices and of the head matrix (2 bytes per parameter: the weight memory doubles),
  * inside the first step that takes them; that call synchronises the stream. With more than 80 rows it fails with
  * LASER_E_HIP if the memory is not there and with LASER_E_LIMIT if a weight exceeds the fp16 range (|w| > 65280); up to 80
- * rows it then does without, as it does while the stream is being captured and where the copies would take more than a
+ * rows it then does without, as it does where the copies would take more than a
  * quarter of the free memory. laser_verify_head makes its copy with more than 80 rows, and up to there reads the caller's
- * matrix at every call; laser_verify_head_static makes none.
+ * matrix at every call; laser_verify_head_static makes none. No call makes copies while its stream is being captured.
+ * Their memory stays where it is until the handle is destroyed, so that captured graphs may keep reading it.
  * Copies are made once: weights changed in place afterwards are seen only after the option below has been set again.
  * Without copies (option "f16_copies" = 0 makes none) the tiled kernels widen the bf16 weights on the fly (slower).
  * Weights need the alignment of their elements only; off the 16-byte grid and without copies they take kernels that stage
@@ -358,8 +359,9 @@ int laser_generate(laser_model* model, laser_kv* kv, const laser_pool* pool, con
  * shape or the workspace cannot take falls back to 1). The parts are added in a fixed order by the
  * kernel that follows, so a given setting is deterministic; different settings may differ in the
  * last bits. Tuning and test knobs: the default is what the benchmark measures.
- * "f16_copies" = 1 (default) or 0: see laser_model_create. Either value drops the copies made so far (the call waits for
- * the device); with 1 the next step that takes them makes them anew.
+ * "f16_copies" = 1 (default) or 0: see laser_model_create. Either value ends the use of the copies made so far; with 1 the
+ * next call that takes them, and whose stream is not being captured, makes them anew in the same memory. A graph captured
+ * before reads that memory: the old weights until then, the new ones afterwards.
  * "mid_waves" = 0 (default): 17..80 rows take the tiled GEMM; 4 or 8: the one that stages rows through
  * registers, with that many waves per workgroup.
  * "tile" = 0 (default: chosen from the launch shape) or i: with more than 16 rows every tiled product takes the i-th entry

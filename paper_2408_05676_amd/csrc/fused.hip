@@ -1573,9 +1573,9 @@ int run_fused(Model* m, KV* kv, const int32_t* ids_dev, const int32_t* pending, 
                   "context of %d tokens needs %d attention splits; the persistent kernel holds %d",
                   max_len_ub + R, B * d.n_heads * S, ws->bh_cap);      // fused_supported() has already ruled this out
     FusedArgs a{};
-    const bool w16 = m->w16[0] && m->wlm16;
+    const bool w16 = m->w16[0] && m->w16[4];
     a.wqkv = w16 ? m->w16[0] : d.wqkv; a.wo = w16 ? m->w16[1] : d.wo; a.wgu = w16 ? m->w16[2] : d.wgu; a.wdown = w16 ? m->w16[3] : d.wdown;
-    a.emb = d.emb; a.wlm = w16 ? m->wlm16 : d.wlm;
+    a.emb = d.emb; a.wlm = w16 ? m->w16[4] : d.wlm;
     a.g1 = d.g1; a.g2 = d.g2; a.gf = d.gf;
     a.L = d.n_layers; a.d = d.d_model; a.H = d.n_heads; a.dh = m->dh; a.F = d.ffn; a.V = d.vocab; a.eps = d.eps;
     a.rope = m->rope;

@@ -329,10 +329,8 @@ static int run_head_bufs(Model* m, const uint16_t* few16, const uint16_t* h, con
         launch_gemm_mid<EPI_HEAD, false>(t, pl, stream);
     } else {
         hp.chunks = (V + 127) / 128;
-        if (m->f16_copies && !m->wlm16) {          // first many-row head: widen the head matrix to fp16 once
-            const WidenSource src{m->d.wlm, 1, V, dm};
-            const int rc = widen_copies(&src, 1, &m->wlm16, stream);
-            if (rc) return rc;
+        if (m->f16_copies && !m->w16[4]) {         // first many-row head: widen the head matrix to fp16 once
+            if (const int rc = widen_copies(m, kHeadMatrix, stream)) return rc;
         }
         if (!on_16_byte_grid(h)) {
             const size_t n8 = (size_t)M * dm / 8;
@@ -341,9 +339,9 @@ static int run_head_bufs(Model* m, const uint16_t* few16, const uint16_t* h, con
         }
         int ncu = 0;
         LASER_HIP_CHECK(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, 0));
-        GemmTileArgs t{m->wlm16 ? m->wlm16 : m->d.wlm, h, nullptr, M, V, dm, 0, 0, 1, nullptr, nullptr, hp};
+        GemmTileArgs t{m->w16[4] ? m->w16[4] : m->d.wlm, h, nullptr, M, V, dm, 0, 0, 1, nullptr, nullptr, hp};
         t.want_tile = m->tile;
-        launch_tile_head(t, m->wlm16 != nullptr, ncu, stream);
+        launch_tile_head(t, m->w16[4] != nullptr, ncu, stream);
     }
     AcceptArgs aa{hb.hp_max, hb.hp_sum, hb.hp_arg, hb.hp_topv, hb.hp_topi, hb.cand_beg, hb.cand_cnt, hb.cand_x, hb.cand_lx, hb.node_cand,
                   tokens, parent, n_nodes, M, B, K, hp.chunks, topk, mode, p, hb.row_mx, hb.row_sum, hb.row_arg, hb.cand_rank,
@@ -361,7 +359,7 @@ int run_head(Model* m, bool few_copy, const uint16_t* h, const int32_t* tokens, 
              hipStream_t stream) {
     HeadBufs hb{m->cand_beg, m->cand_cnt, m->cand_x, m->node_cand, m->cand_lx, m->hp_max, m->hp_sum, m->hp_arg, m->hp_topv, m->hp_topi,
                 m->row_mx, m->row_sum, m->row_arg, m->cand_rank};
-    return run_head_bufs(m, few_copy ? m->wlm16 : nullptr, h, tokens, parent, n_nodes, B, K, topk, p, mode, accept_len, out_tokens, accept_path, logits_dbg, hb, stream);
+    return run_head_bufs(m, few_copy ? m->w16[4] : nullptr, h, tokens, parent, n_nodes, B, K, topk, p, mode, accept_len, out_tokens, accept_path, logits_dbg, hb, stream);
 }
 
 // ---- the head without any allocation ------------------------------------------------------------------------

@@ -287,23 +287,37 @@ __global__ __launch_bounds__(256) void widen_weights_kernel(const uint16_t* __re
     if (bad) atomicAdd(overflow, bad);
 }
 
-// fp16 copies of `n` groups of bf16 matrices for the tiled many-row kernels (made once, at the first call that needs them; that
-// call synchronises the stream). All or nothing: on failure nothing is kept. LASER_E_LIMIT if a weight does not fit fp16.
-int widen_copies(const WidenSource* src, int n, uint16_t** dst, hipStream_t stream) {
-    uint16_t* cp[4] = {nullptr, nullptr, nullptr, nullptr};
+static bool capturing(hipStream_t stream) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone;
+}
+
+// The copies named by `which` (made at the first call that needs them; that call synchronises the stream). All or
+// nothing: on failure none of them is kept. LASER_E_LIMIT if a weight does not fit fp16. Copies that were dropped
+// are made again in the memory they had. While the stream is being captured none are made: the call takes the caller's weights.
+int widen_copies(Model* m, unsigned which, hipStream_t stream) {
+    if (capturing(stream)) return LASER_OK;
+    const laser_model_desc& d = m->d;
+    const struct { const uint16_t* w; int mats, N, Kd; } src[5] = {
+        {d.wqkv, d.n_layers, 3 * d.d_model, d.d_model}, {d.wo, d.n_layers, d.d_model, d.d_model}, {d.wgu, d.n_layers, 2 * d.ffn, d.d_model},
+        {d.wdown, d.n_layers, d.d_model, d.ffn}, {d.wlm, 1, d.vocab, d.d_model}};
+    uint16_t* fresh[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};
     int* flag = nullptr;
-    auto drop = [&] { for (int i = 0; i < n; ++i) if (cp[i]) (void)hipFree(cp[i]); if (flag) (void)hipFree(flag); };
+    auto elems = [&](int i) { return (size_t)src[i].mats * src[i].N * src[i].Kd; };
+    auto drop = [&] { for (uint16_t* p : fresh) if (p) (void)hipFree(p); if (flag) (void)hipFree(flag); };
     hipError_t e = hipMalloc((void**)&flag, sizeof(int));
-    for (int i = 0; i < n && e == hipSuccess; ++i) e = hipMalloc((void**)&cp[i], (size_t)src[i].mats * src[i].N * src[i].Kd * 2);
+    for (int i = 0; i < 5 && e == hipSuccess; ++i)
+        if ((which >> i & 1) && !m->w16_mem[i]) e = hipMalloc((void**)&fresh[i], elems(i) * 2);
     if (e == hipSuccess) e = hipMemsetAsync(flag, 0, sizeof(int), stream);
     if (e != hipSuccess) {
         drop();
         set_error("allocating the fp16 weight copies failed: %s", hipGetErrorString(e));
         return LASER_E_HIP;
     }
-    for (int i = 0; i < n; ++i)
-        hipLaunchKernelGGL(widen_weights_kernel, dim3(2048), dim3(256), 0, stream, src[i].w, cp[i], src[i].N, src[i].Kd,
-                           (size_t)src[i].mats * src[i].N * src[i].Kd / 8, flag);
+    for (int i = 0; i < 5; ++i)
+        if (which >> i & 1)
+            hipLaunchKernelGGL(widen_weights_kernel, dim3(2048), dim3(256), 0, stream, src[i].w, m->w16_mem[i] ? m->w16_mem[i] : fresh[i],
+                               src[i].N, src[i].Kd, elems(i) / 8, flag);
     int bad = 0;
     e = hipMemcpyAsync(&bad, flag, sizeof(int), hipMemcpyDeviceToHost, stream);
     if (e == hipSuccess) e = hipStreamSynchronize(stream);
@@ -314,7 +328,11 @@ int widen_copies(const WidenSource* src, int n, uint16_t** dst, hipStream_t stre
         return LASER_E_LIMIT;
     }
     (void)hipFree(flag);
-    for (int i = 0; i < n; ++i) dst[i] = cp[i];
+    for (int i = 0; i < 5; ++i)
+        if (which >> i & 1) {
+            if (fresh[i]) m->w16_mem[i] = fresh[i];
+            m->w16[i] = m->w16_mem[i];
+        }
     return LASER_OK;
 }
 
@@ -746,28 +764,16 @@ __global__ void rope_table_kernel(float2* tab, int max_pos, int half, int dh, do
 }
 
 // ------------------------------------------------------------------------------------------------
-// fp16 copies of the four projection matrices, made once (same rounding as the kernels' own)
-static int widen_projections(Model* m, hipStream_t stream) {
-    const laser_model_desc& d = m->d;
-    const WidenSource src[4] = {{d.wqkv, d.n_layers, 3 * d.d_model, d.d_model}, {d.wo, d.n_layers, d.d_model, d.d_model},
-                                {d.wgu, d.n_layers, 2 * d.ffn, d.d_model}, {d.wdown, d.n_layers, d.d_model, d.ffn}};
-    return widen_copies(src, 4, m->w16, stream);
-}
-
 // The copies for steps of up to 80 rows, whose kernels take the caller's weights as well (10 % slower): made at the first one,
 // out of memory that is plainly spare; where they cannot be made (a weight beyond fp16) the steps do without. Nothing is
 // made while the stream is being captured.
 static void copies_for_few_rows(Model* m, hipStream_t stream) {
     const laser_model_desc& d = m->d;
-    const bool projections = !m->w16[0];
-    if (!m->f16_copies || m->no_few_copies || (!projections && m->wlm16)) return;
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return;
-    const size_t dm = d.d_model, need = (m->wlm16 ? 0 : (size_t)d.vocab * dm * 2) + (projections ? (size_t)d.n_layers * (4 * dm * dm + 3 * dm * d.ffn) * 2 : 0);
+    if (!m->f16_copies || m->no_few_copies || (m->w16[0] && m->w16[4]) || capturing(stream)) return;
+    const size_t dm = d.d_model, need = (m->w16_mem[4] ? 0 : (size_t)d.vocab * dm * 2) + (m->w16_mem[0] ? 0 : (size_t)d.n_layers * (4 * dm * dm + 3 * dm * d.ffn) * 2);
     size_t free_b = 0, total_b = 0;
-    const WidenSource lm{d.wlm, 1, d.vocab, d.d_model};
     m->no_few_copies = hipMemGetInfo(&free_b, &total_b) != hipSuccess || need > free_b / 4 ||
-                       (projections && widen_projections(m, stream) != LASER_OK) || (!m->wlm16 && widen_copies(&lm, 1, &m->wlm16, stream) != LASER_OK);
+                       (!m->w16[0] && widen_copies(m, kProjections, stream) != LASER_OK) || (!m->w16[4] && widen_copies(m, kHeadMatrix, stream) != LASER_OK);
     if (m->no_few_copies) (void)hipGetLastError();
 }
 
@@ -781,7 +787,7 @@ static int forward(Model* m, KV* kv, const int32_t* ids_dev, const int32_t* pend
     hipLaunchKernelGGL(embed_rmsnorm_kernel, dim3(M), dim3(256), 0, stream, d.emb, d.g1, pending, drafts, draft_len,
                        R, dm, d.vocab, d.eps, m->x, m->xn, m->xn_lo);
     if (M > kSkinnyMaxRows && m->f16_copies && !m->w16[0]) {
-        if (const int rc = widen_projections(m, stream)) return rc;
+        if (const int rc = widen_copies(m, kProjections, stream)) return rc;
     }
     if (M > 16 && !m->kpart) {
         // workspace for reduction-split partial results: up to 8 parts of [max_rows][d] or 2 of [max_rows][3 d], 4 up to 80 rows
@@ -877,7 +883,7 @@ using namespace laser;
 extern "C" int laser_model_destroy(laser_model* h) {
     if (!h) return LASER_OK;
     Model* m = reinterpret_cast<Model*>(h);
-    void* ptrs[] = {m->kpart, m->wlm16, m->w16[0], m->w16[1], m->w16[2], m->w16[3], m->x, m->xn, m->q_lo, m->qkv, m->q, m->attn, m->act, m->row_pos, m->att_part, m->rope, m->hp_max,
+    void* ptrs[] = {m->kpart, m->w16_mem[0], m->w16_mem[1], m->w16_mem[2], m->w16_mem[3], m->w16_mem[4], m->x, m->xn, m->q_lo, m->qkv, m->q, m->attn, m->act, m->row_pos, m->att_part, m->rope, m->hp_max,
                     m->hp_sum, m->hp_arg, m->hp_topv, m->hp_topi, m->cand_beg, m->cand_cnt, m->cand_x, m->node_cand, m->cand_lx, m->row_slot, m->row_anc,
                     m->row_mx, m->row_sum, m->row_arg, m->cand_rank};
     for (void* p : ptrs) if (p) (void)hipFree(p);
@@ -1095,10 +1101,7 @@ extern "C" int laser_model_set_option(laser_model* mh, const char* name, int val
     if (std::string(name) == "f16_copies") {
         LASER_REQUIRE(value == 0 || value == 1, LASER_E_INVALID_ARG, "f16_copies must be 0 or 1");
         m->f16_copies = value;
-        for (uint16_t** p : {&m->w16[0], &m->w16[1], &m->w16[2], &m->w16[3], &m->wlm16}) {     // (hipFree waits for the steps that read them)
-            if (*p) LASER_HIP_CHECK(hipFree(*p));
-            *p = nullptr;
-        }
+        for (uint16_t*& p : m->w16) p = nullptr;      // (their memory stays: captured graphs read it)
         m->no_few_copies = false;
         return LASER_OK;
     }

@@ -96,11 +96,12 @@ struct Model {
     void* fused_ws = nullptr;          // workspace of the persistent few-row kernel (fused.hip)
     int use_fused = 1;                 // 0 forces the generic multi-kernel path
     int fused_trace = 0;               // 1: thread 0 of every workgroup stamps the wall clock at phase edges
-    uint16_t* w16[4] = {nullptr, nullptr, nullptr, nullptr};   // fp16 copies of wqkv, wo, wgu, wdown for the tiled and the persistent kernels,
-                                                               // laid out by fragments ([Kd / 32][N][32] per layer), made
-                                                               // at the first step that takes them
+    // fp16 copies of the weights for the tiled and the persistent kernels, laid out by fragments ([Kd / 32][N][32] per layer): wqkv, wo,
+    // wgu, wdown, wlm. Made at the first step that takes them; NULL: not made, or dropped by option "f16_copies".
+    uint16_t* w16[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};
+    uint16_t* w16_mem[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};   // their memory, from the first time they are made
+                                       // until the handle is destroyed: a captured graph holds its address
     bool no_few_copies = false;        // they could not be made for a step of up to 80 rows, which does without
-    uint16_t* wlm16 = nullptr;         // fp16 copy of the head matrix, likewise
     int f16_copies = 1;                // 0: the tiled kernels stream the bf16 weights and widen them in the loop (no copies)
     float* kpart = nullptr;            // partial results of reduction-split tiled GEMMs (many-row path), [parts][rows][N]
     size_t kpart_floats = 0;
@@ -112,8 +113,8 @@ struct Model {
     int split_ffn = 0;                 // 1: the many-row (tiled) gate/up product also takes split activations
 };
 
-// `mats` matrices [N][Kd] in a row, and their fp16 copies for the tiled kernels (model.hip)
-struct WidenSource { const uint16_t* w; int mats, N, Kd; };
-int widen_copies(const WidenSource* src, int n, uint16_t** dst, hipStream_t stream);
+constexpr unsigned kProjections = 0xF, kHeadMatrix = 0x10;      // bits of w16
+// Makes the copies named by the mask (model.hip).
+int widen_copies(Model* m, unsigned which, hipStream_t stream);
 
 }  // namespace laser

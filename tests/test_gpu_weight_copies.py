@@ -68,3 +68,64 @@ def test_a_steps_head_on_the_copies(rows, topk):
         model.set_option("f16_copies", copies)
         got.append(_step(model, sh, rows, 7, topk))
     assert all(torch.equal(a, b) for a, b in zip(*got))
+
+
+@pytest.mark.parametrize("what", ["head 96", "step 24", "step 96"])
+def test_captured_graphs_after_the_option_is_set(what):
+    """A graph keeps the addresses of the copies. Setting the option leaves their memory alone; the next call makes the copies
+    anew in the same place, and what is captured before that takes the caller's weights."""
+    import paper_2408_05676_amd as laser
+    kind, rows = what.split()[0], int(what.split()[1])
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        if kind == "head":
+            w, h, drafts, n = _head(256, 1040, 12)
+            h, drafts, n = h.repeat(8, 1, 1), drafts.repeat(8, 1), n.repeat(8)
+            weights = {"wlm": w}
+            model = laser.Model(0, 256, 4, 128, 1040, weights, rows, 8, 0)
+            out = [torch.empty(8, dtype=torch.int32, device="cuda"), torch.empty((8, 12), dtype=torch.int32, device="cuda")]
+
+            def call():
+                return laser.verify_head(model, h, drafts, n, 2, -1.0, 2, want_logits=True, out=out)[2]
+        else:
+            sh = _shape()
+            weights = gu.gpu_weights(sh)
+            model = _model(sh, weights, rows)
+            kv = gu.make_kv(sh, n_pages=rows, max_seqs=rows, max_pages_per_seq=1)
+            for s in range(rows):
+                kv.reserve(s, 16)
+            tok = torch.arange(rows, device="cuda", dtype=torch.int32)
+            none, n = torch.empty((rows, 0), dtype=torch.int32, device="cuda"), torch.zeros(rows, dtype=torch.int32, device="cuda")
+            out = [torch.empty(rows, dtype=torch.int32, device="cuda"), torch.empty((rows, 1), dtype=torch.int32, device="cuda")]
+
+            def call():
+                return laser.verify_step(model, kv, list(range(rows)), tok, none, n, 2, -1.0, 2, want_logits=True, out=out)[2]
+
+        def capture():
+            stream.synchronize()
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph, stream=stream):
+                logits = call()
+            return lambda: (graph.replay(), stream.synchronize(), logits.clone())[2]
+
+        old = call().clone()
+        first = capture()
+        assert torch.equal(first(), old)
+        for value in (1, 0, 1):
+            model.set_option("f16_copies", value)
+            junk = [torch.full((t.numel(),), 7.0, dtype=torch.bfloat16, device="cuda") for t in weights.values()]   # would take freed memory
+            assert torch.equal(first(), old), value
+            del junk
+        for t in weights.values():
+            if t.dtype == torch.bfloat16:
+                t.copy_(t.flip(-2))
+        model.set_option("f16_copies", 1)
+        second = capture()                                  # no copies: the caller's weights
+        live = second()
+        new = call().clone()
+        assert not torch.equal(new, old) and torch.equal(first(), new)
+        model.set_option("f16_copies", 0)
+        assert torch.equal(call(), live) and torch.equal(second(), live) and torch.equal(first(), new)
+        # (above 80 rows other tiles take the caller's weights: sums in another order)
+        assert float((live.double() - new.double()).norm() / new.double().norm()) <= 1.6e-3
+        stream.synchronize()
