@@ -192,8 +192,8 @@ typedef struct laser_model_desc {
  * fp16 copies of the four projection matrices and of the head matrix (2 bytes per parameter: the weight memory doubles),
  * inside the first step that takes them; that call synchronises the stream. With more than 80 rows it fails with
  * LASER_E_HIP if the memory is not there and with LASER_E_LIMIT if a weight exceeds the fp16 range (|w| > 65280); up to 80
- * rows it then does without, as it does where the copies would take more than a
- * quarter of the free memory. laser_verify_head makes its copy with more than 80 rows, and up to there reads the caller's
+ * rows it then does without, as it does where the copies would take more than a quarter of the free memory, and no step of
+ * so few rows tries again until the option below is set. laser_verify_head makes its copy with more than 80 rows, and up to there reads the caller's
  * matrix at every call; laser_verify_head_static makes none. No call makes copies while its stream is being captured.
  * Their memory stays where it is until the handle is destroyed, so that captured graphs may keep reading it.
  * Copies are made once: weights changed in place afterwards are seen only after the option below has been set again.

@@ -765,15 +765,15 @@ __global__ void rope_table_kernel(float2* tab, int max_pos, int half, int dh, do
 
 // ------------------------------------------------------------------------------------------------
 // The copies for steps of up to 80 rows, whose kernels take the caller's weights as well (10 % slower): made at the first one,
-// out of memory that is plainly spare; where they cannot be made (a weight beyond fp16) the steps do without. Nothing is
-// made while the stream is being captured.
+// out of memory that is plainly spare; where they cannot be made (a weight beyond fp16 in any of the five matrices) none is, and
+// the steps do without from then on. Nothing is made while the stream is being captured.
 static void copies_for_few_rows(Model* m, hipStream_t stream) {
     const laser_model_desc& d = m->d;
-    if (!m->f16_copies || m->no_few_copies || (m->w16[0] && m->w16[4]) || capturing(stream)) return;
+    const unsigned which = (m->w16[0] ? 0 : kProjections) | (m->w16[4] ? 0 : kHeadMatrix);
+    if (!m->f16_copies || m->no_few_copies || !which || capturing(stream)) return;
     const size_t dm = d.d_model, need = (m->w16_mem[4] ? 0 : (size_t)d.vocab * dm * 2) + (m->w16_mem[0] ? 0 : (size_t)d.n_layers * (4 * dm * dm + 3 * dm * d.ffn) * 2);
     size_t free_b = 0, total_b = 0;
-    m->no_few_copies = hipMemGetInfo(&free_b, &total_b) != hipSuccess || need > free_b / 4 ||
-                       (!m->w16[0] && widen_copies(m, kProjections, stream) != LASER_OK) || (!m->w16[4] && widen_copies(m, kHeadMatrix, stream) != LASER_OK);
+    m->no_few_copies = hipMemGetInfo(&free_b, &total_b) != hipSuccess || need > free_b / 4 || widen_copies(m, which, stream) != LASER_OK;
     if (m->no_few_copies) (void)hipGetLastError();
 }
 

@@ -129,3 +129,25 @@ def test_captured_graphs_after_the_option_is_set(what):
         # (above 80 rows other tiles take the caller's weights: sums in another order)
         assert float((live.double() - new.double()).norm() / new.double().norm()) <= 1.6e-3
         stream.synchronize()
+
+
+@pytest.mark.parametrize("name", ["wdown", "wlm"])
+@pytest.mark.parametrize("rows", [4, 24])
+def test_all_copies_or_none(name, rows):
+    """One weight beyond fp16, in the last projection or in the head: up to 80 rows a step keeps no copy of any matrix."""
+    import paper_2408_05676_amd as laser
+    sh = synth.SHAPES["tiny"].with_(n_layers=6, d=1024, n_heads=8, ffn=4096, vocab=16384)        # copies of 200 and 32 MB
+    w = gu.gpu_weights(sh)
+    w[name].view(-1)[12345] = 1e5
+    taken, got = [], []
+    for copies in (0, 1):
+        model = _model(sh, w, 96)
+        model.set_option("f16_copies", copies)
+        torch.cuda.synchronize()
+        free = torch.cuda.mem_get_info()[0]
+        got.append(_step(model, sh, rows)[2])
+        torch.cuda.synchronize()
+        taken.append(free - torch.cuda.mem_get_info()[0])
+    assert torch.equal(*got) and taken[1] <= taken[0] + (8 << 20), taken
+    with pytest.raises(laser.LaserError, match="fp16 range"):
+        _step(model, sh, 96)
