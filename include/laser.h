@@ -164,7 +164,13 @@ int laser_own_text_append(int32_t* own_tokens, int32_t* own_len, int own_cap, co
  * Pre-norm decoder: RMSNorm, rotary positions (element i paired with i + head_dim/2), multi-head
  * causal attention, SwiGLU FFN, no biases, untied embedding / output head.
  * All weight pointers are [dev], row-major [out_features][in_features], bf16 unless noted, and
- * must stay valid and unchanged while the handle lives.
+ * must stay valid and unchanged while the handle lives. A program that changes them in place between calls all the same
+ * has to set option "f16_copies" after each change: the next call of every kind then uses the new values. Until it does, calls
+ * mix old and new, because the handle keeps fp16 copies of the matrices (see laser_model_create). Steps on the persistent kernel and
+ * steps of more than 16 rows use the copies they find, laser_verify_head with more than 80 rows its copy of wlm; steps of up
+ * to 16 rows on the general path (option "fused" = 0, or contexts beyond what the persistent kernel holds),
+ * laser_verify_head up to 80 rows and laser_verify_head_static read the caller's matrices; emb and the gains are
+ * always read from the caller's arrays.
  */
 typedef struct laser_model_desc {
     int32_t n_layers, d_model, n_heads, ffn, vocab;
@@ -196,7 +202,7 @@ typedef struct laser_model_desc {
  * so few rows tries again until the option below is set. laser_verify_head makes its copy with more than 80 rows, and up to there reads the caller's
  * matrix at every call; laser_verify_head_static makes none. No call makes copies while its stream is being captured.
  * Their memory stays where it is until the handle is destroyed, so that captured graphs may keep reading it.
- * Copies are made once: weights changed in place afterwards are seen only after the option below has been set again.
+ * Copies are made once and not compared with the weights again.
  * Without copies (option "f16_copies" = 0 makes none) the tiled kernels widen the bf16 weights on the fly (slower).
  * Weights need the alignment of their elements only; off the 16-byte grid and without copies they take kernels that stage
  * them through registers (slower). */

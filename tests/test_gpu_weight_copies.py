@@ -151,3 +151,32 @@ def test_all_copies_or_none(name, rows):
     assert torch.equal(*got) and taken[1] <= taken[0] + (8 << 20), taken
     with pytest.raises(laser.LaserError, match="fp16 range"):
         _step(model, sh, 96)
+
+
+@pytest.mark.parametrize("rows", [4, 24, 96])
+def test_weights_changed_in_place_without_and_with_the_option(rows):
+    """Which calls see the change before the option is set, and that every route sees it afterwards."""
+    import paper_2408_05676_amd as laser
+    sh = _shape()
+    w = gu.gpu_weights(sh)
+    new = {**w, "wqkv": w["wqkv"].flip(1).contiguous(), "wlm": w["wlm"].flip(0).contiguous()}
+    h = torch.ones((1, 12, sh.d), dtype=torch.float16, device="cuda")
+    drafts, n = torch.zeros((1, 11), dtype=torch.int32, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda")
+
+    def all_routes(model):
+        got = []
+        for fused in (1, 0):
+            model.set_option("fused", fused)
+            got.append(_step(model, sh, rows)[2])
+        return got + [laser.verify_head(model, h, drafts, n, 2, -1.0, 2, want_logits=True)[2]]
+
+    want = all_routes(_model(sh, new, max(rows, 12)))
+    model = _model(sh, w, max(rows, 12))
+    old = all_routes(model)
+    w["wqkv"].copy_(new["wqkv"])
+    w["wlm"].copy_(new["wlm"])
+    kept = [True, rows > 16, False]                       # the step, the step on the general path, the head alone
+    for got, before, after, copies in zip(all_routes(model), old, want, kept):
+        assert torch.equal(got, before if copies else after) and not torch.equal(before, after)
+    model.set_option("f16_copies", 1)
+    assert all(torch.equal(got, after) for got, after in zip(all_routes(model), want))
