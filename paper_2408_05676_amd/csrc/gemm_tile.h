@@ -123,13 +123,14 @@ void gemm_tile_kernel(GemmTileArgs a) {
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds + wave * 1024;
     const uint32_t last = lds0 + (PIECES - 1 - wave) * 1024;                 // (p = PIECES - 1)
     uint32_t lslot = 0;                                                     // LDS offset of the slot being filled
-    // Load j of the stage being requested.
+    // Load j of the stage being requested. m0 = the piece's LDS byte address, one wait state before its use. The compiler warns that m0
+    // is a reserved register which it does not preserve around the statement: nothing else in this kernel uses it.
     auto issue = [&](auto jc) {
         constexpr int j = decltype(jc)::value;
         const uint64_t base = j < WPW ? wbase : j < XPW ? xbase : lbase;
         const u32x4 srd{(uint32_t)base, (uint32_t)(base >> 32), 0xFFFFFFFFu, 0x00020000u};
         const uint32_t vo = voff[j], at = (PIECES % NW != 0 && j == LPS - 1 && wave + j * NW >= PIECES ? last : lds0 + j * NW * 1024) + lslot;
-        asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %2, 0 offen lds" ::"v"(vo), "s"(at), "s"(srd) : "memory");
+        asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %2, 0 offen lds" ::"v"(vo), "s"(at), "s"(srd) : "memory", "m0");
     };
     // On to the next stage. Requests past the last step repeat it: nobody reads what they bring, but the counts stay uniform.
     int kreq = 0;

@@ -69,6 +69,25 @@ def test_the_reader_sees_a_write_that_is_too_close():
     assert violations(text % 9)[0] and not violations(text % 10)[0]
 
 
+def other_uses_of_m0(listing):
+    """Instructions of the kernels that write m0 in inline assembly (for their loads into LDS) which read it, or write it in any other
+    way: the compiler does not preserve m0 around those statements."""
+    found, kernel = [], None
+    for line in listing.splitlines():
+        head = re.match(r"^[0-9a-f]+ <(.*)>:$", line)
+        kernel = head[1] if head else kernel
+        ins = line.split("//")[0].strip()
+        if kernel and re.search(r"gemm_tile_kernel|verify_fused_kernel", kernel) and re.search(r"\bm0\b", ins) and not head:
+            if not re.fullmatch(r"s_mov_b32 m0, (?!m0)\S+", ins):
+                found.append((kernel, ins))
+    return found
+
+
+def test_the_reader_sees_other_uses_of_m0():
+    text = "0000 <gemm_tile_kernel>:\n\ts_mov_b32 m0, s3 // 00\n\t%s // 04\n"
+    assert not other_uses_of_m0(text % "s_nop 0") and other_uses_of_m0(text % "s_mov_b32 s4, m0") and other_uses_of_m0(text % "s_add_u32 m0, m0, s1")
+
+
 @pytest.mark.skipif(not os.path.exists(OBJDUMP), reason="no disassembler")
 def test_waits_of_the_built_kernels(tmp_path):
     from paper_2408_05676_amd import build as b
@@ -83,5 +102,6 @@ def test_waits_of_the_built_kernels(tmp_path):
         bad, n = violations(r.stdout)
         total += n
         found.update(bad)
+        assert not other_uses_of_m0(r.stdout)
     assert total > 5000, "no matrix instructions found"
     assert not found, {k: v[:2] for k, v in found.items()}
