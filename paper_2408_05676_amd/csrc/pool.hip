@@ -29,6 +29,7 @@ namespace laser {
 // ------------------------------------------------------------------------------------ kernel
 constexpr int kCand = 512;         // occurrences a wave keeps in LDS (more: streamed from the index, re-checked against the chain); see retrieve_kernel
 constexpr int kVote = 512;         // vote-table slots (power of two; wider votes are partitioned)
+constexpr int kWideVote = 1024;    // ... up to kFourGroupsMax contexts, for votes out of LDS that overflow the smaller table
 // Groups of 64 occurrences whose loads a vote over a streamed run has in flight together. A wave alone waits for memory: four.
 // Beyond 1024 contexts the waves of a compute unit cover each other's waits and four groups each outgrow its cache: one. A run
 // of 10000 occurrences, chains of 16, one group / four, us: 8 contexts 12075 / 9417, 1024 contexts 12278 / 10199, 2048
@@ -64,25 +65,24 @@ struct RetrieveArgs {
 // their own, K = 1 / 4 / 16: ballots alone 47.8 / 48.8 / 56.4 us, now 14.6 / 14.3 / 27.4; votes by the table alone 14.1 /
 // 20.1 / 45.0. Occurrences that agree but for a tenth per step: ballots alone 10.1 / 11.1 / 20.0, now 12.5 / 9.6 / 20.3,
 // the table alone 12.0 / 29.4 / 75.2.
-constexpr int follow_table(int q) { return q > 4 ? 64 * q : kVote; }       // slots: as many as the 64 q voters or more (each may bring a token of its own)
 template <int Q, int kAhead, bool OWN>
 __device__ __forceinline__ int follow_lanes(const RetrieveArgs& a, const uint32_t* cand, const uint32_t* cand_end, uint32_t m, const uint32_t* own_cand,
                                    const int32_t* own, uint32_t own_len, uint32_t mo, int j0, int* chain, int* vote_tok, int* vote_cnt,
                                    uint32_t& lane_min, uint32_t& lane_own) {
-    constexpr int kBallots = 8, kTable = follow_table(Q);
+    constexpr int kBallots = 8;
+    static_assert(64 * Q < kVote, "every voter may bring a token of its own");
     const int lane = threadIdx.x;
     uint32_t e[Q], end[Q];
     const int32_t* text[Q];
-    uint32_t live = 0, mine_own = 0;               // bit s: occurrence s of this lane (in lane masks, sixteen occurrences ran out of scalar registers)
+    bool live[Q], mine_own[Q];
 #pragma unroll
     for (int s = 0; s < Q; ++s) {
         const uint32_t i = (uint32_t)(s * 64 + lane);
-        const bool have = i < m + mo, is_own = OWN && have && i >= m;
-        live |= (have ? 1u : 0u) << s;
-        mine_own |= (is_own ? 1u : 0u) << s;
-        e[s] = is_own ? own_cand[OWN ? i - m : 0] : have ? cand[i] : 0u;
-        end[s] = is_own ? own_len : have ? cand_end[i] : 0u;
-        text[s] = is_own ? own : a.P;
+        live[s] = i < m + mo;
+        mine_own[s] = OWN && live[s] && i >= m;
+        e[s] = mine_own[s] ? own_cand[OWN ? i - m : 0] : live[s] ? cand[i] : 0u;
+        end[s] = mine_own[s] ? own_len : live[s] ? cand_end[i] : 0u;
+        text[s] = mine_own[s] ? own : a.P;
     }
     int len = j0 - 1;
     bool more = true;
@@ -94,64 +94,67 @@ __device__ __forceinline__ int follow_lanes(const RetrieveArgs& a, const uint32_
         for (int s = 0; s < Q; ++s)
 #pragma unroll
             for (int q = 0; q < kAhead; ++q)
-                tok[s][q] = ((live >> s) & 1u) && j + q <= a.K && e[s] + (uint32_t)(j + q) < end[s] ? text[s][e[s] + (uint32_t)(j + q)] : 0;
+                tok[s][q] = live[s] && j + q <= a.K && e[s] + (uint32_t)(j + q) < end[s] ? text[s][e[s] + (uint32_t)(j + q)] : 0;
 #pragma unroll
         for (int q = 0; q < kAhead; ++q) {
-            uint32_t rest = 0, win = 0;                // voters not counted yet, the winner's
-            int left = 0;
+            bool ok[Q];
+            uint64_t rest[Q], win[Q];
+            int left = 0;                              // voters not counted yet
 #pragma unroll
             for (int s = 0; s < Q; ++s) {
-                const bool ok = more && ((live >> s) & 1u) && j + q <= a.K && e[s] + (uint32_t)(j + q) < end[s];
-                rest |= (ok ? 1u : 0u) << s;
-                left += __popcll(__ballot(ok));
+                ok[s] = more && live[s] && j + q <= a.K && e[s] + (uint32_t)(j + q) < end[s];
+                rest[s] = __ballot(ok[s]);
+                win[s] = 0;
+                left += __popcll(rest[s]);
             }
             int win_tok = 0, win_cnt = 0, ballots = 0;
-            while (left >= win_cnt) {                  // larger count, then smaller token id: an equal count can still win
-                const uint64_t voters = __ballot(rest != 0);
-                if (!voters) break;
-                if (Q > 1 && ballots++ == kBallots) { left = -1; break; }
-                int mine = 0;                          // a token of this lane that is not counted yet
 #pragma unroll
-                for (int u = Q - 1; u >= 0; --u) mine = ((rest >> u) & 1u) ? tok[u][q] : mine;
-                const int t = __builtin_amdgcn_readlane(mine, __ffsll((unsigned long long)voters) - 1);
-                uint32_t same = 0;
-                int c = 0;
+            for (int s = 0; s < Q; ++s)
+                while (rest[s] && left >= win_cnt) {   // larger count, then smaller token id: an equal count can still win
+                    if (Q > 1 && ballots++ == kBallots) { left = -1; break; }
+                    const int t = __builtin_amdgcn_readlane(tok[s][q], __ffsll((unsigned long long)rest[s]) - 1);
+                    uint64_t same[Q];
+                    int c = 0;
 #pragma unroll
-                for (int u = 0; u < Q; ++u) {
-                    const bool is = ((rest >> u) & 1u) && tok[u][q] == t;
-                    same |= (is ? 1u : 0u) << u;
-                    c += __popcll(__ballot(is));
+                    for (int u = 0; u < Q; ++u) {
+                        same[u] = u < s ? 0ull : __ballot(ok[u] && tok[u][q] == t);
+                        c += __popcll(same[u]);
+                        rest[u] &= ~same[u];
+                    }
+                    left -= c;
+                    if (c > win_cnt || (c == win_cnt && t < win_tok)) {
+                        win_cnt = c; win_tok = t;
+#pragma unroll
+                        for (int u = 0; u < Q; ++u) win[u] = same[u];
+                    }
                 }
-                rest &= ~same;
-                left -= c;
-                if (c > win_cnt || (c == win_cnt && t < win_tok)) { win_cnt = c; win_tok = t; win = same; }
-            }
             if (Q > 1 && left < 0) { open = j + q; win_cnt = 0; }
             if (win_cnt == 0) { more = false; continue; }          // no survivor has a successor left, or K steps are done
             if (lane == 0) chain[j + q - 1] = win_tok;
             len = j + q;
-            live = win;
+#pragma unroll
+            for (int s = 0; s < Q; ++s) live[s] = (win[s] >> lane) & 1ull;
         }
         if (Q > 1 && open) {
             int t[Q];
 #pragma unroll
-            for (int s = 0; s < Q; ++s) t[s] = ((live >> s) & 1u) && e[s] + (uint32_t)open < end[s] ? text[s][e[s] + (uint32_t)open] : -1;
-            for (int i = lane; i < kTable; i += 64) { vote_tok[i] = kEmptyTok; vote_cnt[i] = 0; }
+            for (int s = 0; s < Q; ++s) t[s] = live[s] && e[s] + (uint32_t)open < end[s] ? text[s][e[s] + (uint32_t)open] : -1;
+            for (int i = lane; i < kVote; i += 64) { vote_tok[i] = kEmptyTok; vote_cnt[i] = 0; }
             __syncthreads();
 #pragma unroll
             for (int s = 0; s < Q; ++s)
                 if (t[s] >= 0) {
-                    uint32_t at = fmix32((uint32_t)t[s]) & (kTable - 1);
+                    uint32_t at = fmix32((uint32_t)t[s]) & (kVote - 1);
                     for (;;) {
                         const int was = atomicCAS(&vote_tok[at], kEmptyTok, t[s]);
                         if (was == kEmptyTok || was == t[s]) break;
-                        at = (at + 1) & (kTable - 1);
+                        at = (at + 1) & (kVote - 1);
                     }
                     atomicAdd(&vote_cnt[at], 1);
                 }
             __syncthreads();
             int bt = 0, bc = 0;
-            for (int i = lane; i < kTable; i += 64) {
+            for (int i = lane; i < kVote; i += 64) {
                 const int c = vote_cnt[i], tk = vote_tok[i];
                 if (c > bc || (c == bc && c > 0 && tk < bt)) { bc = c; bt = tk; }
             }
@@ -162,9 +165,8 @@ __device__ __forceinline__ int follow_lanes(const RetrieveArgs& a, const uint32_
             __syncthreads();
             if (lane == 0) chain[open - 1] = bt;
             len = open;
-            live = 0;
 #pragma unroll
-            for (int s = 0; s < Q; ++s) live |= (t[s] == bt ? 1u : 0u) << s;
+            for (int s = 0; s < Q; ++s) live[s] = t[s] == bt;
             next = open + 1;
             more = true;
         }
@@ -172,8 +174,8 @@ __device__ __forceinline__ int follow_lanes(const RetrieveArgs& a, const uint32_
     lane_min = lane_own = 0xFFFFFFFFu;
 #pragma unroll
     for (int s = 0; s < Q; ++s) {
-        if (((live & ~mine_own) >> s) & 1u) lane_min = min(lane_min, e[s]);
-        if (((live & mine_own) >> s) & 1u) lane_own = min(lane_own, e[s]);
+        if (live[s] && !mine_own[s]) lane_min = min(lane_min, e[s]);
+        if (live[s] && mine_own[s]) lane_own = min(lane_own, e[s]);
     }
     return len;
 }
@@ -183,10 +185,10 @@ __device__ __forceinline__ int follow_lanes(const RetrieveArgs& a, const uint32_
 // in LDS (own_cand, position-ascending) and take part in every vote and filter next to the pool's.
 template <bool OWN, int kGroups>
 __global__ __launch_bounds__(64) void retrieve_kernel(RetrieveArgs a) {
-    // Up to kFourGroupsMax contexts a compute unit has few waves and LDS to spare: twice the occurrences are kept, and a lane follows up
-    // to sixteen of them. Eight contexts over runs of some 900 occurrences, chains of 8, thinned by a tenth per step: 139 us streamed, 39 so.
-    constexpr int kCand = kGroups == 4 ? 1024 : laser::kCand, kLanesMax = kGroups == 4 ? 1024 : 256;
-    constexpr int kTable = follow_table(kLanesMax / 64);
+    // Up to kFourGroupsMax contexts a compute unit has few waves and LDS to spare: twice the occurrences are kept, the vote table is
+    // larger, and votes that are likely to agree go by ballot at once (below).
+    constexpr bool kWide = kGroups == 4;
+    constexpr int kCand = kWide ? 1024 : laser::kCand, kTable = kWide ? kWideVote : kVote;
     __shared__ uint32_t cand[kCand];
     // Beside each occurrence kept in LDS: the end of its sequence, and the successor token the current vote read for
     // it (-1: none). The filter that follows a vote then needs no memory round trip at all, the vote one instead of
@@ -277,31 +279,76 @@ __global__ __launch_bounds__(64) void retrieve_kernel(RetrieveArgs a) {
             // ballots pay off for fewer: 64 occurrences that all differ, 2048 lookups, K = 1 / 2: 12.7 / 12.8 us, by the
             // vote table 9.5 / 10.4.
             const int steps = a.K - j + 1;
-            if (in_lds && m + mo <= (steps > 1 ? (uint32_t)kLanesMax : 32u)) {
+            if (in_lds && m + mo <= (steps > 1 ? 256u : 32u)) {
                 in_lanes = true;
                 auto follow = [&](auto q, auto ahead) {
                     len = follow_lanes<decltype(q)::value, decltype(ahead)::value, OWN>(a, cand, cand_end, m, own_cand, own, own_len, mo, j, chain, vote_tok, vote_cnt, lane_min, lane_own);
                 };
                 using std::integral_constant;
                 if (m + mo <= (steps > 2 ? 64u : 32u)) follow(integral_constant<int, 1>{}, integral_constant<int, 8>{});
-                else if (m + mo <= 256u) {
-                    if (steps <= 4) follow(integral_constant<int, 4>{}, integral_constant<int, 1>{});
-                    else follow(integral_constant<int, 4>{}, integral_constant<int, 8>{});
-                } else if constexpr (kLanesMax > 256) {
-                    if (steps <= 4) follow(integral_constant<int, 16>{}, integral_constant<int, 1>{});
-                    else follow(integral_constant<int, 16>{}, integral_constant<int, 8>{});
-                }
+                else if (steps <= 4) follow(integral_constant<int, 4>{}, integral_constant<int, 1>{});
+                else follow(integral_constant<int, 4>{}, integral_constant<int, 8>{});
                 break;
             }
             int win_tok = -1, win_cnt = 0;
+            bool open = true;
+            // More survivors that agreed at the step before (j > 1) are likely to agree again: a ballot per distinct token, sixteen
+            // survivors to a lane; a vote still open after eight of them goes through the table. 1024 contexts, chains of 8, us with the
+            // table alone / with 16 survivors to a lane from the first step to the last / so: 512 occurrences that agree 69 / 24 / 39,
+            // that split over 20 tokens at once 16.1 / 44 / 16.0; 800 thinned by a tenth per step 115 (streamed) / 26 / 46. The second
+            // form paid in ballots and registers whatever the occurrences did, and held up the lookups of few by 3 to 18 %.
+            if constexpr (kWide) {
+                if (in_lds && j > 1 && m + mo <= (uint32_t)kCand) {
+                    constexpr int Q = kCand / 64;
+                    int tok[Q];
+                    uint32_t rest = 0;                     // bit u: this lane's voter u is not counted yet
+                    int left = 0;
+#pragma unroll
+                    for (int u = 0; u < Q; ++u) {
+                        const uint32_t i = u * 64 + lane;
+                        const bool is_own = OWN && i >= m && i < m + mo;
+                        const uint32_t e = is_own ? own_cand[OWN ? i - m : 0] : i < m ? cand[i] : 0u;
+                        const bool ok = e + (uint32_t)j < (is_own ? own_len : i < m ? cand_end[i] : 0u);
+                        tok[u] = ok ? (is_own ? own : a.P)[e + j] : -1;
+                    }
+#pragma unroll
+                    for (int u = 0; u < Q; ++u) {
+                        if (u * 64 + lane < m) cand_tok[u * 64 + lane] = tok[u];
+                        rest |= (tok[u] >= 0 ? 1u : 0u) << u;
+                        left += __popcll(__ballot(tok[u] >= 0));
+                    }
+                    open = false;
+                    int ballots = 0;
+                    while (left >= win_cnt) {              // larger count, then smaller token id: an equal count can still win
+                        const uint64_t voters = __ballot(rest != 0);
+                        if (!voters) break;
+                        if (ballots++ == 8) { open = true; break; }
+                        int mine = 0;
+#pragma unroll
+                        for (int u = Q - 1; u >= 0; --u) mine = ((rest >> u) & 1u) ? tok[u] : mine;
+                        const int t = __builtin_amdgcn_readlane(mine, __ffsll((unsigned long long)voters) - 1);
+                        int c = 0;
+#pragma unroll
+                        for (int u = 0; u < Q; ++u) {
+                            const bool is = tok[u] == t;
+                            rest &= ~((is ? 1u : 0u) << u);
+                            c += __popcll(__ballot(is));
+                        }
+                        left -= c;
+                        if (c > win_cnt || (c == win_cnt && t < win_tok)) { win_cnt = c; win_tok = t; }
+                    }
+                    __syncthreads();
+                }
+            }
             // The table is only as large as this vote can need (4 slots per voter, 64..kVote): clearing and scanning
             // 1024 slots with one wave cost more than the votes of the few dozen occurrences a typical lookup has.
             const uint32_t voters = (in_lds ? m : count) + mo;
             int vsz = 64;
             while (vsz < kVote && (uint32_t)vsz < 4u * voters) vsz *= 2;
-            const int vfill = vsz / 4 * 3;             // distinct tokens beyond which a vote pass is split
             // The vote may need several passes when too many distinct successors show up.
-            for (uint32_t nparts = 1;; nparts *= 2) {
+            for (uint32_t nparts = 1; open;) {
+                // distinct tokens beyond which a vote pass is repeated, with the larger table or split; a slot for every voter is enough
+                const int vfill = (uint32_t)vsz >= voters ? vsz : vsz / 4 * 3;
                 win_tok = -1; win_cnt = 0;
                 bool overflow = false;
                 for (uint32_t part = 0; part < nparts && !overflow; ++part) {
@@ -349,7 +396,7 @@ __global__ __launch_bounds__(64) void retrieve_kernel(RetrieveArgs a) {
                             }
                             if (ok[u]) {
                                 uint32_t hh = fmix32((uint32_t)tok[u]);
-                                if (nparts == 1 || (hh / kVote) % nparts == part) {
+                                if (nparts == 1 || (hh / kTable) % nparts == part) {
                                     uint32_t s = hh & (vsz - 1);
                                     for (int probe = 0; probe < vsz; ++probe) {
                                         int cur = vote_tok[s];
@@ -388,6 +435,8 @@ __global__ __launch_bounds__(64) void retrieve_kernel(RetrieveArgs a) {
                     __syncthreads();
                 }
                 if (!overflow) break;
+                if (kWide && in_lds && vsz < kTable) vsz = kTable;
+                else nparts *= 2;
             }
             if (win_cnt == 0) break;       // no survivor has a successor left
             if (lane == 0) chain[j - 1] = win_tok;
