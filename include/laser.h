@@ -167,10 +167,10 @@ int laser_own_text_append(int32_t* own_tokens, int32_t* own_len, int own_cap, co
  * must stay valid and unchanged while the handle lives. A program that changes them in place between calls all the same
  * has to set option "f16_copies" after each change: the next call of every kind then uses the new values. Until it does, calls
  * mix old and new, because the handle keeps fp16 copies of the matrices (see laser_model_create). Steps on the persistent kernel and
- * steps of more than 16 rows use the copies they find, laser_verify_head with more than 80 rows its copy of wlm; steps of up
- * to 16 rows on the general path (option "fused" = 0, or contexts beyond what the persistent kernel holds),
- * laser_verify_head up to 80 rows and laser_verify_head_static read the caller's matrices; emb and the gains are
- * always read from the caller's arrays.
+ * steps of more than 16 rows use the copies they find (but with 17..80 rows and topk > 2 the caller's wlm), laser_verify_head with
+ * more than 80 rows its copy of wlm; steps of up to 16 rows on the general path (option "fused" = 0, or contexts beyond what the
+ * persistent kernel holds), laser_verify_head up to 80 rows and laser_verify_head_static read the caller's matrices; emb and
+ * the gains are always read from the caller's arrays.
  */
 typedef struct laser_model_desc {
     int32_t n_layers, d_model, n_heads, ffn, vocab;

@@ -72,6 +72,7 @@ void launch_tile_swiglu(const GemmTileArgs& t, bool f16, int ncu, hipStream_t st
 // The same for 17..80 rows (gemm_tile_few.hip); SwiGLU takes split activations.
 int launch_few_f32(const GemmTileArgs& t, bool f16, int ncu, int want_split, int max_split, hipStream_t stream);
 void launch_few_swiglu(const GemmTileArgs& t, bool f16, int ncu, hipStream_t stream);
+// topk <= 2
 void launch_few_head(const GemmTileArgs& t, bool f16, hipStream_t stream);
 void launch_tile_head(const GemmTileArgs& t, bool f16, int ncu, hipStream_t stream);
 // The same for t.W bf16 off the 16-byte grid, more than 80 rows (gemm_off_grid.hip).

@@ -7,8 +7,11 @@
 //   M <= 16   lm_head_kernel: every wavefront owns a contiguous chunk of the vocabulary, streams those rows of the
 //             head matrix once through the matrix cores against all verified rows and keeps the running statistics
 //             in registers (chunk = wavefront).
-//   M <= 80   the tiled GEMM with one row tile (chunk = a wave's 32 columns), which reads the head matrix once; with operands off
-//             the 16-byte grid the kernel of gemm_mid.h with its head epilogue (chunk = workgroup, 64 or 128 vocabulary entries).
+//   M <= 80   the head matrix is read once. k <= 2: the tiled GEMM with one row tile (chunk = a wave's 32 columns). Longer lists, or
+//             operands off the 16-byte grid: the kernel of gemm_mid.h with its head epilogue (chunk = workgroup, 64 or 128
+//             vocabulary entries, a quarter of the lists to keep and to merge). Head alone, us, k = 2 / 5: 72 rows x 32000 at a
+//             width of 2048 tiled 51 / 90, gemm_mid.h 54 / 78; 72 rows x 128256 at 4096 290 / 445 and 334 / 427; 17 rows x
+//             32000 at 2048 44 / 66 and 45 / 61.
 //   more      the LDS-tiled matrix-core GEMM of gemm_tile.h with its head epilogue (chunk = a wave's 128 columns); rows off
 //             the 16-byte grid are copied onto it first (1024 rows at a 128 k vocabulary: 1205 us, on the grid 1198).
 // Pass 2: a wavefront per row merges the per-chunk partials. The draft's rank is the number of partial-list entries
@@ -302,8 +305,8 @@ __global__ __launch_bounds__(256) void copy_rows_kernel(const uint16_t* __restri
 }
 
 // candidates -> pass 1 -> acceptance. Allocates nothing up to 80 rows. tokens / parent / n_nodes: the drafts as a pseudo-sequence
-// (parent == NULL: a chain, n_nodes = draft_len). few16: the fp16 copy of the head matrix for 17..80 rows, or NULL for the
-// caller's own matrix.
+// (parent == NULL: a chain, n_nodes = draft_len). few16: the fp16 copy of the head matrix for 17..80 rows and k <= 2, or NULL for
+// the caller's own matrix.
 static int run_head_bufs(Model* m, const uint16_t* few16, const uint16_t* h, const int32_t* tokens, const int32_t* parent, const int32_t* n_nodes, int B, int K,
                          int topk, float p, int mode, int32_t* accept_len, int32_t* out_tokens, int32_t* accept_path, float* logits_dbg,
                          const HeadBufs& hb, hipStream_t stream) {
@@ -318,7 +321,7 @@ static int run_head_bufs(Model* m, const uint16_t* few16, const uint16_t* h, con
         HeadArgs a{m->d.wlm, h, M, V, dm, tpw, hp};
         dim3 grid((unsigned)((m->head_chunks + 3) / 4), 1u);         // at most 16 rows: one row tile
         hipLaunchKernelGGL(lm_head_kernel<1>, grid, dim3(256), 0, stream, a);
-    } else if (M <= kHeadMidMaxRows && m->mid_waves == 0 && (few16 || on_16_byte_grid(m->d.wlm)) && on_16_byte_grid(h)) {
+    } else if (M <= kHeadMidMaxRows && topk <= 2 && m->mid_waves == 0 && (few16 || on_16_byte_grid(m->d.wlm)) && on_16_byte_grid(h)) {
         hp.chunks = (V + 31) / 32;
         GemmTileArgs t{few16 ? few16 : m->d.wlm, h, nullptr, M, V, dm, 0, 0, 1, nullptr, nullptr, hp};
         launch_few_head(t, few16 != nullptr, stream);

@@ -210,6 +210,21 @@ def test_head_of_17_to_80_rows(B, K, topk, copies):
     assert torch.equal(out[:, K // 2], want.view(B, K + 1, V)[:, K // 2].argmax(-1).to(torch.int32))
 
 
+@pytest.mark.parametrize("topk", [2, 3, 8])
+@pytest.mark.parametrize("B,K", [(1, 16), (8, 8), (8, 9)])
+def test_long_lists_of_17_to_80_rows(B, K, topk):
+    """Lists of more than two entries take the kernel that keeps them per workgroup (seen by the order of its sums: the logits are
+    those of option mid_waves bit for bit), shorter ones the tiled kernel."""
+    import paper_2408_05676_amd as laser
+    d, V = 2048, 4112
+    w, h = _head_case(d, V, B, K, topk, B)
+    drafts, n = torch.zeros((B, K), dtype=torch.int32, device="cuda"), torch.full((B,), K, dtype=torch.int32, device="cuda")
+    model = laser.Model(0, d, 16, 128, V, {"wlm": w}, B * (K + 1), B, 0)
+    got = laser.verify_head(model, h, drafts, n, topk, -1.0, 2, want_logits=True)[2]
+    model.set_option("mid_waves", 4)
+    assert torch.equal(got, laser.verify_head(model, h, drafts, n, topk, -1.0, 2, want_logits=True)[2]) == (topk > 2)
+
+
 @pytest.mark.parametrize("B,K", [(8, 8), (9, 10), (30, 12)])
 @pytest.mark.parametrize("topk", [1, 2, 3])
 def test_head_ties(B, K, topk):

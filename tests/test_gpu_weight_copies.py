@@ -70,6 +70,18 @@ def test_a_steps_head_on_the_copies(rows, topk):
     assert all(torch.equal(a, b) for a, b in zip(*got))
 
 
+@pytest.mark.parametrize("topk", [2, 3])
+def test_long_lists_read_the_callers_head_matrix(topk):
+    """A step of 17..80 rows after wlm was changed in place: with more than two entries to a list it sees the change, else the copy."""
+    sh = _shape()
+    w = gu.gpu_weights(sh)
+    model = _model(sh, w, 24)
+    new = {**w, "wlm": w["wlm"].flip(0).contiguous()}
+    before, after = _step(model, sh, 24, 7, topk)[2], _step(_model(sh, new, 24), sh, 24, 7, topk)[2]
+    w["wlm"].copy_(new["wlm"])
+    assert torch.equal(_step(model, sh, 24, 7, topk)[2], after if topk > 2 else before) and not torch.equal(before, after)
+
+
 @pytest.mark.parametrize("what", ["head 96", "step 24", "step 96"])
 def test_captured_graphs_after_the_option_is_set(what):
     """A graph keeps the addresses of the copies. Setting the option leaves their memory alone; the next call makes the copies
