@@ -3,6 +3,7 @@
 #include <algorithm>
 #include <cstring>
 
+#include "mfma.h"
 #include "state.h"
 
 namespace laser {
@@ -87,21 +88,48 @@ __global__ void ctx_advance_kernel(int32_t* ctx_tail, int32_t* pending, const in
     pending[b] = out[a];
 }
 
-// k, v: [n_tokens][H][dh] -> pages of one layer
-__global__ void kv_import_kernel(uint16_t* kpages, uint8_t* klpages, uint16_t* vpages, const int32_t* block_row,
-                                 const uint16_t* k, const uint16_t* v, int n_tokens, int H, int dh,
-                                 int layer, int n_pages) {
-    const size_t total = (size_t)n_tokens * H * dh;
-    size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= total) return;
-    const int c = (int)(i % dh);
-    const int h = (int)((i / dh) % H);
-    const int t = (int)(i / ((size_t)dh * H));
-    const int pg = block_row[t / kPageSize], tp = t % kPageSize;
+// k, v: [n_tokens][H][dh] -> pages of one layer. A thread takes eight channels of four tokens that share a page: pieces of 16 (keys),
+// 8 (their low plane) and, four tokens of a channel together, 8 bytes (values). Bound by the pieces it stores: element by element
+// 3000 tokens of 32 heads of 128 channels took 43 us, now 31.6; 500 tokens 9.8 and 8.8 (a launch).
+typedef unsigned u32x4_any __attribute__((ext_vector_type(4), aligned(2)));      // a caller's array may be aligned to its elements only
+__global__ __launch_bounds__(256) void kv_import_kernel(uint16_t* kpages, uint8_t* klpages, uint16_t* vpages, const int32_t* block_row,
+                                                        const uint16_t* k, const uint16_t* v, int n_tokens, int H, int dh,
+                                                        int layer, int n_pages) {
+    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int c = (int)(i % (dh / 8)) * 8;
+    const int h = (int)((i / (dh / 8)) % H);
+    const size_t t0 = i / ((size_t)(dh / 8) * H) * 4;
+    if (t0 >= (size_t)n_tokens) return;
+    const int n = min(4, n_tokens - (int)t0);
+    const int pg = block_row[t0 / kPageSize], tp = (int)(t0 % kPageSize);
     const size_t base = (((size_t)layer * n_pages + pg) * H + h) * kPageSize * dh;
-    kpages[base + page_k(tp, c)] = k[i];
-    klpages[base + page_kl(tp, c)] = 0;               // imported keys are plain fp16
-    vpages[base + page_v(tp, c)] = v[i];
+    Frag8 kt[4], vt[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {                     // (past the last token: that token again)
+        const size_t o = ((t0 + min(j, n - 1)) * H + h) * dh + c;
+        kt[j].v4 = *reinterpret_cast<const u32x4_any*>(k + o);
+        vt[j].v4 = *reinterpret_cast<const u32x4_any*>(v + o);
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+        if (j < n) {
+            *reinterpret_cast<u32x4*>(kpages + base + page_k(tp + j, c)) = kt[j].v4;
+            *reinterpret_cast<u32x2*>(klpages + base + page_kl(tp + j, c)) = u32x2{0, 0};     // imported keys are plain fp16
+        }
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        uint16_t* dst = vpages + base + page_v(tp, c + q);
+        if (n == 4) {
+            Frag4 f;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) f.h[j] = vt[j].h[q];
+            *reinterpret_cast<u32x2*>(dst) = f.v2;
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (j < n) dst[j] = vt[j].h[q];
+        }
+    }
 }
 
 }  // namespace laser
@@ -223,7 +251,7 @@ extern "C" int laser_kv_import(laser_kv* h, int seq, int layer, const uint16_t* 
                   "%d tokens exceed the capacity reserved for slot %d", n_tokens, seq);
     if (n_tokens == 0) return LASER_OK;
     LASER_REQUIRE(k && v, LASER_E_INVALID_ARG, "NULL k/v");
-    const size_t total = (size_t)n_tokens * kv->d.n_heads * kv->d.head_dim;
+    const size_t total = ((size_t)n_tokens + 3) / 4 * kv->d.n_heads * (kv->d.head_dim / 8);
     hipLaunchKernelGGL(kv_import_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, (hipStream_t)stream,
                        kv->kpages, kv->klpages, kv->vpages, kv->block_table + (size_t)seq * kv->d.max_pages_per_seq, k, v,
                        n_tokens, kv->d.n_heads, kv->d.head_dim, layer, kv->d.n_pages);

@@ -43,6 +43,34 @@ def test_imported_and_written_pages(heads, fused, ctx, K):
         assert ok, (step, err, ratio)
 
 
+@pytest.mark.parametrize("heads", [4, 2])
+@pytest.mark.parametrize("ctx,first", [(1, 1), (7, 3), (16, 5), (21, 6), (47, 33)])
+def test_import_off_the_grid_and_over_a_part(heads, ctx, first):
+    """Arrays aligned to their elements only give the same pages, and an import of the first tokens leaves the others as they are."""
+    import paper_2408_05676_amd as laser
+    sh = synth.SHAPES["tiny"].with_(d=256, n_heads=heads, ffn=640, vocab=512)
+    model = gu.make_model(sh, max_rows=4, max_batch=1, max_pos=128)
+    gen = torch.Generator(device="cuda").manual_seed(ctx)
+    k, v = torch.empty((2, sh.n_layers, ctx, heads, sh.head_dim), dtype=torch.float16, device="cuda").normal_(generator=gen)
+    tok, n = torch.full((1, 1), 7, dtype=torch.int32, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda")
+    got = []
+    for off in (0, 1, 3):
+        kv = gu.make_kv(sh, n_pages=4, max_seqs=1, max_pages_per_seq=4)
+        kv.reserve(0, ctx + 4)
+        for layer in range(sh.n_layers):
+            if off == 0:
+                kv.import_layer(0, layer, k[layer], v[layer])
+                continue
+            for count, scale in ((ctx, 1), (first, 2), (first, 1)):            # the first tokens: others over them, then the same again
+                a, b = (torch.empty(off + count * 256, dtype=torch.float16, device="cuda")[off:].view(count, heads, -1) for _ in range(2))
+                a.copy_(k[layer, :count] * scale)
+                b.copy_(v[layer, :count] * scale)
+                kv.import_layer(0, layer, a, b)
+        kv.set_len(0, ctx)
+        got.append(laser.verify_step(model, kv, [0], tok[:, 0].contiguous(), tok[:, :0].contiguous(), n, 1, -1.0, 0, want_logits=True)[2].clone())
+    assert torch.equal(got[0], got[1]) and torch.equal(got[0], got[2])
+
+
 @pytest.mark.parametrize("rows", [4, 24, 96])
 def test_weights_changed_in_place_are_seen_after_the_option_is_set(rows):
     """A step before and after: the fp16 copies are made anew, and without copies the weights are the caller's own."""
