@@ -256,15 +256,10 @@ __global__ __launch_bounds__(64) void retrieve_kernel(RetrieveArgs a) {
         bool in_lds = count <= (uint32_t)kCand;
         uint32_t m = count;
         if (in_lds)
-            for (uint32_t i0 = lane; i0 < count; i0 += 64 * kGroups) {
-                uint32_t e[kGroups], end[kGroups];
-#pragma unroll
-                for (int u = 0; u < kGroups; ++u) e[u] = i0 + u * 64 < count ? a.sa[start + i0 + u * 64] : 0u;
-#pragma unroll
-                for (int u = 0; u < kGroups; ++u) end[u] = i0 + u * 64 < count ? a.seq_end[e[u]] : 0u;
-#pragma unroll
-                for (int u = 0; u < kGroups; ++u)
-                    if (i0 + u * 64 < count) { cand[i0 + u * 64] = e[u]; cand_end[i0 + u * 64] = end[u]; }
+            for (uint32_t i = lane; i < count; i += 64) {         // (four groups requested together held up lookups of few by 3 %)
+                const uint32_t e = a.sa[start + i];
+                cand[i] = e;
+                cand_end[i] = a.seq_end[e];
             }
         __syncthreads();
 
