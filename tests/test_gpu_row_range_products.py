@@ -108,9 +108,12 @@ def test_every_tile_above_80_rows(tile, B, K, copies):
 
 @pytest.mark.parametrize("tile", [1, 2, 3])
 @pytest.mark.parametrize("B,K", [(1, 16), (4, 7), (3, 10), (4, 11), (7, 8), (5, 12), (8, 8), (10, 7)])
-def test_every_tile_of_17_to_80_rows(tile, B, K):
+@pytest.mark.parametrize("copies", [1, 0])
+def test_every_tile_of_17_to_80_rows(tile, B, K, copies):
+    """With weights from the fp16 copies and from the caller's own."""
     sh = _tile_shape()
     model = gu.make_model(sh, max_rows=80, max_batch=16, max_pos=256)
+    model.set_option("f16_copies", copies)
     model.set_option("tile", tile)
     got = _step(model, sh, B, K)
     model.set_option("mid_waves", 4)
@@ -141,12 +144,6 @@ def test_every_tile_of_the_head(tile, topk, copies, B, K):
     assert (acc == K // 2).all()
     assert torch.equal(out[:, :K // 2], drafts[:, :K // 2])
     assert torch.equal(out[:, K // 2], want.view(B, K + 1, V)[:, K // 2].argmax(-1).to(torch.int32))
-
-
-@pytest.mark.parametrize("B,K", [(7, 12), (16, 25)])
-def test_tile_of_128_rows_and_192_columns(B, K):
-    """The entry of the plain table behind those above, as they are tested."""
-    test_every_tile_above_80_rows(14, B, K, 1)
 
 
 @pytest.mark.parametrize("d,heads,ffn", [(128, 2, 128), (640, 5, 1920)])
@@ -192,7 +189,8 @@ def _head_case(d, V, B, K, topk, seed):
 @pytest.mark.parametrize("copies", [1, 0])
 @pytest.mark.parametrize("B,K", [(1, 16), (4, 7), (3, 10), (6, 7), (9, 7), (8, 9)])
 def test_head_of_17_to_80_rows(B, K, topk, copies):
-    """Logits against a float64 product; drafts of rank topk - 1 pass, the one of rank topk does not."""
+    """Logits against a float64 product; drafts of rank topk - 1 pass, the one of rank topk does not. (The head alone reads the caller's
+    matrix here whatever the option says; a step's head on the copies: test_gpu_weight_copies.py.)"""
     import paper_2408_05676_amd as laser
     d, V = 256, 1040
     w, h = _head_case(d, V, B, K, topk, B)
