@@ -11,8 +11,8 @@ struct GemmTileShape { int wm, wn; };                   // 16-row and 16-column 
 // and took 172 of {4, 8}, 60.6 us -> 52.9). The first entries also exist for bf16 weights.
 constexpr GemmTileShape kTilePlain[] = {{3, 4}, {4, 4}, {5, 4}, {6, 6}, {11, 6}, {5, 2}, {3, 8}, {4, 8}, {5, 8}, {6, 4}, {8, 4}, {8, 8}, {11, 4}, {4, 6}};
 constexpr GemmTileShape kTileSplit[] = {{3, 4}, {4, 4}, {5, 4}, {6, 6}, {3, 6}, {4, 6}, {5, 6}, {6, 4}, {8, 4}};
-// The head's record is 128 columns: wn = 8. {8, 8} spills 196 bytes a lane in its epilogue (no other tile uses scratch); the
-// 1024-row head takes 1.25 ms with it.
+// The head's record is 128 columns: wn = 8. {8, 8} spills 72 bytes a lane in its two-entry epilogue (no other tile uses
+// scratch); the 1024-row head at a vocabulary of 128256 takes 1.00 ms with it.
 constexpr GemmTileShape kTileHead[] = {{4, 8}, {6, 8}, {3, 8}, {8, 8}};
 constexpr int kTilePlainCommon = 5, kTileSplitCommon = 4, kTileHeadCommon = 2;
 
