@@ -32,8 +32,8 @@ struct GemmTilePlan { int v, S; };
 // One workgroup per compute unit at a time. Cycles of a reduction step of one workgroup: its matrix instructions (16 each) plus
 // 17 for each kilobyte it stages; 8000 for a workgroup's start and epilogue; a reduction part more costs a write
 // and a read of the output. Against every tile in turn at 96, 136, 256, 352, 512 and 704 rows of the 7B and 1B widths the one
-// taken is the best or within 10 % of it in 46 of 48 products (QKV at 704 rows 119.5 us of 119.5 .. 167, gate/up 108 of 108 ..
-// 183); the others are the down product at 352 rows (51.6 us, 6 x 4 takes 41.5) and 512 rows (60.4, 8 x 4 takes 48.6).
+// taken is the best or within 10 % of it in all 48 products (QKV at 704 rows 118.7 us of 118.7 .. 168, gate/up 107.6 of 107.6 ..
+// 179, down at 352 rows 45.4, 8 tiles of 44.0 .. 51 beside it, at 512 rows 55.7 of 51.8 .. 76).
 template <int NV>
 inline GemmTilePlan gemm_tile_plan(const GemmTileShape (&shapes)[NV], int nv, const GemmTileArgs& t, bool swiglu, bool split, int ncu,
                                    int want_split, int max_split) {

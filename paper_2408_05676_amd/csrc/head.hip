@@ -13,7 +13,7 @@
 //             width of 2048 tiled 51 / 90, gemm_mid.h 54 / 78; 72 rows x 128256 at 4096 290 / 445 and 334 / 427; 17 rows x
 //             32000 at 2048 44 / 66 and 45 / 61.
 //   more      the LDS-tiled matrix-core GEMM of gemm_tile.h with its head epilogue (chunk = a wave's 128 columns); rows off
-//             the 16-byte grid are copied onto it first (1024 rows at a 128 k vocabulary: 1205 us, on the grid 1198).
+//             the 16-byte grid are copied onto it first (1024 rows at a 128 k vocabulary: 943..958 us, on the grid 942..952).
 // Pass 2: a wavefront per row merges the per-chunk partials. The draft's rank is the number of partial-list entries
 // ordered before it; if a chunk hides an entry that precedes the draft, that chunk already contributes
 // >= LASER_MAX_TOPK >= k listed ones, so "rank < k" is exact. A wavefront per sequence then examines the nodes
