@@ -340,7 +340,9 @@ __global__ __launch_bounds__(64) void retrieve_kernel(RetrieveArgs a) {
             const uint32_t voters = (in_lds ? m : count) + mo;
             int vsz = 64;
             while (vsz < kVote && (uint32_t)vsz < 4u * voters) vsz *= 2;
-            // The vote may need several passes when too many distinct successors show up.
+            // The vote may need several passes when too many distinct successors show up. Splitting ends: the finest part is 512 neighbouring
+            // hash values, and no such 512 belong to more than 318 tokens (counted over all; 1024 belong to up to 597, which would
+            // not fit: the divisor stays kVote beside the larger table, too).
             for (uint32_t nparts = 1; open;) {
                 // distinct tokens beyond which a vote pass is repeated, with the larger table or split; a slot for every voter is enough
                 const int vfill = (uint32_t)vsz >= voters ? vsz : vsz / 4 * 3;
@@ -391,7 +393,7 @@ __global__ __launch_bounds__(64) void retrieve_kernel(RetrieveArgs a) {
                             }
                             if (ok[u]) {
                                 uint32_t hh = fmix32((uint32_t)tok[u]);
-                                if (nparts == 1 || (hh / kTable) % nparts == part) {
+                                if (nparts == 1 || (hh / kVote) % nparts == part) {
                                     uint32_t s = hh & (vsz - 1);
                                     for (int probe = 0; probe < vsz; ++probe) {
                                         int cur = vote_tok[s];

@@ -28,6 +28,46 @@ def test_votes_over_many_tokens(count, agree, spread):
     compare_pool(pool[0], pool[1], pool[2], [3, 3], [[1, 7], [1, 7]], 1, 2, 16)
 
 
+def _tokens_of_hashes(first, count):
+    """The tokens (>= 0) whose hash in the vote table is one of `count` neighbouring values: the mixer's inverse."""
+    h = np.arange(first, first + count, dtype=np.uint64)
+    mask = np.uint64(0xFFFFFFFF)
+    for shift, factor in ((16, 0xC2B2AE35), (13, 0x85EBCA6B), (16, None)):
+        x = h
+        for _ in range(32 // shift):
+            x = h ^ (x >> np.uint64(shift))
+        h = x if factor is None else (x * np.uint64(pow(factor, -1, 1 << 32))) & mask
+    return h[h < 1 << 31].astype(np.int64)
+
+
+def test_tokens_of_hashes():
+    t = _tokens_of_hashes(5 << 10, 1024).astype(np.uint64)
+    mask = np.uint64(0xFFFFFFFF)
+    h = t ^ (t >> np.uint64(16))
+    h = (h * np.uint64(0x85EBCA6B)) & mask
+    h ^= h >> np.uint64(13)
+    h = (h * np.uint64(0xC2B2AE35)) & mask
+    h ^= h >> np.uint64(16)
+    assert len(t) > 400 and (h >> np.uint64(10) == 5).all()
+
+
+@pytest.mark.parametrize("form", ["pool", "own"])
+@pytest.mark.parametrize("count", [900, 1024, 1025, 1600])
+def test_votes_over_tokens_that_share_their_upper_hash_bits(count, form):
+    """More different successors than the table may hold, all with the same upper bits: parts of the vote by those bits alone would never
+    be small enough."""
+    rng = np.random.default_rng(count)
+    tokens = _tokens_of_hashes(5 << 10, 1024)
+    pick = np.concatenate([tokens, rng.choice(tokens, count - len(tokens))])
+    toks = np.stack([np.full(count, 7), pick, pick[::-1]], 1).reshape(-1).astype(np.int32)
+    off, keys = np.arange(count + 1, dtype=np.int64) * 3, np.full(count, 3, dtype=np.int64)
+    if form == "pool":
+        compare_pool(toks, off, keys, [3, 3], [[1, 7], [1, 7]], 1, 2, 3)
+    else:
+        own = np.stack([np.full(300, 7), rng.choice(tokens, 300)], 1).reshape(-1).tolist() + [5, 7]
+        compare_own(toks, off, keys, [3, 3], [own, [5, 7]], 1, 2, 3)
+
+
 @pytest.mark.parametrize("count", [400, 1000, 1020, 1024])
 def test_pool_and_own_text_beyond_four_waves(count):
     rng = np.random.default_rng(count)
